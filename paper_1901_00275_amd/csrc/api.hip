@@ -1001,12 +1001,12 @@ static int search_impl(vlq_index *idx, const float *d_q, int32_t nq, int32_t w1,
         }
         {
             StageTimer t(idx, s, VLQ_STAGE_SUBREGIONS, timed);
-            // the streaming scan takes the visited sub-regions from desc alone, in any order
+            // the scans with one table per query take the visited sub-regions from desc alone, in any order
             const bool stream = scan_will_stream(scan_args(c));
             launch_subregions(q, nqp, D, idx->C, idx->S, idx->E, n, k, c.cells, c.cell_dist, w1, w2, idx->qlam_lo,
                               idx->qlam_hi, d_sub ? d_sub + (int64_t)c.q0 * w2 : nullptr,
                               d_sub_score ? d_sub_score + (int64_t)c.q0 * w2 : nullptr, stream ? nullptr : c.slab,
-                              stream ? nullptr : c.sg, idx->off, c.desc, c.nws, pairs_counted, s);
+                              stream ? nullptr : c.sg, idx->off, c.desc, scan_takes_labels(scan_args(c)), c.nws, pairs_counted, s);
         }
         LAUNCHCHK();
         if (d_cells)

@@ -236,7 +236,8 @@ void launch_select_cells(const float *dist, int64_t ld, int rows, int k, const f
 
 // Line scores of the w1*n sub-regions of the probed cells and the w2 best of them; the query's
 // lambda is restricted to [lam_min, lam_max] (-inf / +inf: the whole line).
-// desc (optional): per visited sub-region {list begin, list length, a, b - a} for the streaming scan.
+// desc (optional): per visited sub-region {list begin, list length, a, b - a} for the streaming scan, or with
+// desc_labels {label, 1, a, g}; a zero second word where fewer than w2 sub-regions exist.
 // ws (optional, neighbour_dists_workspace() bytes): the distances to the neighbour centroids are
 // then computed cell by cell over the whole batch first; neighbour_dists_by_cell() says when
 // that pays.
@@ -260,7 +261,8 @@ void launch_pair_counts_zero(const PairWs &pw, int k, hipStream_t st);
 void launch_subregions(const float *Q, int nq, int D, const float *C, const int32_t *S, const float *E,
                        int n, int k, const int32_t *cells, const float *cell_dist, int w1, int w2,
                        float lam_min, float lam_max, int32_t *sub, float *sub_score, int32_t *scan_label,
-                       float *scan_g, const int64_t *off, uint4 *desc, void *ws, bool pairs_counted, hipStream_t st);
+                       float *scan_g, const int64_t *off, uint4 *desc, bool desc_labels, void *ws, bool pairs_counted,
+                       hipStream_t st);
 
 struct ScanArgs {
     const float *Q;
@@ -276,7 +278,7 @@ struct ScanArgs {
     const float *sx;   // per point: query-independent part of the distance (streaming scan)
     const float *mu;   // [D] the vector both s_x and the query's table are taken relative to
     float lam_step, lam_zero;
-    const uint4 *desc; // [nq x w2] {begin, length, a, b - a} per visited sub-region (streaming scan)
+    const uint4 *desc; // [nq x w2] {begin, length, a, b - a} per visited sub-region, or {label, 1, a, g}: scan_takes_labels
     int packed;        // streaming scan: short lists, several per chunk of lanes
     bool force_generic; // the 2m-lookup kernel whatever the shape
     const int32_t *scan_label;
@@ -287,8 +289,11 @@ struct ScanArgs {
 };
 void launch_scan(const ScanArgs &a, hipStream_t st);
 bool scan_stream_supported(const ScanArgs &a);
-bool scan_will_stream(const ScanArgs &a); // the choice launch_scan is going to make
+bool scan_will_stream(const ScanArgs &a); // launch_scan is going to take the lists from desc, in any order
 void launch_scan_stream(const ScanArgs &a, hipStream_t st);
+bool scan_wide_supported(const ScanArgs &a);
+bool scan_takes_labels(const ScanArgs &a); // ... in their {label, 1, a, g} form
+void launch_scan_wide(const ScanArgs &a, hipStream_t st);
 void launch_merge(const uint64_t *partial, int nq, int nsplit, int K, float *out_dist, int32_t *out_ids,
                   hipStream_t st);
 int scan_pick_nsplit(int nq, int w2, int K);

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void k_subregions(const float *__restrict__ Q,
                                                     int32_t *__restrict__ scan_label,
                                                     float *__restrict__ scan_g,
                                                     const int64_t *__restrict__ off,
-                                                    uint4 *__restrict__ desc,
+                                                    uint4 *__restrict__ desc, int desc_labels,
                                                     const float *__restrict__ bpre)
 {
     extern __shared__ unsigned char smem[];
@@ -348,6 +348,7 @@ __global__ __launch_bounds__(256) void k_subregions(const float *__restrict__ Q,
                 const float g = lean ? bpre[(int64_t)q * total + t] : bval[t];
                 // b - a = c - 2 g
                 dsc = make_uint4((uint32_t)b0, (uint32_t)(b1 - b0), __float_as_uint(a), __float_as_uint(fmaf(-2.f, g, E[label])));
+                if (desc_labels) dsc = make_uint4((uint32_t)label, 1u, __float_as_uint(a), __float_as_uint(g));
             }
             desc[(int64_t)q * w2 + r] = dsc;
         }
@@ -398,6 +399,7 @@ __global__ __launch_bounds__(256) void k_subregions(const float *__restrict__ Q,
             if (desc) {
                 const int64_t b0 = off[label], b1 = off[label + 1];
                 dsc = make_uint4((uint32_t)b0, (uint32_t)(b1 - b0), __float_as_uint(a), __float_as_uint(fmaf(-2.f, g, E[label])));
+                if (desc_labels) dsc = make_uint4((uint32_t)label, 1u, __float_as_uint(a), __float_as_uint(g));
             }
         }
         if (desc) desc[(int64_t)q * w2 + r] = dsc;
@@ -433,7 +435,7 @@ __global__ __launch_bounds__(256) void k_subregions_lean(const float *__restrict
                                                          const float *__restrict__ cell_dist, int w1, int w2,
                                                          float lam_min, float lam_max,
                                                          const int64_t *__restrict__ off,
-                                                         uint4 *__restrict__ desc,
+                                                         uint4 *__restrict__ desc, int desc_labels,
                                                          const float *__restrict__ bpre)
 {
     extern __shared__ uint32_t picked[]; // [w2] {label, b - a, probed cell} of the selected sub-regions
@@ -444,7 +446,7 @@ __global__ __launch_bounds__(256) void k_subregions_lean(const float *__restrict
     const int total = w1 * n;
     uint32_t o[KPT];     // ordered score bits; 0xFFFFFFFF = no sub-region
     uint32_t label[KPT];
-    float bma[KPT];      // b - a = c - 2 g for the scan
+    float bma[KPT];      // b - a = c - 2 g for the scan (g itself with desc_labels)
     const int tb = tid * KPT;
     {
         // all loads without branches (indices clamped), so that they are in flight together
@@ -474,7 +476,7 @@ __global__ __launch_bounds__(256) void k_subregions_lean(const float *__restrict
             label[e] = ok ? (uint32_t)(ci[e] * n + (t - (t / n) * n)) : 0xFFFFFFFFu;
             // (a score whose pattern is all ones would count as absent below: one step down keeps it present)
             o[e] = ok ? min(f2ord(score), 0xFFFFFFFEu) : 0xFFFFFFFFu;
-            bma[e] = fmaf(-2.f, gv[e], c);
+            bma[e] = desc_labels ? gv[e] : fmaf(-2.f, gv[e], c);
         }
     }
     // sum of a wave-uniform count over the four waves; `round` alternates the LDS slots, so one
@@ -554,8 +556,8 @@ __global__ __launch_bounds__(256) void k_subregions_lean(const float *__restrict
         for (int u = 0; u < 4; ++u) {
             const int r = r0 + 256 * u;
             lb[u] = r < w2eff ? picked[3 * r] : 0u;
-            b0[u] = off[lb[u]];
-            b1[u] = off[lb[u] + 1];
+            b0[u] = desc_labels ? (int64_t)lb[u] : off[lb[u]];
+            b1[u] = desc_labels ? b0[u] + 1 : off[lb[u] + 1];
             a[u] = cell_dist[(int64_t)q * w1 + (r < w2eff ? picked[3 * r + 2] : 0u)];
         }
 #pragma unroll
@@ -876,7 +878,8 @@ void launch_pair_counts_zero(const PairWs &pw, int k, hipStream_t st)
 void launch_subregions(const float *Q, int nq, int D, const float *C, const int32_t *S, const float *E,
                        int n, int k, const int32_t *cells, const float *cell_dist, int w1, int w2,
                        float lam_min, float lam_max, int32_t *sub, float *sub_score, int32_t *scan_label,
-                       float *scan_g, const int64_t *off, uint4 *desc, void *ws, bool pairs_counted, hipStream_t st)
+                       float *scan_g, const int64_t *off, uint4 *desc, bool desc_labels, void *ws, bool pairs_counted,
+                       hipStream_t st)
 {
     if (nq <= 0) return;
     const float *bpre = nullptr;
@@ -916,20 +919,21 @@ void launch_subregions(const float *Q, int nq, int D, const float *C, const int3
         const size_t pk = (size_t)w2 * 12;
         if (total <= 1024)
             hipLaunchKernelGGL(k_subregions_lean<4>, dim3((unsigned)nq), dim3(256), pk, st, E, n, cells, cell_dist, w1, w2,
-                               lam_min, lam_max, off, desc, bpre);
+                               lam_min, lam_max, off, desc, (int)desc_labels, bpre);
         else if (total <= 2048)
             hipLaunchKernelGGL(k_subregions_lean<8>, dim3((unsigned)nq), dim3(256), pk, st, E, n, cells, cell_dist, w1, w2,
-                               lam_min, lam_max, off, desc, bpre);
+                               lam_min, lam_max, off, desc, (int)desc_labels, bpre);
         else
             hipLaunchKernelGGL(k_subregions_lean<16>, dim3((unsigned)nq), dim3(256), pk, st, E, n, cells, cell_dist, w1, w2,
-                               lam_min, lam_max, off, desc, bpre);
+                               lam_min, lam_max, off, desc, (int)desc_labels, bpre);
         return;
     }
     size_t smem = lean ? (size_t)sz * (8 + 4) : (size_t)sz * (8 + 4 + 2 + 4) + (size_t)D * 4;
     if (smem > 49152) // (48 KB of dynamic LDS beside the static part need no asking)
         (void)hipFuncSetAttribute((const void *)k_subregions, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     hipLaunchKernelGGL(k_subregions, dim3((unsigned)nq), dim3(256), smem, st, Q, D, C, S, E, n, cells,
-                       cell_dist, w1, w2, lam_min, lam_max, sz, sub, sub_score, scan_label, scan_g, off, desc, bpre);
+                       cell_dist, w1, w2, lam_min, lam_max, sz, sub, sub_score, scan_label, scan_g, off, desc,
+                       (int)desc_labels, bpre);
 }
 
 // ---------------------------------------------------------------------------
@@ -1119,13 +1123,22 @@ int scan_pick_nsplit(int nq, int w2, int K)
     return ns;
 }
 
-bool scan_will_stream(const ScanArgs &a) { return !a.force_generic && scan_stream_supported(a); }
+// Which scan: up to 128 results of 8- or 16-byte codes by k_scan_stream, every other shape by k_scan_wide; the
+// 2m-lookup scan below is for VLQ_OPT_SCAN_GENERIC and for indexes without points.
+bool scan_will_stream(const ScanArgs &a)
+{
+    return !a.force_generic && (scan_stream_supported(a) || scan_wide_supported(a));
+}
+bool scan_takes_labels(const ScanArgs &a) { return scan_will_stream(a) && !scan_stream_supported(a); }
 
 void launch_scan(const ScanArgs &a, hipStream_t st)
 {
     if (a.nq <= 0) return;
     if (scan_will_stream(a)) {
-        launch_scan_stream(a, st);
+        if (scan_stream_supported(a))
+            launch_scan_stream(a, st);
+        else
+            launch_scan_wide(a, st);
         return;
     }
     int KP, SZ;

@@ -1,0 +1,68 @@
+"""The scan for K > 128 and for code lengths other than 8 and 16 against the 2m-lookup scan: many turns of the
+workgroup (the candidate buffer is cut several times), one point per list, one long list, K at its limits, split
+queries, and points that coincide in distance and id (more of them than the candidate buffer holds)."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_parity import DEV, dev, gpu_search, make_index, vlq  # noqa: F401  (vlq: fixture)
+from util import problem
+
+pytestmark = pytest.mark.gpu
+
+
+def both_scans(vlq, idx, Y, w1, w2, K):  # noqa: F811
+    out = []
+    for generic in (1, 0):
+        vlq.vlq_index_set_option(idx, vlq.VLQ_OPT_SCAN_GENERIC, generic)
+        out.append(gpu_search(vlq, idx, Y, w1, w2, K)[:2])
+    return out
+
+
+def add(vlq, idx, pr, N, cells, ids=None, same=False, seed=0):  # noqa: F811
+    rng = np.random.default_rng(seed)
+    cell = rng.integers(0, cells, N).astype(np.int32)
+    edge = rng.integers(0, pr.n, N).astype(np.int32)
+    lam = rng.integers(60, 256, N).astype(np.uint8)
+    codes = rng.integers(0, 256, (N, pr.m)).astype(np.uint8)
+    if same:
+        cell[:], edge[:], lam[:], codes[:] = 0, 0, 100, 7
+    vlq.vlq_index_add_encoded(idx, dev(cell), dev(edge), dev(lam), dev(codes), None if ids is None else dev(ids), N)
+    vlq.vlq_index_finalize(idx)
+
+
+@pytest.mark.parametrize(
+    "m,D,K,N,cells,nq",
+    [(8, 32, 129, 60_000, 32, 40), (8, 128, 1000, 60_000, 32, 40), (16, 96, 1024, 60_000, 32, 3), (10, 60, 1, 20_000, 32, 33),
+     (10, 60, 1000, 50_000, 32, 1500), (20, 100, 128, 30_000, 32, 20), (5, 35, 200, 30_000, 32, 20), (1, 3, 300, 5_000, 32, 20),
+     (32, 128, 100, 30_000, 32, 20), (64, 128, 1024, 30_000, 32, 20), (8, 32, 1000, 40, 32, 20), (8, 32, 500, 30_000, 1, 1)])
+def test_wide_scan_equals_generic(vlq, m, D, K, N, cells, nq):  # noqa: F811
+    pr = problem(N=2000, k=32, n=4, m=m, G=16, nq=nq, D=D, iters=1)
+    idx = make_index(vlq, pr)
+    try:
+        add(vlq, idx, pr, N, cells)
+        (dg, ig), (dw, iw) = both_scans(vlq, idx, pr.Y, 16, 60, K)
+        # the result's distances are the 2m-lookup scan's own, bit for bit
+        assert np.array_equal(dg, dw) and np.array_equal(ig, iw)
+    finally:
+        vlq.vlq_index_free(idx)
+
+
+@pytest.mark.parametrize("same_ids", [False, True])
+@pytest.mark.parametrize("K", [129, 1000])
+def test_coinciding_points(vlq, K, same_ids):  # noqa: F811
+    """30 000 copies of one point: the smallest ids stay; with one id for all of them, K times that id."""
+    pr = problem(N=2000, k=32, n=4, m=8, G=16, nq=40, D=32, iters=1)
+    idx = make_index(vlq, pr)
+    try:
+        N = 30_000
+        ids = np.full(N, 5, np.int32) if same_ids else np.random.default_rng(1).permutation(N).astype(np.int32)
+        add(vlq, idx, pr, N, 1, ids=ids, same=True)
+        d, i = (torch.empty(40, K, device=DEV), torch.empty(40, K, dtype=torch.int32, device=DEV))
+        vlq.vlq_search(idx, dev(pr.Y), 40, 32, 128, K, d, i)
+        torch.cuda.synchronize()
+        d, i = d.cpu().numpy(), i.cpu().numpy()
+        assert (d == d[:, :1]).all() and np.isfinite(d).all()
+        assert (i == (5 if same_ids else np.arange(K))).all()
+    finally:
+        vlq.vlq_index_free(idx)
