@@ -480,6 +480,27 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
     int shift = 62;
     while (shift > 0 && ((int64_t)1 << (62 - shift)) < nt) --shift;
 
+    if (lloyd_lanes_supported(D, k)) { // small codebooks of few dimensions: both halves in one pass
+        DevBuf small;
+        uint64_t *part;
+        uint32_t *amax;
+        HIPCHK(small.get(&part, lloyd_lanes_words(nt, D, k)));
+        HIPCHK(small.get(&amax, 64));
+        HIPCHK(hipMemsetAsync(amax, 0, 4, st));
+        launch_absmax(d_x, nt * D, amax, st);
+        LAUNCHCHK();
+        for (int it = 0; it < iters; ++it) {
+            launch_lloyd_lanes(d_x, nt, D, k, d_centroids, amax, shift, true, part, nullptr, nullptr, st);
+            LAUNCHCHK();
+        }
+        if (d_assign || d_counts) {
+            launch_lloyd_lanes(d_x, nt, D, k, d_centroids, amax, shift, false, part, d_assign, d_counts, st);
+            LAUNCHCHK();
+        }
+        HIPCHK(hipStreamSynchronize(st)); // the temporaries are freed on return
+        return VLQ_OK;
+    }
+
     DevBuf buf;
     float *xn, *cn, *mu, *mu_c, *xc = nullptr, *cc = nullptr;
     uint64_t *cand;
