@@ -296,6 +296,7 @@ bool scan_takes_labels(const ScanArgs &a); // ... in their {label, 1, a, g} form
 void launch_scan_wide(const ScanArgs &a, hipStream_t st);
 void launch_merge(const uint64_t *partial, int nq, int nsplit, int K, float *out_dist, int32_t *out_ids,
                   hipStream_t st);
+#define SCAN_MAX_SPLIT 16 // workgroups per query
 int scan_pick_nsplit(int nq, int w2, int K);
 
 struct EncodeArgs {

@@ -1110,6 +1110,9 @@ static void scan_sizes(int K, int *KP, int *SZ)
     *SZ = sz;
 }
 
+// At most SCAN_MAX_SPLIT workgroups per query.  (64 were measured: one query of 100 M points scans in 16 us instead of
+// 20, but seventeen queries of 10 M points in 33 us instead of 21, lists of 19 points being too few to lay end to end,
+// and the merge of 64 lists takes back more than the scan gains.)
 int scan_pick_nsplit(int nq, int w2, int K)
 {
     // aim at >= 4 workgroups per compute unit (256 CUs); never more splits than lists
@@ -1118,7 +1121,7 @@ int scan_pick_nsplit(int nq, int w2, int K)
     const int kp = next_pow2(K);
     const int cap = 8192 / kp; // the merge holds nsplit * K keys in LDS
     if (ns > cap) ns = cap;
-    if (ns > 16) ns = 16;
+    if (ns > SCAN_MAX_SPLIT) ns = SCAN_MAX_SPLIT;
     if (ns < 1) ns = 1;
     return ns;
 }
@@ -1154,39 +1157,128 @@ void launch_scan(const ScanArgs &a, hipStream_t st)
 // merged order is its position in its own list plus the number of keys that precede it in every
 // other list (a binary search each): no sorting.  Equal keys (possible only when the caller's ids
 // repeat) are ordered by list, so that every place is taken once.
-__global__ __launch_bounds__(256) void k_merge(const uint64_t *__restrict__ partial, int nsplit, int K,
-                                               float *__restrict__ out_dist, int32_t *__restrict__ out_ids)
+//
+// What bounds it is the chain of dependent LDS reads, so few keys may reach the ranking: a depth j with
+// v_j = the ceil(K / j)-th smallest among the lists' j-th keys has at least K keys at or below v_j, a
+// wave tries one depth each, and only the lists' prefixes up to the smallest v_j are read and ranked
+// (seventeen queries, K = 100: 53 us when all 1 600 keys were ranked, 14 us so).  Up to MERGE_FEW keys there is a
+// thread for each and nothing to gain by a cut (16 lists of 10: 8.9 us with it, 6.6 us without).
+#define MERGE_FEW 256
+
+// keys of the sorted list l [n] that precede x: smaller ones and, with or_equal, equal ones; top is the largest
+// power of two within the longest list
+__device__ __forceinline__ int merge_before(const uint64_t *l, int n, uint64_t x, bool or_equal, int top)
 {
-    extern __shared__ unsigned char smem[];
-    uint64_t *keys = (uint64_t *)smem; // [nsplit][K]
-    uint64_t *outk = keys + nsplit * K; // [K]
-    const int tid = threadIdx.x, q = blockIdx.x;
-    const int total = nsplit * K;
-    for (int i = tid; i < total; i += 256) keys[i] = partial[(int64_t)q * total + i];
-    for (int i = tid; i < K; i += 256) outk[i] = KEY_MAX;
+    const uint64_t lim = x + (or_equal ? 1 : 0);
+    int pos = 0;
+    for (int st = top; st > 0; st >>= 1) {
+        const int at = pos + st;
+        if (at <= n && l[at - 1] < lim) pos = at;
+    }
+    return pos;
+}
+
+__global__ __launch_bounds__(MERGE_FEW) void k_merge_few(const uint64_t *__restrict__ partial, int nsplit, int K,
+                                                         float *__restrict__ out_dist, int32_t *__restrict__ out_ids)
+{
+    __shared__ uint64_t keys[MERGE_FEW], outk[MERGE_FEW];
+    const int tid = threadIdx.x, q = blockIdx.x, total = nsplit * K;
+    const uint64_t x = tid < total ? partial[(int64_t)q * total + tid] : KEY_MAX;
+    keys[tid] = x;
+    outk[tid] = KEY_MAX;
     __syncthreads();
-    for (int e = tid; e < total; e += 256) {
-        const uint64_t x = keys[e];
-        if (x == KEY_MAX) continue;
-        const int s = e / K;
-        int rank = e - s * K;
-        for (int o = 0; o < nsplit && rank < K; ++o) {
-            if (o == s) continue;
-            const uint64_t *l = keys + o * K;
-            int lo = 0, hi = K; // keys of list o that precede x: smaller ones, and equal ones of earlier lists
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (l[mid] < x || (o < s && l[mid] == x))
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            rank += lo;
+    if (x != KEY_MAX) {
+        const int s = tid / K, top = 1 << (31 - __clz(K));
+        int rank = tid - s * K;
+#pragma unroll 4
+        for (int o = 0; o < nsplit; ++o) {
+            const int pos = merge_before(keys + o * K, K, x, o < s, top);
+            rank += o == s ? 0 : pos;
         }
         if (rank < K) outk[rank] = x;
     }
     __syncthreads();
-    for (int i = tid; i < K; i += 256) {
+    if (tid < K) {
+        const uint64_t key = outk[tid];
+        const bool ok = key != KEY_MAX;
+        out_dist[(int64_t)q * K + tid] = ok ? ord2f((uint32_t)(key >> 32)) : INFINITY;
+        out_ids[(int64_t)q * K + tid] = ok ? (int32_t)(uint32_t)key : -1;
+    }
+}
+__global__ __launch_bounds__(1024) void k_merge(const uint64_t *__restrict__ partial, int nsplit, int K,
+                                                float *__restrict__ out_dist, int32_t *__restrict__ out_ids)
+{
+    extern __shared__ unsigned char smem[];
+    uint64_t *keys = (uint64_t *)smem; // [nsplit][K]
+    uint64_t *outk = keys + nsplit * K; // [K]
+    __shared__ uint64_t depth_cut[16];
+    __shared__ int len[SCAN_MAX_SPLIT], first[SCAN_MAX_SPLIT + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.x;
+    const int nt = blockDim.x, nw = nt >> 6;
+    const uint64_t *src = partial + (int64_t)q * nsplit * K;
+    for (int i = tid; i < K; i += nt) outk[i] = KEY_MAX;
+    {
+        const int j0 = (K + nsplit - 1) / nsplit; // ceil(K / j0) <= nsplit
+        const int j = min(K, j0 + wave * ((j0 + 1) / 2));
+        const int need = (K + j - 1) / j;
+        const uint64_t v = lane < nsplit ? src[lane * K + j - 1] : KEY_MAX;
+        int before = 0;
+        for (int l = 0; l < nsplit; ++l) {
+            const uint64_t o = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+            before += (o < v || (o == v && l < lane)) ? 1 : 0;
+        }
+        if (lane < nsplit && before == need - 1) depth_cut[wave] = v;
+    }
+    __syncthreads();
+    uint64_t cut = KEY_MAX;
+    for (int w = 0; w < nw; ++w) cut = depth_cut[w] < cut ? depth_cut[w] : cut;
+    if (cut == KEY_MAX) cut = KEY_MAX - 1; // absent keys never count
+    for (int s = wave; s < nsplit; s += nw) {
+        int cnt = 0;
+        for (int i0 = 0; i0 < K; i0 += 64) {
+            const uint64_t x = i0 + lane < K ? src[s * K + i0 + lane] : KEY_MAX;
+            const bool in = x <= cut;
+            if (in) keys[s * K + i0 + lane] = x;
+            const int got = __popcll(__ballot(in));
+            cnt += got;
+            if (got < 64) break;
+        }
+        if (lane == 0) len[s] = cnt;
+    }
+    __syncthreads();
+    int top = 1; // largest power of two within the longest prefix
+    {
+        const int l = lane < nsplit ? len[lane] : 0;
+        int run = l, mx = l;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(run, o, 64);
+            if (lane >= o) run += u;
+            mx = max(mx, __shfl_xor(mx, o, 64));
+        }
+        if (wave == 0 && lane < nsplit) first[lane + 1] = run;
+        if (tid == 0) first[0] = 0;
+        while (2 * top <= mx) top *= 2;
+    }
+    __syncthreads();
+    const int total = first[nsplit];
+    for (int e = tid; e < total; e += nt) {
+        int s = 0; // list of the e-th key: first[s] <= e < first[s + 1]
+        for (int st = SCAN_MAX_SPLIT / 2; st > 0; st >>= 1)
+            if (s + st < nsplit && first[s + st] <= e) s += st;
+        const int own = e - first[s];
+        const uint64_t x = keys[s * K + own];
+        int rank = own;
+#pragma unroll 4
+        for (int o = 0; o < nsplit; ++o) {
+            const int pos = merge_before(keys + o * K, len[o], x, o < s, top);
+            rank += o == s ? 0 : pos;
+        }
+        if (rank < K) outk[rank] = x;
+    }
+    __syncthreads();
+    for (int i = tid; i < K; i += nt) {
         const uint64_t key = outk[i];
         const bool ok = key != KEY_MAX;
         out_dist[(int64_t)q * K + i] = ok ? ord2f((uint32_t)(key >> 32)) : INFINITY;
@@ -1198,8 +1290,13 @@ void launch_merge(const uint64_t *partial, int nq, int nsplit, int K, float *out
                   hipStream_t st)
 {
     if (nq <= 0) return;
+    if (nsplit * K <= MERGE_FEW) {
+        hipLaunchKernelGGL(k_merge_few, dim3((unsigned)nq), dim3(MERGE_FEW), 0, st, partial, nsplit, K, out_dist, out_ids);
+        return;
+    }
     size_t smem = (size_t)(nsplit + 1) * K * 8;
     if (smem > 49152) // (48 KB of dynamic LDS beside the static part need no asking)
         (void)hipFuncSetAttribute((const void *)k_merge, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    hipLaunchKernelGGL(k_merge, dim3((unsigned)nq), dim3(256), smem, st, partial, nsplit, K, out_dist, out_ids);
+    const int nt = nsplit > 4 ? 1024 : 256; // (a wave per list and round; many queries have few lists)
+    hipLaunchKernelGGL(k_merge, dim3((unsigned)nq), dim3(nt), smem, st, partial, nsplit, K, out_dist, out_ids);
 }
