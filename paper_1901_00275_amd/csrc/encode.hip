@@ -260,23 +260,42 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish(EncodeArgs a, int PB)
 //    loads.  Every lane keeps its own running (distance, codeword) minimum, so the
 //    step has no cross-lane reduction at all; strict "<" in ascending codeword
 //    order keeps the smaller codeword of a tie (Alg. 2).
+// Small batches (ENC_FEW_MAX) take four vectors per workgroup, one per wave, so that the chip is not left idle:
+// phase 2 then has a wave's lanes share the codewords of its vector, four neighbouring ones each, same sums
+// and same choice.  100 vectors, n = 32, m = 16: 264 us with two workgroups of 64, 21 us with 25 of four.
 // ---------------------------------------------------------------------------
 #define ENC2_PB 64
+#define ENC_FEW_PB 4 // a vector per wave
+#define ENC_FEW_MAX 8192 // (4 096: 69-112 us instead of 228-294 for the call; 16 384: 169-341 instead of 251-319, the wide sub-spaces lose)
 typedef const float __attribute__((address_space(4))) cfloat;
 
-template <int DS>
+// smallest value of the wave, in every lane (no NaN)
+__device__ __forceinline__ float wave_min_f32(float v)
+{
+#define VLQ_DPP_MIN(ctrl)                                                                                      \
+    v = fminf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, 0xF, 0xF, true)))
+    VLQ_DPP_MIN(0xB1);
+    VLQ_DPP_MIN(0x4E);
+    VLQ_DPP_MIN(0x141);
+    VLQ_DPP_MIN(0x140);
+#undef VLQ_DPP_MIN
+    v = fminf(v, __shfl_xor(v, 16, 64));
+    return fminf(v, __shfl_xor(v, 32, 64));
+}
+
+template <int DS, int PB>
 __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
 {
     extern __shared__ unsigned char smem[];
     const int D = a.D, m = a.m, n = a.n;
     const int RS = D + 1; // odd row stride: lane = vector reads are conflict-free
-    float *res = (float *)smem;                        // [ENC2_PB][RS]
-    uint8_t *cod = (uint8_t *)(res + ENC2_PB * RS);    // [ENC2_PB][m]
+    float *res = (float *)smem;                        // [PB][RS]
+    uint8_t *cod = (uint8_t *)(res + PB * RS);         // [PB][m]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane >> 4, l16 = lane & 15;
-    const int64_t g0 = (int64_t)blockIdx.x * ENC2_PB;
-    const int np = (int)min((int64_t)ENC2_PB, a.nb - g0);
+    const int64_t g0 = (int64_t)blockIdx.x * PB;
+    const int np = (int)min((int64_t)PB, a.nb - g0);
     const int d0 = l16 * 4, d1 = 64 + l16 * 4;
     const bool has0 = d0 < D, has1 = d1 < D;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -413,6 +432,35 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
             if (a.lamq) a.lamq[gid] = (uint8_t)qf;
         }
     }
+    if (PB == ENC_FEW_PB) {
+        // phase 2, a vector per wave: lane l takes codewords 4 l .. 4 l + 3 (the wave's residual is its own work)
+        if (wave < np) {
+            const float *r = res + wave * RS;
+            const float *w = a.P + (int64_t)lane * 4 * DS;
+            for (int p = 0; p < m; ++p, w += 256 * DS) {
+                float best = INFINITY;
+                int bt = 0;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    float s = 0.f;
+#pragma unroll
+                    for (int d = 0; d < DS; ++d) {
+                        const float tv = r[p * DS + d] - w[u * DS + d];
+                        s = fmaf(tv, tv, s);
+                    }
+                    if (s < best) {
+                        best = s;
+                        bt = u;
+                    }
+                }
+                const float mn = wave_min_f32(best);
+                const uint64_t mask = __ballot(best == mn);
+                const int src = __ffsll((unsigned long long)mask) - 1;
+                if (lane == src) a.codes[(g0 + wave) * m + p] = (uint8_t)(4 * lane + bt);
+            }
+        }
+        return;
+    }
     __syncthreads();
 
     // phase 2: lane = vector, wave = sub-space, codewords in ascending order
@@ -470,10 +518,17 @@ void launch_encode_finish(const EncodeArgs &a, hipStream_t st)
 {
     if (a.nb <= 0) return;
     if (!a.wave_per_vector && encode_lanes_supported(a)) {
-        const size_t smem2 = (size_t)ENC2_PB * (a.D + 1) * 4 + (size_t)ENC2_PB * a.m;
-        const unsigned grid2 = (unsigned)((a.nb + ENC2_PB - 1) / ENC2_PB);
+        const bool few = a.nb <= ENC_FEW_MAX;
+        const int pb = few ? ENC_FEW_PB : ENC2_PB;
+        const size_t smem2 = (size_t)pb * (a.D + 1) * 4 + (size_t)pb * a.m;
+        const unsigned grid2 = (unsigned)((a.nb + pb - 1) / pb);
 #define ENC2_LAUNCH(DSV)                                                                                       \
-    hipLaunchKernelGGL(k_encode_finish_lanes<DSV>, dim3(grid2), dim3(ENC_NT), smem2, st, a)
+    do {                                                                                                       \
+        if (few)                                                                                               \
+            hipLaunchKernelGGL((k_encode_finish_lanes<DSV, ENC_FEW_PB>), dim3(grid2), dim3(ENC_NT), smem2, st, a); \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_encode_finish_lanes<DSV, ENC2_PB>), dim3(grid2), dim3(ENC_NT), smem2, st, a);  \
+    } while (0)
         switch (a.D / a.m) {
         case 4: ENC2_LAUNCH(4); break;
         case 6: ENC2_LAUNCH(6); break;
