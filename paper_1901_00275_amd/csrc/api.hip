@@ -100,6 +100,7 @@ struct vlq_index {
     float qlam_lo = -INFINITY, qlam_hi = INFINITY;
     // centroids split into bf16 (hi, lo) for the matrix-core shortlist; null when D does not allow it
     void *Cimg = nullptr;
+    void *Chalf = nullptr; // the centroids' image of the encoder's product
     int32_t *flags = nullptr;
     // staged points, in insertion order
     int64_t ntotal = 0, cap = 0;
@@ -177,7 +178,7 @@ extern "C" void vlq_index_free(vlq_index_t *idx)
     (void)hipDeviceSynchronize();
     void *ptrs[] = {idx->C, idx->cn, idx->P, idx->E, idx->S, idx->st_label, idx->st_ids, idx->st_lam,
                     idx->st_codes, idx->off, idx->ids, idx->codes, idx->lam, idx->sx, idx->ws,
-                    idx->Cimg, idx->flags, idx->mu, idx->mu_c, idx->Cc};
+                    idx->Cimg, idx->Chalf, idx->flags, idx->mu, idx->mu_c, idx->Cc};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &r : idx->recs) {
@@ -299,6 +300,9 @@ extern "C" int vlq_build_index(const vlq_params_t *params, const float *d_centro
             HIPCHK(hipMalloc(&idx->flags, 256));
             launch_split_bf16(idx->C, k, D, idx->mu_c, idx->Cimg, idx->flags, st);
             LAUNCHCHK();
+            HIPCHK(hipMalloc(&idx->Chalf, half_image_bytes(k, D)));
+            launch_half_image(idx->C, k, D, idx->mu_c, idx->Chalf, true, nullptr, nullptr, st);
+            LAUNCHCHK();
         }
         int r = build_graph(idx, st);
         if (r) return r;
@@ -345,18 +349,19 @@ static int encode_impl(vlq_index *idx, const float *d_x, int64_t nb, int32_t *d_
     const int k = idx->p.nlist, D = idx->p.d, n = idx->p.n_edges, m = idx->p.m;
     const int64_t chunk = nb < ENC_CHUNK ? nb : ENC_CHUNK;
     const int nsplit = coarse_gemm_nn_splits((int)chunk, k);
-    // shortlist on the bf16 matrix cores unless the dimension rules it out (or the fp32 product is
+    // shortlist on the fp16 matrix cores unless the dimension rules it out (or the fp32 product is
     // asked for: VLQ_OPT_COARSE_FP32)
-    const bool bf16 = idx->Cimg && !idx->opt[VLQ_OPT_COARSE_FP32];
-    float *xn, *xc = nullptr;
+    const bool half = idx->Chalf && !idx->opt[VLQ_OPT_COARSE_FP32];
+    float *xn, *xres = nullptr, *xc = nullptr;
     uint64_t *cand;
     uint8_t *ximg = nullptr;
     int32_t *tcell, *tedge, *flag;
     auto carve = [&](Bump &b) {
         xn = b.take<float>((size_t)chunk);
-        if (bf16)
-            ximg = b.take<uint8_t>(coarse_bf16_image_bytes(chunk, D));
-        else
+        if (half) {
+            ximg = b.take<uint8_t>(half_image_bytes(chunk, D));
+            xres = b.take<float>((size_t)chunk);
+        } else
             xc = b.take<float>((size_t)chunk * D);
         cand = b.take<uint64_t>((size_t)chunk * nsplit * VLQ_NN_CANDS);
         tcell = b.take<int32_t>((size_t)chunk);
@@ -373,20 +378,20 @@ static int encode_impl(vlq_index *idx, const float *d_x, int64_t nb, int32_t *d_
         const int64_t cnt = nb - s < chunk ? nb - s : chunk;
         const float *x = d_x + s * D;
         // the split count is fixed by the buffer; a short tail only leaves less work per split
-        launch_row_norms(x, cnt, D, idx->mu_c, xn, st);
-        LAUNCHCHK();
-        EncodeArgs a;
-        if (bf16) {
-            launch_split_bf16(x, cnt, D, idx->mu_c, ximg, flag + 1, st);
+        EncodeArgs a = {};
+        if (half) {
+            launch_half_image(x, cnt, D, idx->mu_c, ximg, false, xn, xres, st);
             LAUNCHCHK();
-            HIPCHK((hipError_t)launch_coarse_gemm_nn_bf16(ximg, flag + 1, (int)cnt, idx->Cimg, k, D, xn, idx->cn, cand,
-                                                          nsplit, &a.band_norm, &a.band_dist, st));
+            HIPCHK((hipError_t)launch_nearest_half(ximg, (int)cnt, idx->Chalf, k, D, xn, xres, idx->cn, cand, nsplit,
+                                                   &a.band_dist, &a.bhdr, st));
+            a.xres = xres;
         } else {
+            launch_row_norms(x, cnt, D, idx->mu_c, xn, st);
+            LAUNCHCHK();
             launch_center_rows(x, cnt, D, idx->mu_c, xc, st);
             LAUNCHCHK();
             launch_coarse_gemm_nn(xc, (int)cnt, idx->Cc, k, D, xn, idx->cn, cand, nsplit, st);
             a.band_norm = vlq_fp32_band_norm(D);
-            a.band_dist = 0.f;
         }
         LAUNCHCHK();
         a.mu = idx->mu_c;
@@ -476,7 +481,7 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
     const int D = d;
     const int64_t chunk = nt < ENC_CHUNK ? nt : ENC_CHUNK;
     const int nsplit = coarse_gemm_nn_splits((int)chunk, k);
-    const bool bf16 = coarse_bf16_supported(D);
+    const bool half = coarse_bf16_supported(D);
     int shift = 62;
     while (shift > 0 && ((int64_t)1 << (62 - shift)) < nt) --shift;
 
@@ -502,9 +507,9 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
     }
 
     DevBuf buf;
-    float *xn, *cn, *mu, *mu_c, *xc = nullptr, *cc = nullptr;
+    float *xn, *xres = nullptr, *cn, *mu, *mu_c, *xc = nullptr, *cc = nullptr;
     uint64_t *cand;
-    int32_t *assign, *cnt, *flag;
+    int32_t *assign, *cnt;
     long long *sums;
     uint32_t *absmax;
     uint8_t *ximg = nullptr, *cimg = nullptr;
@@ -515,12 +520,12 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
     HIPCHK(buf.get(&cand, (size_t)chunk * nsplit * VLQ_NN_CANDS));
     HIPCHK(buf.get(&assign, (size_t)nt));
     HIPCHK(buf.get(&cnt, (size_t)k));
-    HIPCHK(buf.get(&flag, 64));
     HIPCHK(buf.get(&sums, (size_t)k * D));
     HIPCHK(buf.get(&absmax, 64));
-    if (bf16) {
-        HIPCHK(buf.get(&ximg, coarse_bf16_image_bytes(chunk, D)));
-        HIPCHK(buf.get(&cimg, coarse_bf16_image_bytes(k, D)));
+    if (half) {
+        HIPCHK(buf.get(&xres, (size_t)chunk));
+        HIPCHK(buf.get(&ximg, half_image_bytes(chunk, D)));
+        HIPCHK(buf.get(&cimg, half_image_bytes(k, D)));
     } else {
         HIPCHK(buf.get(&xc, (size_t)chunk * D));
         HIPCHK(buf.get(&cc, (size_t)k * D));
@@ -534,31 +539,31 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
     auto assign_all = [&]() -> int {
         launch_col_means(d_centroids, k, D, mu, mu_c, st);
         LAUNCHCHK();
-        launch_row_norms(d_centroids, k, D, mu_c, cn, st);
-        LAUNCHCHK();
-        if (bf16) {
-            launch_split_bf16(d_centroids, k, D, mu_c, cimg, flag, st);
+        if (half) {
+            launch_half_image(d_centroids, k, D, mu_c, cimg, true, cn, nullptr, st);
         } else {
+            launch_row_norms(d_centroids, k, D, mu_c, cn, st);
+            LAUNCHCHK();
             launch_center_rows(d_centroids, k, D, mu_c, cc, st);
         }
         LAUNCHCHK();
         for (int64_t s = 0; s < nt; s += chunk) {
             const int64_t n = nt - s < chunk ? nt - s : chunk;
             const float *x = d_x + s * D;
-            launch_row_norms(x, n, D, mu_c, xn, st);
-            LAUNCHCHK();
             EncodeArgs a = {};
-            if (bf16) {
-                launch_split_bf16(x, n, D, mu_c, ximg, flag + 1, st);
+            if (half) {
+                launch_half_image(x, n, D, mu_c, ximg, false, xn, xres, st);
                 LAUNCHCHK();
-                HIPCHK((hipError_t)launch_coarse_gemm_nn_bf16(ximg, flag + 1, (int)n, cimg, k, D, xn, cn, cand, nsplit,
-                                                              &a.band_norm, &a.band_dist, st));
+                HIPCHK((hipError_t)launch_nearest_half(ximg, (int)n, cimg, k, D, xn, xres, cn, cand, nsplit, &a.band_dist,
+                                                       &a.bhdr, st));
+                a.xres = xres;
             } else {
+                launch_row_norms(x, n, D, mu_c, xn, st);
+                LAUNCHCHK();
                 launch_center_rows(x, n, D, mu_c, xc, st);
                 LAUNCHCHK();
                 launch_coarse_gemm_nn(xc, (int)n, cc, k, D, xn, cn, cand, nsplit, st);
                 a.band_norm = vlq_fp32_band_norm(D);
-                a.band_dist = 0.f;
             }
             LAUNCHCHK();
             a.mu = mu_c;

@@ -1,4 +1,4 @@
-// First-level quantiser on the bf16 matrix cores (Eq. 2; Alg. 1 "nearest centroid").
+// Cell selection of the search on the bf16 matrix cores (Alg. 3, first loop).
 //
 // An fp32 value v is split into two bf16 numbers, hi = rne(v) and lo = rne(v - hi); a bf16 number
 // has 8 significant bits, so |v - hi| <= 2^-8 |v| and |v - hi - lo| <= 2^-16 |v|.  The inner product of
@@ -120,20 +120,17 @@ void launch_split_bf16(const float *X, int64_t rows, int D, const float *mu, voi
 //   1.4e-4 (3 ||a||^2 + 2 d).  (Typical errors are a factor sqrt(3 D) smaller; the band only
 //   decides how many columns are re-evaluated exactly, never the result.)
 #define BF16_BAND_NORM 1.4e-4f
-// Columns past the end of B get this "norm": finite, so that index bits can be planted
-// in the key, and beyond BF16_NO_KEY, from where on a key counts as absent.
+// Columns past the end of B get this "norm", beyond BF16_NO_KEY, which no threshold exceeds.
 #define BF16_NO_COLUMN 3e38f
 #define BF16_NO_KEY 1e38f
 
 // What the product kernel does with a finished 128 x 128 tile of e = ||b||^2 - 2 <a, b>
 // (the row norm is common to a row and joins at the end):
-//  MODE_NN    running two smallest per row slot of every lane; at the end every kept key inside
-//             the band of the row minimum is emitted (encoding: nearest centroid);
 //  MODE_MIN   running minimum per row slot of every lane, written out as 64 group minima per
 //             (row, split) (search, first sweep);
 //  MODE_EMIT  every column with e <= thr[row] is appended to the row's candidate list
 //             (search, second sweep).
-enum { MODE_NN = 0, MODE_MIN = 1, MODE_EMIT = 2 };
+enum { MODE_MIN = 1, MODE_EMIT = 2 };
 
 struct Bf16Args {
     const u32x4 *A; // image of the rows
@@ -143,10 +140,6 @@ struct Bf16Args {
     const float *an, *bn;
     int nsplit, tiles_per_split;
     int tile_stride; // a split takes every tile_stride-th tile of its range (1: all of them)
-    // MODE_NN
-    uint64_t *cand;
-    int idx_bits; // low mantissa bits of a running key that hold (tile, column block)
-    float band_dist;
     // MODE_MIN
     float *gmin; // [M x nsplit x 64]
     // MODE_EMIT
@@ -169,7 +162,6 @@ struct Bf16Args {
 template <int SPT, int MODE, bool HI>
 __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
 {
-    static_assert(!HI || MODE != MODE_NN, "the nearest-centroid mode needs the split product");
     constexpr int PDEPTH = SPT % 4 == 0 ? 4 : (SPT % 3 == 0 ? 3 : 2);
     static_assert(SPT % 2 == 0 && SPT % PDEPTH == 0, "steps per tile");
     // [A pages: SPT x 2][B ring: 2 x 2 pages]; the tail of the kernel reuses the front
@@ -233,8 +225,8 @@ __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
     // accumulator register r of block i holds row wm + 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4
     auto slot_row = [&](int i, int r) { return wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
 
-    // per row slot: MODE_NN smallest / second smallest key, MODE_MIN minimum, MODE_EMIT threshold
-    float b1[2][16], b2[MODE == MODE_NN ? 2 : 1][16];
+    // per row slot: MODE_MIN minimum, MODE_EMIT threshold
+    float b1[2][16];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -244,10 +236,8 @@ __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
                 b1[i][r] = row < a.M ? a.thr[row] : -INFINITY;
             } else {
                 b1[i][r] = INFINITY;
-                if (MODE == MODE_NN) b2[i][r] = INFINITY;
             }
         }
-    const uint32_t keep = MODE == MODE_NN ? ~((1u << a.idx_bits) - 1u) : 0xFFFFFFFFu;
 
     // (the first product of a tile starts from a constant zero, so the accumulators are never cleared)
     f32x16 acc[2][2];
@@ -339,7 +329,6 @@ __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
         uint32_t miss[2] = {0u, 0u};
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const uint32_t tj = (uint32_t)(tl * 2 + j);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -348,14 +337,7 @@ __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
                         const float t = fmaf(2.f, acc[i][j][r], b1[i][r] - cb[j]);
                         miss[j] = __builtin_amdgcn_alignbit(miss[j], __float_as_uint(t), 31);
                     } else {
-                        const float e = fmaf(-2.f, acc[i][j][r], cb[j]);
-                        if (MODE == MODE_NN) {
-                            const float key = __uint_as_float((__float_as_uint(e) & keep) | tj);
-                            b2[i][r] = __builtin_amdgcn_fmed3f(b1[i][r], b2[i][r], key);
-                            b1[i][r] = fminf(b1[i][r], key);
-                        } else {
-                            b1[i][r] = fminf(b1[i][r], e);
-                        }
+                        b1[i][r] = fminf(b1[i][r], fmaf(-2.f, acc[i][j][r], cb[j]));
                     }
                 }
         }
@@ -408,7 +390,6 @@ __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
         }
     }
 
-    if (MODE == MODE_EMIT) return;
     if (MODE == MODE_MIN) {
         // 64 group minima per (row, split): column class (lane & 31) of each column half
 #pragma unroll
@@ -418,76 +399,6 @@ __global__ __launch_bounds__(256, 2) void k_coarse_bf16(Bf16Args a)
                 const int64_t row = m0 + slot_row(i, r);
                 if (row < a.M) a.gmin[(row * a.nsplit + split) * 64 + (wn >> 6) * 32 + (lane & 31)] = b1[i][r];
             }
-        return;
-    }
-
-    // ---- MODE_NN: row minimum over the workgroup, then every kept key inside the band of it ----
-    __syncthreads(); // the operand pages are dead from here on
-    unsigned *rowmin = (unsigned *)lds;                                         // [BT]
-    int *rowcnt = (int *)(rowmin + BT);                                         // [BT]
-    int *rowovf = rowcnt + BT;                                                  // [BT]
-    unsigned long long *rowcand = (unsigned long long *)(rowovf + BT);          // [BT][VLQ_NN_CANDS]
-    if (tid < BT) {
-        rowmin[tid] = 0xFFFFFFFFu;
-        rowcnt[tid] = 0;
-        rowovf[tid] = -1;
-#pragma unroll
-        for (int s = 0; s < VLQ_NN_CANDS; ++s) rowcand[tid * VLQ_NN_CANDS + s] = KEY_MAX;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (b1[i][r] < BF16_NO_KEY) atomicMin(&rowmin[slot_row(i, r)], f2ord(b1[i][r]));
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int rl = slot_row(i, r);
-            const uint32_t mo = rowmin[rl];
-            if (mo == 0xFFFFFFFFu || m0 + rl >= a.M) continue;
-            const float ra = a.an[m0 + rl];
-            const float emin = __uint_as_float(__float_as_uint(ord2f(mo)) & keep);
-            const float dmin = fmaxf(emin + ra, 0.f);
-            const float band = emin + a.band_dist * (ra + dmin) + BF16_BAND_NORM * (3.f * ra + 2.f * dmin);
-            const float ks[2] = {b1[i][r], b2[MODE == MODE_NN ? i : 0][r]};
-            // a lane keeps two keys per row: when its second one lies inside the band a third may
-            // have been dropped, so the row is handed on as incomplete
-            if (ks[1] < BF16_NO_KEY && __uint_as_float(__float_as_uint(ks[1]) & keep) <= band) {
-                const int slot = (wn >> 6) * 32 + (lane & 31);
-                const int old = atomicCAS(&rowovf[rl], -1, slot);
-                if (old != -1 && old != slot) rowovf[rl] = 64; // several slots
-            }
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                if (!(ks[s] < BF16_NO_KEY)) continue;
-                const uint32_t u = __float_as_uint(ks[s]);
-                const float e = __uint_as_float(u & keep);
-                if (e <= band) {
-                    const uint32_t tj = u & ~keep;
-                    const uint32_t col = (uint32_t)(t0 + (int)(tj >> 1) * tstride) * BT + wn + 32 * (tj & 1) + (lane & 31);
-                    if (col >= (uint32_t)a.N) continue;
-                    const int pos = atomicAdd(&rowcnt[rl], 1);
-                    const float d = fmaxf(e + ra, 0.f) + 0.f;
-                    if (pos < VLQ_NN_CANDS)
-                        rowcand[rl * VLQ_NN_CANDS + pos] = ((uint64_t)__float_as_uint(d) << 32) | col;
-                }
-            }
-        }
-    __syncthreads();
-    if (tid < BT && m0 + tid < a.M) {
-        uint64_t *dst = a.cand + ((m0 + tid) * a.nsplit + split) * VLQ_NN_CANDS;
-        const int cnt = rowcnt[tid], sl = rowovf[tid];
-        const bool all = cnt > VLQ_NN_CANDS || sl == 64 || (sl >= 0 && cnt >= VLQ_NN_CANDS);
-#pragma unroll
-        for (int s = 0; s < VLQ_NN_CANDS; ++s) {
-            uint64_t key = rowcand[tid * VLQ_NN_CANDS + s];
-            if (all && s == 0) key = ((uint64_t)VLQ_NN_MARK << 32) | VLQ_NN_ALL;
-            if (!all && sl >= 0 && s == cnt) key = ((uint64_t)VLQ_NN_MARK << 32) | (uint32_t)sl;
-            dst[s] = key;
-        }
     }
 }
 
@@ -515,35 +426,6 @@ static int launch_mode(Bf16Args &a, hipStream_t st)
     case 8: return go(k_coarse_bf16<8, MODE, HI>);
     }
     return (int)hipErrorInvalidValue;
-}
-
-int launch_coarse_gemm_nn_bf16(const void *Aimg, const int *a_any_lo, int M, const void *Bimg, int N, int D,
-                               const float *an, const float *bn, uint64_t *cand, int nsplit, float *band_norm,
-                               float *band_dist, hipStream_t st)
-{
-    Bf16Args a = {};
-    a.A = (const u32x4 *)Aimg;
-    a.B = (const u32x4 *)Bimg;
-    a.a_any_lo = a_any_lo;
-    a.M = M;
-    a.N = N;
-    a.D = D;
-    a.an = an;
-    a.bn = bn;
-    a.cand = cand;
-    a.nsplit = nsplit;
-    const int ntiles = (N + BT - 1) / BT;
-    const int per = (ntiles + nsplit - 1) / nsplit;
-    int bits = 1;
-    while ((1 << bits) < 2 * per) ++bits;
-    a.idx_bits = bits;
-    // planting the index moves a key by less than 2^(bits - 23) of its own size, and a key
-    // e = d - ||a||^2 is at most ||a||^2 + d in size; minimum and candidate both carry it
-    a.band_dist = 2.5f * ldexpf(1.f, bits - 23);
-    *band_norm = BF16_BAND_NORM;
-    *band_dist = a.band_dist;
-    if (M <= 0 || N <= 0) return 0;
-    return launch_mode<MODE_NN>(a, st);
 }
 
 // ---------------------------------------------------------------------------

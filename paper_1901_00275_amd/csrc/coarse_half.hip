@@ -1,0 +1,380 @@
+// Nearest-centroid shortlist (Eq. 2; Alg. 1) on the fp16 matrix cores: ONE product per pair.
+//
+// Rows and centroids (minus the index's origin) are rounded once to fp16 with a power-of-two scale per block
+// of 128 rows that brings the block's largest magnitude to [2^14, 2^15): 11 significant bits, and 28 binades
+// below the largest value before a component is flushed to zero.  How far a row's image is from the row is
+// measured when the image is written (residual norm), so the error of a product is bounded by Cauchy-Schwarz
+// from what was actually lost: |<a, b> - <a', b'>| <= |a - a'||b| + |a'||b - b'|; integer-valued descriptors lose
+// nothing.  Every column inside the band of the row minimum is handed on and re-evaluated as a direct fp32 sum
+// of squared differences, so the decision is taken in fp32 exactly, whatever the product's precision.
+// (The form before split both operands into two bf16 parts and multiplied two or three pairs of pages: 1 000 003 x 128
+// vectors against 65 536 centroids 30.7 ms, 16.7 ms so, 0.86 PFLOP/s; 2^18 x 96 against 16 384: 2.26 and 1.02 ms.)
+//
+// Image: blocks of 128 rows x steps of 16 indices; a 4 KB page per (block, step) holds 128 rows x 2 chunks of
+// 8 values, chunk c of row r at position 2 r + (c ^ ((r >> 2) & 1)): fragment reads are free of bank conflicts.
+//
+// Product kernel: 256 threads = 4 waves, 128 rows against all column tiles of the split, a 64 x 64 quadrant per wave.
+// The A fragments stay in registers for the whole sweep (read straight from the image: A takes no LDS), a whole tile
+// of B (D / 16 pages) is copied memory -> LDS without passing registers while the tile before it is multiplied:
+// one barrier per tile, and two workgroups per compute unit, so that one's selection overlaps the other's products.
+// Per tile a wave has 4 D / 16 MFMAs of 32 clocks (D = 128: 1 024) and 192 vector instructions of 4 clocks: the two
+// columns (j = 0, 1) that a lane sees of a row enter the running two smallest as one key, their smaller value.
+#include "common.h"
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+#define HT 128        // rows per block (= VLQ_NN_TILE columns per tile)
+#define HPAGE 256     // 16-byte chunks per page
+#define HALF_NORMAL 6.103515625e-5f // 2^-14: smaller halves are written as zero
+#define NO_COLUMN 3e38f // "norm" of columns past the end: finite, so that index bits can be planted in the key
+#define NO_KEY 1e38f    // from here on a key counts as absent
+
+size_t half_image_bytes(int64_t rows, int D)
+{
+    const int64_t blocks = (rows + HT - 1) / HT;
+    return 256 + ((size_t)blocks * 4 + 255) / 256 * 256 + (size_t)blocks * HT * D * 2;
+}
+
+// header (256 bytes: [0] largest relative residual of a row, [1] largest residual of the rows whose relative one is
+// beyond fp16's rounding), scales, pages
+struct HalfImage {
+    float *hdr;
+    float *scale; // [blocks] a block's values are multiplied by this
+    u32x4 *pages;
+    HalfImage(const void *img, int64_t rows)
+    {
+        char *p = (char *)(uintptr_t)img;
+        const int64_t blocks = (rows + HT - 1) / HT;
+        hdr = (float *)p;
+        scale = (float *)(p + 256);
+        pages = (u32x4 *)(p + 256 + ((size_t)blocks * 4 + 255) / 256 * 256);
+    }
+};
+
+__global__ void k_half_header(float *hdr)
+{
+    if (threadIdx.x < 2) hdr[threadIdx.x] = 0.f;
+}
+
+// One workgroup per block of 128 rows, a thread per (row, chunk of 8 values), SPT times: one pass over X gives the
+// block's scale, the pages, and per row the squared norm and the residual's norm.  Bound by memory.
+template <int SPT>
+__global__ __launch_bounds__(256) void k_half_image(const float *__restrict__ X, int64_t rows,
+                                                    const float *__restrict__ mu, float *__restrict__ hdr,
+                                                    float *__restrict__ scale, u32x4 *__restrict__ pages,
+                                                    float *__restrict__ norm2, float *__restrict__ resid)
+{
+    constexpr int D = SPT * 16, CPR = SPT * 2;
+    __shared__ float pn[HT][CPR + 1], pr[HT][CPR + 1];
+    __shared__ float wmax[4];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t blk = blockIdx.x;
+    float v[SPT][8];
+    float mx = 0.f;
+#pragma unroll
+    for (int j = 0; j < SPT; ++j) {
+        const int i = j * 256 + tid, r = i / CPR, ch = i - r * CPR;
+        const int64_t row = blk * HT + r;
+        f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
+        if (row < rows) {
+            v0 = *(const f32x4 *)(X + row * D + ch * 8) - *(const f32x4 *)(mu + ch * 8);
+            v1 = *(const f32x4 *)(X + row * D + ch * 8 + 4) - *(const f32x4 *)(mu + ch * 8 + 4);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[j][e] = e < 4 ? v0[e] : v1[e - 4];
+            const float m = fabsf(v[j][e]);
+            if (m < INFINITY) mx = fmaxf(mx, m);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) wmax[tid >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    // largest magnitude to [2^14, 2^15); at most 2^+-60, so that the product of two inverse scales stays in range
+    // (beyond that the squared norms of the rows overflow or vanish in fp32 as well)
+    int ex = mx > 0.f ? 14 - ((int)(__float_as_uint(mx) >> 23) - 127) : 0;
+    ex = max(-60, min(60, ex));
+    const float s = __uint_as_float((uint32_t)(127 + ex) << 23), inv = __uint_as_float((uint32_t)(127 - ex) << 23);
+    if (tid == 0) scale[blk] = s;
+#pragma unroll
+    for (int j = 0; j < SPT; ++j) {
+        const int i = j * 256 + tid, r = i / CPR, ch = i - r * CPR;
+        half8 h;
+        float n2 = 0.f, r2 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float t = v[j][e] * s;
+            _Float16 q = (_Float16)t;
+            if (fabsf((float)q) < HALF_NORMAL) q = (_Float16)0.f;
+            const float d = t - (float)q;
+            n2 = fmaf(t, t, n2);
+            r2 = fmaf(d, d, r2);
+            h[e] = q;
+        }
+        pn[r][ch] = n2;
+        pr[r][ch] = r2;
+        pages[(blk * SPT + (ch >> 1)) * HPAGE + 2 * r + ((ch & 1) ^ ((r >> 2) & 1))] = __builtin_bit_cast(u32x4, h);
+    }
+    __syncthreads();
+    if (tid < HT) {
+        float n2 = 0.f, r2 = 0.f;
+#pragma unroll
+        for (int c = 0; c < CPR; ++c) {
+            n2 += pn[tid][c];
+            r2 += pr[tid][c];
+        }
+        const float nrm = sqrtf(n2), res = sqrtf(r2) * 1.0001f; // (the rounding of the sums)
+        const int64_t row = blk * HT + tid;
+        if (row < rows && norm2) norm2[row] = n2 * inv * inv;
+        if (row < rows && resid) resid[row] = res * inv;
+        if (hdr) {
+            const bool ok = res < INFINITY && n2 > 0.f; // (a non-finite row's products never count)
+            float rel = ok && res <= 5e-4f * nrm ? res / nrm * 1.0001f : 0.f;
+            float big = ok && !(res <= 5e-4f * nrm) ? res * inv : 0.f;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                rel = fmaxf(rel, __shfl_xor(rel, o, 64));
+                big = fmaxf(big, __shfl_xor(big, o, 64));
+            }
+            if (lane == 0) {
+                if (rel > ((volatile float *)hdr)[0]) atomicMax((unsigned *)hdr, __float_as_uint(rel));
+                if (big > ((volatile float *)hdr)[1]) atomicMax((unsigned *)hdr + 1, __float_as_uint(big));
+            }
+        }
+    }
+}
+
+void launch_half_image(const float *X, int64_t rows, int D, const float *mu, void *img, bool header, float *norm2,
+                       float *resid, hipStream_t st)
+{
+    if (rows <= 0) return;
+    const HalfImage h(img, rows);
+    const dim3 grid((unsigned)((rows + HT - 1) / HT));
+    if (header) hipLaunchKernelGGL(k_half_header, dim3(1), dim3(64), 0, st, h.hdr);
+#define HALF_LAUNCH(S)                                                                                         \
+    hipLaunchKernelGGL(k_half_image<S>, grid, dim3(256), 0, st, X, rows, mu, header ? h.hdr : nullptr, h.scale, h.pages, \
+                       norm2, resid)
+    switch (D / 16) {
+    case 2: HALF_LAUNCH(2); break;
+    case 4: HALF_LAUNCH(4); break;
+    case 6: HALF_LAUNCH(6); break;
+    default: HALF_LAUNCH(8); break;
+    }
+#undef HALF_LAUNCH
+}
+
+struct HalfArgs {
+    const u32x4 *A, *B;
+    const float *ascale, *bscale, *bhdr;
+    int M, N;
+    const float *an, *ares, *bn;
+    int nsplit, tiles_per_split;
+    uint64_t *cand;
+    int idx_bits; // low mantissa bits of a running key that hold the tile
+    float band_dist;
+};
+
+template <int SPT>
+__global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
+{
+    extern __shared__ u32x4 lds[]; // two tiles of B: [2][SPT][HPAGE]; the tail of the kernel reuses the front
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int64_t m0 = (int64_t)blockIdx.x * HT;
+    const int split = blockIdx.y;
+    const int ntiles = (a.N + HT - 1) / HT;
+    const int t0 = split * a.tiles_per_split;
+    const int t1 = min(ntiles, t0 + a.tiles_per_split);
+
+    // a tile of B into LDS: thread t's chunk of every page goes to place t of that page (a wave's 64 chunks are
+    // contiguous on both sides, as the direct copy requires)
+    auto copy_tile = [&](int t) {
+        const u32x4 *src = a.B + (int64_t)t * SPT * HPAGE + tid;
+        u32x4 *dst = lds + ((t - t0) & 1) * SPT * HPAGE + wave * 64;
+#pragma unroll
+        for (int p = 0; p < SPT; ++p)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + p * HPAGE),
+                                             (__attribute__((address_space(3))) void *)(dst + p * HPAGE), 16, 0, 0);
+    };
+    // fragment of a 32-row block: lane reads row (lane & 31), chunk (lane >> 5)
+    const int frow = lane & 31;
+    const int fpos = 2 * frow + ((lane >> 5) ^ ((frow >> 2) & 1));
+    half8 ah[SPT][2];
+    {
+        const u32x4 *src = a.A + (int64_t)blockIdx.x * SPT * HPAGE + 2 * wm + fpos;
+#pragma unroll
+        for (int u = 0; u < SPT; ++u) {
+            ah[u][0] = __builtin_bit_cast(half8, src[u * HPAGE]);
+            ah[u][1] = __builtin_bit_cast(half8, src[u * HPAGE + 64]);
+        }
+    }
+    // accumulator register r of block i holds row wm + 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4
+    auto slot_row = [&](int i, int r) { return wm + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
+    float b1[2][16], b2[2][16]; // per row slot: smallest and second smallest key
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) b1[i][r] = b2[i][r] = INFINITY;
+    const uint32_t keep = ~((1u << a.idx_bits) - 1u);
+    const uint32_t aexp = __float_as_uint(a.ascale[blockIdx.x]);
+    // column norms and scale of a tile, asked for a tile ahead and before its copies, so that the one wait covers both
+    float cbn[2], scn;
+    auto fetch_cols = [&](int t) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int64_t col = (int64_t)t * HT + wn + 32 * j + (lane & 31);
+            cbn[j] = a.bn[min(col, (int64_t)a.N - 1)];
+        }
+        scn = a.bscale[t];
+    };
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+
+    if (t0 < t1) {
+        fetch_cols(t0);
+        copy_tile(t0);
+    }
+    for (int t = t0; t < t1; ++t) {
+        // this tile has arrived (every wave waits for its own copies), and the other half of the ring is free
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        float cb[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) cb[j] = (int64_t)t * HT + wn + 32 * j + (lane & 31) < a.N ? cbn[j] : NO_COLUMN;
+        // -2 / (scale of the rows * scale of the columns): powers of two, 1 / 2^x by its exponent
+        const float inv = -2.f * __uint_as_float(0x7F000000u - aexp) * __uint_as_float(0x7F000000u - __float_as_uint(scn));
+        if (t + 1 < t1) {
+            fetch_cols(t + 1);
+            copy_tile(t + 1);
+        }
+        const u32x4 *bp = lds + ((t - t0) & 1) * SPT * HPAGE + 2 * wn + fpos;
+        f32x16 acc[2][2];
+#pragma unroll
+        for (int u = 0; u < SPT; ++u) {
+            half8 bh[2];
+            bh[0] = __builtin_bit_cast(half8, bp[u * HPAGE]);
+            bh[1] = __builtin_bit_cast(half8, bp[u * HPAGE + 64]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[u][i], bh[j], u == 0 ? zero16 : acc[i][j], 0, 0, 0);
+        }
+        const uint32_t tj = (uint32_t)(t - t0);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float e = fminf(fmaf(inv, acc[i][0][r], cb[0]), fmaf(inv, acc[i][1][r], cb[1]));
+                const float key = __uint_as_float((__float_as_uint(e) & keep) | tj);
+                b2[i][r] = __builtin_amdgcn_fmed3f(b1[i][r], b2[i][r], key);
+                b1[i][r] = fminf(b1[i][r], key);
+            }
+    }
+
+    // ---- row minimum over the workgroup, then every kept key inside the band of it ----
+    __syncthreads(); // the tiles are dead from here on
+    unsigned *rowmin = (unsigned *)lds;                                // [HT]
+    int *rowcnt = (int *)(rowmin + HT);                                // [HT]
+    unsigned long long *rowcand = (unsigned long long *)(rowcnt + HT); // [HT][VLQ_NN_CANDS]
+    if (tid < HT) {
+        rowmin[tid] = 0xFFFFFFFFu;
+        rowcnt[tid] = 0;
+#pragma unroll
+        for (int s = 0; s < VLQ_NN_CANDS; ++s) rowcand[tid * VLQ_NN_CANDS + s] = KEY_MAX;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (b1[i][r] < NO_KEY) atomicMin(&rowmin[slot_row(i, r)], f2ord(b1[i][r]));
+    __syncthreads();
+    const float rho = a.bhdr[0], big = a.bhdr[1];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int rl = slot_row(i, r);
+            const uint32_t mo = rowmin[rl];
+            if (mo == 0xFFFFFFFFu || m0 + rl >= a.M) continue;
+            const float ra = a.an[m0 + rl];
+            const float emin = __uint_as_float(__float_as_uint(ord2f(mo)) & keep);
+            const float dmin = fmaxf(emin + ra, 0.f);
+            const float band = emin + nn_half_band(ra, a.ares[m0 + rl], rho, big, dmin, a.band_dist, SPT * 16);
+            const float e = __uint_as_float(__float_as_uint(b1[i][r]) & keep);
+            if (!(b1[i][r] < NO_KEY) || !(e <= band)) continue;
+            // the key stands for both columns of its tile; a second one inside the band may have pushed out a
+            // third, so the slot's columns are handed on instead
+            const bool more = b2[i][r] < NO_KEY && __uint_as_float(__float_as_uint(b2[i][r]) & keep) <= band;
+            const uint32_t col = (uint32_t)(t0 + (int)(__float_as_uint(b1[i][r]) & ~keep)) * HT + wn + (lane & 31);
+            const uint32_t entry = more ? VLQ_NN_SLOT | (uint32_t)((wn >> 6) * 32 + (lane & 31)) : col;
+            const int pos = atomicAdd(&rowcnt[rl], 1);
+            if (pos < VLQ_NN_CANDS)
+                rowcand[rl * VLQ_NN_CANDS + pos] = ((uint64_t)__float_as_uint(fmaxf(e + ra, 0.f) + 0.f) << 32) | entry;
+        }
+    __syncthreads();
+    if (tid < HT && m0 + tid < a.M) {
+        uint64_t *dst = a.cand + ((m0 + tid) * a.nsplit + split) * VLQ_NN_CANDS;
+        const bool all = rowcnt[tid] > VLQ_NN_CANDS; // more than there is room for: the split's columns
+        const float emin = __uint_as_float(__float_as_uint(ord2f(rowmin[tid])) & keep);
+        const uint64_t whole =
+            ((uint64_t)__float_as_uint(fmaxf(emin + a.an[m0 + tid], 0.f) + 0.f) << 32) | VLQ_NN_ALL;
+#pragma unroll
+        for (int s = 0; s < VLQ_NN_CANDS; ++s) {
+            const uint64_t key = rowcand[tid * VLQ_NN_CANDS + s];
+            dst[s] = all ? (s == 0 ? whole : KEY_MAX) : key;
+        }
+    }
+}
+
+int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *an, const float *ares,
+                        const float *bn, uint64_t *cand, int nsplit, float *band_dist, const float **bhdr, hipStream_t st)
+{
+    const HalfImage A(Aimg, M), B(Bimg, N);
+    HalfArgs a = {};
+    a.A = A.pages;
+    a.ascale = A.scale;
+    a.B = B.pages;
+    a.bscale = B.scale;
+    a.bhdr = B.hdr;
+    a.M = M;
+    a.N = N;
+    a.an = an;
+    a.ares = ares;
+    a.bn = bn;
+    a.cand = cand;
+    a.nsplit = nsplit;
+    const int ntiles = (N + HT - 1) / HT;
+    a.tiles_per_split = (ntiles + nsplit - 1) / nsplit;
+    int bits = 1;
+    while ((1 << bits) < a.tiles_per_split) ++bits;
+    a.idx_bits = bits;
+    // planting the index moves a key by less than 2^(bits - 23) of its own size, and a key
+    // e = d - ||a||^2 is at most ||a||^2 + d in size; minimum and candidate both carry it
+    a.band_dist = 2.5f * ldexpf(1.f, bits - 23);
+    *band_dist = a.band_dist;
+    *bhdr = B.hdr;
+    if (M <= 0 || N <= 0) return 0;
+    const size_t tail = HT * (8 + 8 * VLQ_NN_CANDS), ring = (size_t)2 * (D / 16) * HPAGE * 16;
+    const size_t bytes = ring > tail ? ring : tail;
+    const dim3 grid((unsigned)((M + HT - 1) / HT), (unsigned)nsplit);
+    auto go = [&](auto kern) -> int {
+        if (bytes > 49152) { // (48 KB of dynamic LDS need no asking)
+            hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+            if (e != hipSuccess) return (int)e;
+        }
+        hipLaunchKernelGGL(kern, grid, dim3(256), bytes, st, a);
+        return 0;
+    };
+    switch (D / 16) {
+    case 2: return go(k_nearest_half<2>);
+    case 4: return go(k_nearest_half<4>);
+    case 6: return go(k_nearest_half<6>);
+    case 8: return go(k_nearest_half<8>);
+    }
+    return (int)hipErrorInvalidValue;
+}

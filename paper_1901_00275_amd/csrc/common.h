@@ -178,6 +178,10 @@ void launch_coarse_gemm_full(const float *A, int M, const float *B, int N, int D
 #define VLQ_NN_MARK 0xFFFFFFFEu
 #define VLQ_NN_ALL 0xFFFFFFFFu
 #define VLQ_NN_TILE 128
+// The fp16 product's keys carry the distance of the best column they stand for in the high word, and in the low word
+// a column c, for c and c + 32; or VLQ_NN_SLOT | slot, for the slot's columns of the split; or VLQ_NN_ALL, for all
+// columns of the split.
+#define VLQ_NN_SLOT 0x80000000u
 // Width of the band around the smallest distance d of a row a:
 // band_norm * (3 ||a||^2 + 2 d) + band_dist * (||a||^2 + d); the fp32 product has band_dist = 0.
 // fp32 product: each value ||a||^2 + ||b||^2 - 2 <a, b> is off by at most
@@ -189,18 +193,38 @@ int coarse_gemm_nn_splits(int M, int N);
 void launch_coarse_gemm_nn(const float *A, int M, const float *B, int N, int D, const float *an,
                            const float *bn, uint64_t *cand, int nsplit, hipStream_t st);
 
-// The same shortlist on the bf16 matrix cores (coarse_bf16.hip).  Both operands are first
-// rewritten by launch_split_bf16 into an image of coarse_bf16_image_bytes(rows, D) bytes
-// (bf16 hi/lo pairs in the order the product kernel reads them).  Requires
-// coarse_bf16_supported(D).  The band the consumer has to apply is returned in
-// *band_norm / *band_dist; the return value is 0 or a hipError_t.
-// mu (optional, [D]) is subtracted from every row before the split.
+// The same shortlist on the fp16 matrix cores (coarse_half.hip), for the dimensions of coarse_bf16_supported.  Both
+// operands are first rewritten by launch_half_image (minus mu) into an image of half_image_bytes(rows, D) bytes, which
+// also gives the rows' squared norms and residual norms (each may be NULL); the columns' image needs its header.
+// The band the consumer has to apply is nn_half_band with *bhdr and *band_dist; the return value is 0 or a hipError_t.
+size_t half_image_bytes(int64_t rows, int D);
+void launch_half_image(const float *X, int64_t rows, int D, const float *mu, void *img, bool header, float *norm2,
+                       float *resid, hipStream_t st);
+int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *an, const float *ares,
+                        const float *bn, uint64_t *cand, int nsplit, float *band_dist, const float **bhdr, hipStream_t st);
+// Width of the band around the smallest distance dmin of a row a, xn = ||a||^2, res = ||a - a'||, for columns with
+// ||b - b'|| <= max(rho ||b||, big).  One value ||b||^2 - 2 <a', b'> is off by at most
+//   2 (res ||b|| + ||a'|| max(rho ||b||, big))      rounding to fp16 (Cauchy-Schwarz), ||a'|| <= 1.002 ||a||
+//   + 4 D 2^-24 s^2                                 fp32 accumulation of D products (twice D 2^-24 |a||b|) and the norms'
+//                                                   own rounding, |a|, |b| <= s
+// and a comparison involves two.  ||b|| <= ||a|| + sqrt(d) <= s for the columns that matter: their distance exceeds dmin by
+// no more than the values' error, for which s has a tenth to spare (and the term in big).  A row that lost more than 2^-9 of its norm
+// (a tiny row beside a huge one) gets every column.
+__device__ __forceinline__ float nn_half_band(float xn, float res, float rho, float big, float dmin, float band_dist, int D)
+{
+    const float na = sqrtf(xn);
+    if (!(res <= 0x1p-9f * na)) return INFINITY;
+    const float s = 1.1f * (na + sqrtf(dmin)) + 1.5f * sqrtf(na * big);
+    return 4.f * ((res + 1.01f * rho * na) * s + 1.01f * na * big) + 8.f * (float)(D + 8) * 0x1p-24f * s * s +
+           band_dist * (xn + dmin);
+}
+
+// Operands of the search's sweeps on the bf16 matrix cores (coarse_bf16.hip): launch_split_bf16 rewrites
+// rows into an image of coarse_bf16_image_bytes(rows, D) bytes (bf16 hi/lo pairs in the order the product kernel
+// reads them).  mu (optional, [D]) is subtracted from every row before the split.
 bool coarse_bf16_supported(int D);
 size_t coarse_bf16_image_bytes(int64_t rows, int D);
 void launch_split_bf16(const float *X, int64_t rows, int D, const float *mu, void *img, int *any_lo, hipStream_t st);
-int launch_coarse_gemm_nn_bf16(const void *Aimg, const int *a_any_lo, int M, const void *Bimg, int N, int D,
-                               const float *an, const float *bn, uint64_t *cand, int nsplit, float *band_norm,
-                               float *band_dist, hipStream_t st);
 
 // w1 nearest centroids of every query from two sweeps of the bf16 product, without the nq x k
 // matrix (coarse_bf16.hip).  cells_bf16_plan says whether the shape allows it and fixes the
@@ -313,7 +337,8 @@ struct EncodeArgs {
     bool wave_per_vector; // the wave-per-vector kernel for every shape
     const uint64_t *cand;
     int nsplit;
-    float band_norm, band_dist; // error band of the shortlist's distances
+    float band_norm, band_dist; // error band of the shortlist's distances: of the fp32 product, or (bhdr given)
+    const float *xres, *bhdr;   // of the fp16 product, nn_half_band with the rows' residual norms and the columns' header
     int32_t *cell, *edge;
     uint8_t *lamq, *codes;
     float *res; // optional [nb x D]: the residual x - ((1 - l) c_i + l s_ij) of Eq. 12

@@ -39,13 +39,16 @@ __device__ __forceinline__ uint64_t exact_nearest_of(const float *x, const float
     const int sub = lane >> 4, l16 = lane & 15;
     const bool vec = (D % 4 == 0) && (((uintptr_t)C) % 16 == 0);
     uint64_t best = KEY_MAX;
-    for (int c0 = 0; c0 < count; c0 += 4) {
-        const int c = c0 + sub;
-        const int i = c < count ? col_of(c) : k;
-        const float acc = sqdist16(x, C + (int64_t)min(i, k - 1) * D, D, l16, vec);
-        if (i < k) {
-            const uint64_t key = make_key(acc, (uint32_t)i);
-            best = key < best ? key : best;
+    for (int c0 = 0; c0 < count; c0 += 16) { // (four passes at a time: their loads are under way together)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = c0 + 4 * u + sub;
+            const int i = c < count ? col_of(c) : k;
+            const float acc = sqdist16(x, C + (int64_t)min(i, k - 1) * D, D, l16, vec);
+            if (i < k) {
+                const uint64_t key = make_key(acc, (uint32_t)i);
+                best = key < best ? key : best;
+            }
         }
     }
     return wave_min_u64(best);
@@ -83,6 +86,72 @@ __device__ __forceinline__ uint64_t resolve_markers(const uint64_t *__restrict__
         }
     }
     return best;
+}
+
+// width of the band around the smallest shortlist distance of vector gid
+__device__ __forceinline__ float shortlist_band(const EncodeArgs &a, int64_t gid, float xn, float dmin)
+{
+    if (a.bhdr) return nn_half_band(xn, a.xres[gid], a.bhdr[0], a.bhdr[1], dmin, a.band_dist, a.D);
+    return a.band_norm * (3.f * xn + 2.f * dmin);
+}
+
+// Nearest centroid of vector gid from its shortlist: what lies inside the band of the smallest distance is
+// re-evaluated as direct sums of squared differences, the smallest (distance, index) is the cell (Eq. 2).
+// x: the vector (one wave's), xn: its squared norm as the product saw it.
+__device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gid, const float *x, float xn, int lane, bool vec)
+{
+    const int nc = a.nsplit * VLQ_NN_CANDS, l16 = lane & 15;
+    const uint64_t *cd = a.cand + gid * nc;
+    uint64_t mn = KEY_MAX, bk = KEY_MAX;
+    bool marked = false;
+    for (int c = lane; c < nc; c += 64) {
+        const uint64_t key = cd[c];
+        if (!a.bhdr && (uint32_t)(key >> 32) == VLQ_NN_MARK)
+            marked = true;
+        else
+            mn = key < mn ? key : mn;
+    }
+    // fp32 product: incomplete shortlists first, the marked slots (or all columns) exactly
+    if (__ballot(marked)) bk = resolve_markers(cd, nc, a.nsplit, x, a.C, a.k, a.D, lane);
+    mn = wave_min_u64(mn);
+    if (mn != KEY_MAX) {
+        const float dmin = __uint_as_float((uint32_t)(mn >> 32));
+        const float band = dmin + shortlist_band(a, gid, xn, dmin);
+        const int ntiles = (a.k + VLQ_NN_TILE - 1) / VLQ_NN_TILE, per = (ntiles + a.nsplit - 1) / a.nsplit;
+        for (int c0 = 0; c0 < nc; c0 += 64) { // the few candidates inside the band, found 64 keys at a time
+            const uint64_t key = c0 + lane < nc ? cd[c0 + lane] : KEY_MAX;
+            const bool inb = key != KEY_MAX && (a.bhdr || (uint32_t)(key >> 32) != VLQ_NN_MARK) &&
+                             !(__uint_as_float((uint32_t)(key >> 32)) > band);
+            uint64_t mask = __ballot(inb);
+            while (mask) {
+                const int src = __ffsll((unsigned long long)mask) - 1;
+                mask &= mask - 1;
+                const uint32_t idx = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
+                uint64_t got;
+                if (!a.bhdr) {
+                    got = make_key(sqdist16(x, a.C + (int64_t)idx * a.D, a.D, l16, vec), idx);
+                } else if (!(idx & VLQ_NN_SLOT)) { // columns idx and idx + 32, by the even and the odd groups of 16 lanes
+                    const uint32_t i = idx + 32 * ((lane >> 4) & 1);
+                    const float d = sqdist16(x, a.C + (int64_t)min(i, (uint32_t)a.k - 1) * a.D, a.D, l16, vec);
+                    got = i < (uint32_t)a.k ? make_key(d, i) : KEY_MAX;
+                    const uint64_t other = shfl_xor_u64(got, 16);
+                    got = other < got ? other : got;
+                } else {
+                    const int split = (c0 + src) / VLQ_NN_CANDS;
+                    const int t0 = split * per, t1 = min(ntiles, t0 + per);
+                    const int base = (int)((idx >> 5) & 1) * 64 + (int)(idx & 31);
+                    const bool all = idx == VLQ_NN_ALL;
+                    got = exact_nearest_of(x, a.C, a.k, a.D, lane, (t1 - t0) * (all ? VLQ_NN_TILE : 2), [=](int c) {
+                        return all ? t0 * VLQ_NN_TILE + c : (t0 + (c >> 1)) * VLQ_NN_TILE + base + 32 * (c & 1);
+                    });
+                }
+                bk = got < bk ? got : bk;
+            }
+        }
+    }
+    if (bk == KEY_MAX) // only with non-finite input: keep indices in range
+        bk = make_key(sqdist16(x, a.C, a.D, l16, vec), 0u);
+    return bk;
 }
 
 // The byte of lambda and the residual for the chosen line (Eq. 12-13), in fp64 so that both are
@@ -150,38 +219,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish(EncodeArgs a, int PB)
             xn = fmaf(vc, vc, xn);
         }
         xn = wave_sum(xn);
-        // candidates of all column splits
-        const int nc = a.nsplit * VLQ_NN_CANDS;
-        const uint64_t *cd = a.cand + gid * nc;
-        uint64_t mn = KEY_MAX;
-        bool marked = false;
-        for (int c = lane; c < nc; c += 64) {
-            const uint64_t key = cd[c];
-            if ((uint32_t)(key >> 32) == VLQ_NN_MARK)
-                marked = true;
-            else
-                mn = key < mn ? key : mn;
-        }
-        // incomplete shortlists first: the marked slots (or all columns) exactly
-        uint64_t bk = __ballot(marked) ? resolve_markers(cd, nc, a.nsplit, x, a.C, a.k, D, lane) : KEY_MAX;
-        mn = wave_min_u64(mn);
-        if (mn != KEY_MAX) {
-            const float dmin = __uint_as_float((uint32_t)(mn >> 32));
-            const float band = dmin + a.band_dist * (xn + dmin) + a.band_norm * (3.f * xn + 2.f * dmin);
-            for (int c = 0; c < nc; ++c) {
-                const uint64_t key = cd[c]; // same address in all lanes
-                if (key == KEY_MAX || (uint32_t)(key >> 32) == VLQ_NN_MARK || __uint_as_float((uint32_t)(key >> 32)) > band)
-                    continue;
-                const uint32_t idx = (uint32_t)key;
-                const float d = sqdist16(x, a.C + (int64_t)idx * D, D, lane & 15, vec16);
-                const uint64_t ek = make_key(d, idx);
-                bk = ek < bk ? ek : bk;
-            }
-        }
-        if (bk == KEY_MAX) { // only with non-finite input: keep indices in range
-            const uint32_t idx = mn == KEY_MAX ? 0u : (uint32_t)mn;
-            bk = make_key(sqdist16(x, a.C + (int64_t)idx * D, D, lane & 15, vec16), idx);
-        }
+        const uint64_t bk = nearest_cell(a, gid, x, xn, lane, vec16);
         const int cell = (int)(uint32_t)bk;
         const float av = ord2f((uint32_t)(bk >> 32));
         if (!a.S) { // nearest centroid only (Lloyd iterations)
@@ -312,42 +350,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
             xn = fmaf(vc, vc, xn);
         }
         xn = wave_sum(xn);
-        const int nc = a.nsplit * VLQ_NN_CANDS;
-        const uint64_t *cd = a.cand + gid * nc;
-        uint64_t mn = KEY_MAX;
-        bool marked = false;
-        for (int c = lane; c < nc; c += 64) {
-            const uint64_t key = cd[c];
-            if ((uint32_t)(key >> 32) == VLQ_NN_MARK)
-                marked = true;
-            else
-                mn = key < mn ? key : mn;
-        }
-        // incomplete shortlists first: the marked slots (or all columns) exactly
-        uint64_t bk = __ballot(marked) ? resolve_markers(cd, nc, a.nsplit, x, a.C, a.k, D, lane) : KEY_MAX;
-        mn = wave_min_u64(mn);
-        if (mn != KEY_MAX) {
-            const float dmin = __uint_as_float((uint32_t)(mn >> 32));
-            const float band = dmin + a.band_dist * (xn + dmin) + a.band_norm * (3.f * xn + 2.f * dmin);
-            for (int c0 = 0; c0 < nc; c0 += 64) { // the few candidates inside the band, found 64 keys at a time
-                const uint64_t key = c0 + lane < nc ? cd[c0 + lane] : KEY_MAX;
-                const bool inb = key != KEY_MAX && (uint32_t)(key >> 32) != VLQ_NN_MARK &&
-                                 !(__uint_as_float((uint32_t)(key >> 32)) > band);
-                uint64_t mask = __ballot(inb);
-                while (mask) {
-                    const int src = __ffsll((unsigned long long)mask) - 1;
-                    mask &= mask - 1;
-                    const uint32_t idx = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
-                    const float d = sqdist16(x, a.C + (int64_t)idx * D, D, lane & 15, vec16);
-                    const uint64_t ek = make_key(d, idx);
-                    bk = ek < bk ? ek : bk;
-                }
-            }
-        }
-        if (bk == KEY_MAX) { // only with non-finite input: keep indices in range
-            const uint32_t idx = mn == KEY_MAX ? 0u : (uint32_t)mn;
-            bk = make_key(sqdist16(x, a.C + (int64_t)idx * D, D, lane & 15, vec16), idx);
-        }
+        const uint64_t bk = nearest_cell(a, gid, x, xn, lane, vec16);
         const int cell = (int)(uint32_t)bk;
         const float av = ord2f((uint32_t)(bk >> 32));
         // line quantisation inside the cell, four neighbour rows per pass
