@@ -7,8 +7,8 @@
 // from what was actually lost: |<a, b> - <a', b'>| <= |a - a'||b| + |a'||b - b'|; integer-valued descriptors lose
 // nothing.  Every column inside the band of the row minimum is handed on and re-evaluated as a direct fp32 sum
 // of squared differences, so the decision is taken in fp32 exactly, whatever the product's precision.
-// (The form before split both operands into two bf16 parts and multiplied two or three pairs of pages: 1 000 003 x 128
-// vectors against 65 536 centroids 30.7 ms, 16.7 ms so, 0.86 PFLOP/s; 2^18 x 96 against 16 384: 2.26 and 1.02 ms.)
+// (The form before split both operands into two bf16 parts and multiplied two or three pairs of pages: 213 571 x 128
+// integer vectors against 65 536 centroids 7.67 ms, 4.19 ms so, 0.86 PFLOP/s; 2^18 x 96 against 16 384: 2.26 and 1.02 ms.)
 //
 // Image: blocks of 128 rows x steps of 16 indices; a 4 KB page per (block, step) holds 128 rows x 2 chunks of
 // 8 values, chunk c of row r at position 2 r + (c ^ ((r >> 2) & 1)): fragment reads are free of bank conflicts.

@@ -154,6 +154,83 @@ __device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gi
     return bk;
 }
 
+// The cells alone (Lloyd iterations), 16 lanes a vector (D <= 128 in four-component pieces; the fp16 product's
+// shortlists): a wave takes four vectors at a time, so that the chain of dependent loads -- keys, residual
+// norm, centroid row -- is paid once for four of them.  Same sums in the same order as nearest_cell; a vector
+// with a slot or a whole split inside its band is left to the wave.  Bound by memory latency: 2^18 x 96 with one
+// split 280 us a wave per vector, 124 us so.  (In front of k_encode_finish_lanes it gains nothing: 24.3 -> 24.0 ms for
+// 1 000 003 vectors; that kernel has the line distances to overlap the same chain with.)
+#define NC_NT 256
+__global__ __launch_bounds__(NC_NT) void k_nearest_cells(EncodeArgs a)
+{
+    extern __shared__ float xs[]; // [NC_NT / 64][4][D], read only by the wave that wrote it
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, sub = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int D = a.D, nc = a.nsplit * VLQ_NN_CANDS;
+    const int64_t g0 = ((int64_t)blockIdx.x * (NC_NT / 64) + wave) * 4;
+    if (g0 >= a.nb) return;
+    const int64_t gid = min(g0 + sub, a.nb - 1);
+    const float rho = a.bhdr[0], big = a.bhdr[1];
+    const uint64_t *cd = a.cand + gid * nc;
+    uint64_t mn = KEY_MAX;
+    for (int c = l16; c < nc; c += 16) {
+        const uint64_t key = cd[c];
+        mn = key < mn ? key : mn;
+    }
+    const float res = a.xres[gid];
+    float *x = xs + (wave * 4 + sub) * D;
+    float xn = 0.f;
+    for (int d = l16 * 4; d < D; d += 64) {
+        const f32x4 v = *(const f32x4 *)(a.X + gid * D + d), m = *(const f32x4 *)(a.mu + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x[d + e] = v[e];
+            xn = fmaf(v[e] - m[e], v[e] - m[e], xn);
+        }
+    }
+    xn = row16_sum(xn);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        const uint64_t other = shfl_xor_u64(mn, o);
+        mn = other < mn ? other : mn;
+    }
+    const float dmin = __uint_as_float((uint32_t)(mn >> 32));
+    const float band = dmin + nn_half_band(xn, res, rho, big, dmin, a.band_dist, D);
+    uint64_t bk = KEY_MAX;
+    bool hard = mn == KEY_MAX; // (non-finite input)
+    for (int c0 = 0; c0 < nc; c0 += 16) {
+        const uint64_t key = c0 + l16 < nc ? cd[c0 + l16] : KEY_MAX;
+        const bool inb = key != KEY_MAX && !(__uint_as_float((uint32_t)(key >> 32)) > band);
+        uint32_t mask = (uint32_t)(__ballot(inb) >> (16 * sub)) & 0xFFFFu; // this vector's
+        while (__ballot(mask != 0)) { // (all lanes stay: the sums cross lanes)
+            const int src = mask ? __ffs(mask) - 1 : 0;
+            const uint32_t idx = (uint32_t)__shfl((int)(uint32_t)key, 16 * sub + src, 64);
+            const bool on = mask != 0 && !(idx & VLQ_NN_SLOT);
+            hard = hard || (mask != 0 && (idx & VLQ_NN_SLOT));
+            mask &= mask - 1;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t i = on ? idx + 32 * j : 0u;
+                const float d = sqdist16(x, a.C + (int64_t)min(i, (uint32_t)a.k - 1) * D, D, l16, true);
+                if (on && i < (uint32_t)a.k) {
+                    const uint64_t ek = make_key(d, i);
+                    bk = ek < bk ? ek : bk;
+                }
+            }
+        }
+    }
+    // the few left over, one at a time by the whole wave
+    uint64_t left = __ballot(hard && g0 + sub < a.nb);
+    while (left) {
+        const int s = (__ffsll((unsigned long long)left) - 1) >> 4;
+        left &= ~(0xFFFFull << (16 * s));
+        const float sn = __shfl(xn, 16 * s, 64);
+        const uint64_t got = nearest_cell(a, g0 + s, xs + (wave * 4 + s) * D, sn, lane, true);
+        if (sub == s) bk = got;
+    }
+    if (l16 == 0 && g0 + sub < a.nb) a.cell[gid] = (int32_t)(uint32_t)bk;
+}
+
 // The byte of lambda and the residual for the chosen line (Eq. 12-13), in fp64 so that both are
 // known to the rounding of their own size: lambda is taken as the projection
 // <x - c_i, s_ij - c_i> / ||s_ij - c_i||^2, which is Eq. 8 with a, b and c written out (the same
@@ -540,6 +617,12 @@ void launch_encode_finish(const EncodeArgs &a, hipStream_t st)
         default: ENC2_LAUNCH(16); break;
         }
 #undef ENC2_LAUNCH
+        return;
+    }
+    // nearest centroid only, from the fp16 product
+    if (!a.S && a.bhdr && a.D <= 128 && a.D % 4 == 0 && (((uintptr_t)a.X) | ((uintptr_t)a.C) | ((uintptr_t)a.mu)) % 16 == 0) {
+        const unsigned grid1 = (unsigned)((a.nb + NC_NT / 16 - 1) / (NC_NT / 16));
+        hipLaunchKernelGGL(k_nearest_cells, dim3(grid1), dim3(NC_NT), (size_t)(NC_NT / 16) * a.D * 4, st, a);
         return;
     }
     int PB = (int)(65536 / ((size_t)a.D * 4));
