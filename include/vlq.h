@@ -90,7 +90,7 @@ enum {
  * changes what is computed, only by which kernel).  Values are 0 / 1 unless stated.
  */
 enum {
-    VLQ_OPT_COARSE_FP32 = 0,      /* 1: cells and nearest centroids from the fp32 contraction, not the bf16 one */
+    VLQ_OPT_COARSE_FP32 = 0,      /* 1: cells and nearest centroids from the fp32 contraction, not the 16-bit ones */
     VLQ_OPT_NEIGHBOURS_PER_QUERY, /* 1: distances to the neighbour centroids per query, not cell by cell over the batch */
     VLQ_OPT_SCAN_PACKED,          /* -1 (default): by mean list length; 0: one list per wave at a time; 1: short lists packed */
     VLQ_OPT_SCAN_GENERIC,         /* 1: the scan with per-cell / per-sub-region tables (2m lookups, Sec. 3.3.2) for every shape */
