@@ -74,6 +74,15 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
     return v;
 }
 
+// Orders the LDS traffic of one wave across its lanes: what any lane wrote before is what every lane reads behind.
+// The hardware keeps the order of a wave's LDS operations by itself; the compiler has to be told.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ||x - c||^2 by one wave: x in LDS (or any memory), c a global row.  Lanes
 // stride over the dimensions, partial sums are combined by a butterfly, so the
 // result is the same in all lanes and independent of the launch shape.

@@ -189,6 +189,7 @@ __global__ __launch_bounds__(NC_NT) void k_nearest_cells(EncodeArgs a)
         }
     }
     xn = row16_sum(xn);
+    wave_lds_order(); // the sums below read what the other lanes have written
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) {
         const uint64_t other = shfl_xor_u64(mn, o);
@@ -296,6 +297,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish(EncodeArgs a, int PB)
             xn = fmaf(vc, vc, xn);
         }
         xn = wave_sum(xn);
+        wave_lds_order(); // every lane reads the whole of x from here on
         const uint64_t bk = nearest_cell(a, gid, x, xn, lane, vec16);
         const int cell = (int)(uint32_t)bk;
         const float av = ord2f((uint32_t)(bk >> 32));
@@ -427,6 +429,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
             xn = fmaf(vc, vc, xn);
         }
         xn = wave_sum(xn);
+        wave_lds_order(); // every lane reads the whole of x from here on
         const uint64_t bk = nearest_cell(a, gid, x, xn, lane, vec16);
         const int cell = (int)(uint32_t)bk;
         const float av = ord2f((uint32_t)(bk >> 32));
@@ -515,6 +518,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
     if (PB == ENC_FEW_PB) {
         // phase 2, a vector per wave: lane l takes codewords 4 l .. 4 l + 3 (the wave's residual is its own work)
         if (wave < np) {
+            wave_lds_order();
             const float *r = res + wave * RS;
             const float *w = a.P + (int64_t)lane * 4 * DS;
             for (int p = 0; p < m; ++p, w += 256 * DS) {
