@@ -20,12 +20,10 @@
 // 2m-lookup scan, which builds m * 256 table entries per 19-point list and sorts its whole buffer of keys at every
 // cut.  With the K fast distances as results it would be 0.163 ms: the rest is the 1.5M points taken again, 1.5 KB
 // of centroid and codeword rows each.
+#include "bounds.h"
 #include "common.h"
 
-#define SW_NT 512
 #define SW_NW (SW_NT / 64)
-#define SW_U 4                        // chunks of 64 points per wave and turn
-#define SW_TURN (SW_NT * SW_U)        // points per workgroup and turn
 #define SW_CAP (2 * SW_TURN)          // candidate keys per workgroup
 #define SW_BINS SW_NT               // one bin of the selection's histogram per thread
 static_assert(SW_CAP - SW_TURN >= VLQ_MAX_K, "the K best and one turn's candidates fit the buffer");
@@ -72,7 +70,7 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
     float *yv = T + a.m * 256;                      // [D]
     const int lcap = (lists_max + 3) & ~3;
     float2 *lab = (float2 *)(yv + ((a.D + 3) & ~3)); // [lists] a, b - a
-    int *lend = (int *)(lab + lcap);                // [lists] where the list ends in the concatenation
+    sw_place_t *lend = (sw_place_t *)(lab + lcap);  // [lists] where the list ends in the concatenation
     uint32_t *lsh = (uint32_t *)(lend + lcap);      // [lists] position in the arrays minus place in the concatenation
     uint16_t *lat = (uint16_t *)(lsh + lcap);       // [lists] the list's descriptor
     __shared__ int hist[SW_BINS];
@@ -99,7 +97,8 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
     }
     if (tid < VLQ_MAX_M) sh_wmax[tid] = 0;
     // the visited lists that hold points, in the order of the descriptors (at most VLQ_MAX_W2 = 4 x SW_NT)
-    int nl = 0, total = 0;
+    int nl = 0;
+    sw_place_t total = 0;
     for (int s0 = r0; s0 < r1; s0 += SW_NT) {
         const int s = s0 + tid;
         uint4 d = make_uint4(0u, 0u, 0u, 0u);
@@ -141,14 +140,14 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
         }
         if (len > 0) {
             const int slot = nl + at + __popcll(some & ((1ull << lane) - 1ull));
-            const int e = total + before + end;
+            const sw_place_t e = total + (sw_place_t)(before + end);
             lend[slot] = e;
-            lsh[slot] = beg - (uint32_t)(e - len);
+            lsh[slot] = beg - (e - (sw_place_t)len);
             lab[slot] = make_float2(av, bav);
             lat[slot] = (uint16_t)s;
         }
         nl += alln;
-        total += all;
+        total += (sw_place_t)all;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -207,8 +206,8 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
     }
 
     // the 2m-lookup distance of point p of the concatenation (list slot j) by one lane
-    auto full_distance = [&](int p, int j) -> float {
-        const uint32_t g = (uint32_t)p + lsh[j];
+    auto full_distance = [&](sw_place_t p, int j) -> float {
+        const uint32_t g = p + lsh[j];
         const uint4 d = dq[lat[j]];
         const int i = (int)d.x / a.n;
         const float *ci = a.C + (int64_t)i * D, *sj = a.C + (int64_t)a.S[d.x] * D;
@@ -354,8 +353,8 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
             sh_thr = KEY_MAX;
         }
         __syncthreads();
-        for (int turn = 0; turn < total; turn += SW_TURN) {
-            const int base = turn + wave * (64 * SW_U);
+        for (sw_place_t turn = 0; turn < total; turn += SW_TURN) {
+            const sw_place_t base = sw_wave_base(turn, wave);
             const bool any = base < total; // uniform over the wave
             uint32_t g[SW_U];
             int jl[SW_U];
@@ -370,20 +369,20 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
                 }
 #pragma unroll
                 for (int u = 0; u < SW_U; ++u) jl[u] = j0;
-                const int stop = min(base + 64 * SW_U, total) - 1; // last point of the wave
+                const sw_place_t stop = min(base + 64 * SW_U, total) - 1; // last point of the wave
                 for (int jb = j0; jb < nl; jb += 64) {
-                    const int e = lend[min(jb + lane, nl - 1)];
+                    const sw_place_t e = lend[min(jb + lane, nl - 1)];
                     const int cross = __popcll(__ballot(jb + lane < nl && e <= stop)); // lists that end inside the run
                     for (int i = 0; i < cross; ++i) {
-                        const int ei = __builtin_amdgcn_readlane(e, i);
+                        const sw_place_t ei = (sw_place_t)__builtin_amdgcn_readlane((int)e, i);
 #pragma unroll
-                        for (int u = 0; u < SW_U; ++u) jl[u] += ei <= min(base + 64 * u + lane, stop);
+                        for (int u = 0; u < SW_U; ++u) jl[u] += ei <= min(sw_place(base, u, lane), stop);
                     }
                     if (cross < 64) break;
                 }
 #pragma unroll
                 for (int u = 0; u < SW_U; ++u) {
-                    g[u] = (uint32_t)min(base + 64 * u + lane, stop) + lsh[jl[u]]; // idle lanes repeat the last point
+                    g[u] = min(sw_place(base, u, lane), stop) + lsh[jl[u]]; // idle lanes repeat the last point
                     const uint8_t *cp = a.codes + (size_t)g[u] * m;
                     if (M > 0) __builtin_memcpy(cw[u], M % 4 == 0 ? __builtin_assume_aligned(cp, 4) : cp, M);
                     lb[u] = a.lam[g[u]];
@@ -403,8 +402,8 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
             if (any) {
 #pragma unroll
                 for (int u = 0; u < SW_U; ++u) {
-                    if (base + 64 * u >= total) break; // uniform over the wave
-                    const bool live = base + 64 * u + lane < total;
+                    if (sw_place(base, u, 0) >= total) break; // uniform over the wave
+                    const bool live = sw_place(base, u, lane) < total;
                     const float2 ab = lab[jl[u]];
                     const uint8_t *cp = a.codes + (size_t)g[u] * m;
                     float ts = 0.f;
@@ -418,8 +417,8 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
                     const float lba = l * ab.y;
                     const float dist = (sv[u] - ts) + (lba + ab.x);
                     bool pass = live && !(dist > thr_f); // (a NaN is a candidate, as in the 2m-lookup scan)
-                    const int p = base + 64 * u + lane;
-                    uint64_t key = make_key(dist, (uint32_t)p);
+                    const sw_place_t p = sw_place(base, u, lane);
+                    uint64_t key = make_key(dist, p);
                     if (exact && pass) {
                         key = make_key(full_distance(p, jl[u]), (uint32_t)a.ids[g[u]]);
                         pass = key < thr; // K keys at or below the threshold are in the buffer already
@@ -453,7 +452,7 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
             // of different points overlap); the upper half of the buffer is free
             static_assert(SW_CAP - SW_TURN <= SW_CAP / 2, "what a cut leaves fits half the buffer");
             for (int at = tid; at < cnt; at += SW_NT) {
-                const int p = (int)(uint32_t)keys[at];
+                const sw_place_t p = (sw_place_t)keys[at];
                 int lo = 0, hi = nl - 1; // first list that ends behind p
                 while (lo < hi) {
                     const int mid = (lo + hi) >> 1;
@@ -463,7 +462,7 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
                         hi = mid;
                 }
                 const int label = (int)dq[lat[lo]].x;
-                keys[at] = ((uint64_t)(uint32_t)lat[lo] << 32) | ((uint32_t)p + lsh[lo]);
+                keys[at] = ((uint64_t)(uint32_t)lat[lo] << 32) | (p + lsh[lo]);
                 keys[SW_CAP / 2 + at] = ((uint64_t)(uint32_t)a.S[label] << 32) | (uint32_t)(label / a.n);
             }
             __syncthreads();
