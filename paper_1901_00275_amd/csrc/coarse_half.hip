@@ -5,7 +5,8 @@
 // below the largest value before a component is flushed to zero.  How far a row's image is from the row is
 // measured when the image is written (residual norm), so the error of a product is bounded by Cauchy-Schwarz
 // from what was actually lost: |<a, b> - <a', b'>| <= |a - a'||b| + |a'||b - b'|; integer-valued descriptors lose
-// nothing.  Every column inside the band of the row minimum is handed on and re-evaluated as a direct fp32 sum
+// nothing.  A block whose rows differ by more than HALF_GAP binades (a corrupt vector among ordinary ones) gets a scale
+// per row, so that no row loses its components to another's size.  Every column inside the band of the row minimum is handed on and re-evaluated as a direct fp32 sum
 // of squared differences, so the decision is taken in fp32 exactly, whatever the product's precision.
 // (The form before split both operands into two bf16 parts and multiplied two or three pairs of pages: 213 571 x 128
 // integer vectors against 65 536 centroids 7.67 ms, 4.19 ms so, 0.86 PFLOP/s; 2^18 x 96 against 16 384: 2.26 and 1.02 ms.)
@@ -21,6 +22,8 @@
 // columns (j = 0, 1) that a lane sees of a row enter the running two smallest as one key, their smaller value.
 #include "common.h"
 
+#include <type_traits>
+
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -29,18 +32,22 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define HALF_NORMAL 6.103515625e-5f // 2^-14: smaller halves are written as zero
 #define NO_COLUMN 3e38f // "norm" of columns past the end: finite, so that index bits can be planted in the key
 #define NO_KEY 1e38f    // from here on a key counts as absent
+// Rows up to 10 binades below their block's largest keep 18 binades of their own before a component is flushed, and
+// their residual is that of the rounding alone.
+#define HALF_GAP 10
 
 size_t half_image_bytes(int64_t rows, int D)
 {
     const int64_t blocks = (rows + HT - 1) / HT;
-    return 256 + ((size_t)blocks * 4 + 255) / 256 * 256 + (size_t)blocks * HT * D * 2;
+    return 256 + ((size_t)blocks * 4 + 255) / 256 * 256 + (size_t)blocks * HT * 4 + (size_t)blocks * HT * D * 2;
 }
 
 // header (256 bytes: [0] largest relative residual of a row, [1] largest residual of the rows whose relative one is
-// beyond fp16's rounding), scales, pages
+// beyond fp16's rounding), scales, rows' inverse scales, pages
 struct HalfImage {
     float *hdr;
-    float *scale; // [blocks] a block's values are multiplied by this
+    float *scale; // [blocks] a block's values are multiplied by this; 0: every row has its own
+    float *rinv;  // [blocks][HT] 1 / scale of the row, of the blocks whose scale is 0
     u32x4 *pages;
     HalfImage(const void *img, int64_t rows)
     {
@@ -48,7 +55,8 @@ struct HalfImage {
         const int64_t blocks = (rows + HT - 1) / HT;
         hdr = (float *)p;
         scale = (float *)(p + 256);
-        pages = (u32x4 *)(p + 256 + ((size_t)blocks * 4 + 255) / 256 * 256);
+        rinv = (float *)(p + 256 + ((size_t)blocks * 4 + 255) / 256 * 256);
+        pages = (u32x4 *)(rinv + blocks * HT);
     }
 };
 
@@ -57,17 +65,29 @@ __global__ void k_half_header(float *hdr)
     if (threadIdx.x < 2) hdr[threadIdx.x] = 0.f;
 }
 
+// Exponent that brings mx to [2^14, 2^15); at most 2^+-60, so that the product of two inverse scales stays in range
+// (beyond that the squared norms of the rows overflow or vanish in fp32 as well)
+__device__ __forceinline__ int half_exponent(float mx)
+{
+    const int ex = mx > 0.f ? 14 - ((int)(__float_as_uint(mx) >> 23) - 127) : 0;
+    return max(-60, min(60, ex));
+}
+__device__ __forceinline__ float pow2f(int ex) { return __uint_as_float((uint32_t)(127 + ex) << 23); }
+
 // One workgroup per block of 128 rows, a thread per (row, chunk of 8 values), SPT times: one pass over X gives the
 // block's scale, the pages, and per row the squared norm and the residual's norm.  Bound by memory.
 template <int SPT>
 __global__ __launch_bounds__(256) void k_half_image(const float *__restrict__ X, int64_t rows,
                                                     const float *__restrict__ mu, float *__restrict__ hdr,
-                                                    float *__restrict__ scale, u32x4 *__restrict__ pages,
+                                                    float *__restrict__ scale, float *__restrict__ rinv,
+                                                    u32x4 *__restrict__ pages,
                                                     float *__restrict__ norm2, float *__restrict__ resid)
 {
     constexpr int D = SPT * 16, CPR = SPT * 2;
     __shared__ float pn[HT][CPR + 1], pr[HT][CPR + 1];
     __shared__ float wmax[4];
+    __shared__ int rex[HT]; // exponents of the rows' scales, where every row has its own
+    __shared__ int apart;
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t blk = blockIdx.x;
     float v[SPT][8];
@@ -91,45 +111,48 @@ __global__ __launch_bounds__(256) void k_half_image(const float *__restrict__ X,
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
     if (lane == 0) wmax[tid >> 6] = mx;
+    if (tid == 0) apart = 0;
     __syncthreads();
     mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-    // largest magnitude to [2^14, 2^15); at most 2^+-60, so that the product of two inverse scales stays in range
-    // (beyond that the squared norms of the rows overflow or vanish in fp32 as well)
-    int ex = mx > 0.f ? 14 - ((int)(__float_as_uint(mx) >> 23) - 127) : 0;
-    ex = max(-60, min(60, ex));
-    const float s = __uint_as_float((uint32_t)(127 + ex) << 23), inv = __uint_as_float((uint32_t)(127 - ex) << 23);
-    if (tid == 0) scale[blk] = s;
+    const int ex = half_exponent(mx);
+    const float sb = pow2f(ex);
+    if (tid == 0) scale[blk] = sb;
+    // pages, norms and residuals at one scale for the block or (own) with a scale per row
+    auto write = [&](bool own) {
 #pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-        const int i = j * 256 + tid, r = i / CPR, ch = i - r * CPR;
-        half8 h;
-        float n2 = 0.f, r2 = 0.f;
+        for (int j = 0; j < SPT; ++j) {
+            const int i = j * 256 + tid, r = i / CPR, ch = i - r * CPR;
+            const float s = own ? pow2f(rex[r]) : sb;
+            half8 h;
+            float n2 = 0.f, r2 = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float t = v[j][e] * s;
-            _Float16 q = (_Float16)t;
-            if (fabsf((float)q) < HALF_NORMAL) q = (_Float16)0.f;
-            const float d = t - (float)q;
-            n2 = fmaf(t, t, n2);
-            r2 = fmaf(d, d, r2);
-            h[e] = q;
+            for (int e = 0; e < 8; ++e) {
+                const float t = v[j][e] * s;
+                _Float16 q = (_Float16)t;
+                if (fabsf((float)q) < HALF_NORMAL) q = (_Float16)0.f;
+                const float d = t - (float)q;
+                n2 = fmaf(t, t, n2);
+                r2 = fmaf(d, d, r2);
+                h[e] = q;
+            }
+            pn[r][ch] = n2;
+            pr[r][ch] = r2;
+            pages[(blk * SPT + (ch >> 1)) * HPAGE + 2 * r + ((ch & 1) ^ ((r >> 2) & 1))] = __builtin_bit_cast(u32x4, h);
         }
-        pn[r][ch] = n2;
-        pr[r][ch] = r2;
-        pages[(blk * SPT + (ch >> 1)) * HPAGE + 2 * r + ((ch & 1) ^ ((r >> 2) & 1))] = __builtin_bit_cast(u32x4, h);
-    }
-    __syncthreads();
-    if (tid < HT) {
+        __syncthreads();
+        if (tid >= HT) return;
         float n2 = 0.f, r2 = 0.f;
 #pragma unroll
         for (int c = 0; c < CPR; ++c) {
             n2 += pn[tid][c];
             r2 += pr[tid][c];
         }
+        const float inv = pow2f(own ? -rex[tid] : -ex);
         const float nrm = sqrtf(n2), res = sqrtf(r2) * 1.0001f; // (the rounding of the sums)
         const int64_t row = blk * HT + tid;
         if (row < rows && norm2) norm2[row] = n2 * inv * inv;
         if (row < rows && resid) resid[row] = res * inv;
+        if (!own && !hdr && row < rows && nrm < pow2f(14 - HALF_GAP)) apart = 1;
         if (hdr) {
             const bool ok = res < INFINITY && n2 > 0.f; // (a non-finite row's products never count)
             float rel = ok && res <= 5e-4f * nrm ? res / nrm * 1.0001f : 0.f;
@@ -144,7 +167,35 @@ __global__ __launch_bounds__(256) void k_half_image(const float *__restrict__ X,
                 if (big > ((volatile float *)hdr)[1]) atomicMax((unsigned *)hdr + 1, __float_as_uint(big));
             }
         }
+    };
+    write(false);
+    if (hdr) return; // (the columns keep one scale per block: what a column loses is bounded by the header)
+    __syncthreads();
+    if (!apart) return;
+    // a row far below the block's largest: its own size decides (a row of zeros is no reason)
+#pragma unroll
+    for (int j = 0; j < SPT; ++j) {
+        const int i = j * 256 + tid, r = i / CPR, ch = i - r * CPR;
+        float cm = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float m = fabsf(v[j][e]);
+            if (m < INFINITY) cm = fmaxf(cm, m);
+        }
+        pn[r][ch] = cm;
     }
+    __syncthreads();
+    bool own = false;
+    if (tid < HT) {
+        float rm = 0.f;
+        for (int c = 0; c < CPR; ++c) rm = fmaxf(rm, pn[tid][c]);
+        rex[tid] = half_exponent(rm);
+        rinv[blk * HT + tid] = pow2f(-rex[tid]);
+        own = rm > 0.f && rex[tid] > ex + HALF_GAP;
+    }
+    if (!__syncthreads_or(own)) return;
+    if (tid == 0) scale[blk] = 0.f;
+    write(true);
 }
 
 void launch_half_image(const float *X, int64_t rows, int D, const float *mu, void *img, bool header, float *norm2,
@@ -155,8 +206,8 @@ void launch_half_image(const float *X, int64_t rows, int D, const float *mu, voi
     const dim3 grid((unsigned)((rows + HT - 1) / HT));
     if (header) hipLaunchKernelGGL(k_half_header, dim3(1), dim3(64), 0, st, h.hdr);
 #define HALF_LAUNCH(S)                                                                                         \
-    hipLaunchKernelGGL(k_half_image<S>, grid, dim3(256), 0, st, X, rows, mu, header ? h.hdr : nullptr, h.scale, h.pages, \
-                       norm2, resid)
+    hipLaunchKernelGGL(k_half_image<S>, grid, dim3(256), 0, st, X, rows, mu, header ? h.hdr : nullptr, h.scale, h.rinv, \
+                       h.pages, norm2, resid)
     switch (D / 16) {
     case 2: HALF_LAUNCH(2); break;
     case 4: HALF_LAUNCH(4); break;
@@ -168,7 +219,7 @@ void launch_half_image(const float *X, int64_t rows, int D, const float *mu, voi
 
 struct HalfArgs {
     const u32x4 *A, *B;
-    const float *ascale, *bscale, *bhdr;
+    const float *ascale, *arinv, *bscale, *bhdr;
     int M, N;
     const float *an, *ares, *bn;
     int nsplit, tiles_per_split;
@@ -181,6 +232,7 @@ template <int SPT>
 __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
 {
     extern __shared__ u32x4 lds[]; // two tiles of B: [2][SPT][HPAGE]; the tail of the kernel reuses the front
+    float *rinv = (float *)(lds + 2 * SPT * HPAGE); // [HT] inverse scales of the rows, where every row has its own
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
@@ -237,43 +289,54 @@ __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
         fetch_cols(t0);
         copy_tile(t0);
     }
-    for (int t = t0; t < t1; ++t) {
-        // this tile has arrived (every wave waits for its own copies), and the other half of the ring is free
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        float cb[2];
+    if (aexp == 0u && tid < HT) rinv[tid] = a.arinv[m0 + tid]; // (read behind the first tile's barrier)
+    // OWN: every row has a scale of its own, and the keys of a row are formed with it
+    auto sweep = [&](auto OWN) {
+        constexpr bool own = decltype(OWN)::value;
+        for (int t = t0; t < t1; ++t) {
+            // this tile has arrived (every wave waits for its own copies), and the other half of the ring is free
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            float cb[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) cb[j] = (int64_t)t * HT + wn + 32 * j + (lane & 31) < a.N ? cbn[j] : NO_COLUMN;
-        // -2 / (scale of the rows * scale of the columns): powers of two, 1 / 2^x by its exponent
-        const float inv = -2.f * __uint_as_float(0x7F000000u - aexp) * __uint_as_float(0x7F000000u - __float_as_uint(scn));
-        if (t + 1 < t1) {
-            fetch_cols(t + 1);
-            copy_tile(t + 1);
-        }
-        const u32x4 *bp = lds + ((t - t0) & 1) * SPT * HPAGE + 2 * wn + fpos;
-        f32x16 acc[2][2];
+            for (int j = 0; j < 2; ++j) cb[j] = (int64_t)t * HT + wn + 32 * j + (lane & 31) < a.N ? cbn[j] : NO_COLUMN;
+            // -2 / (scale of the rows * scale of the columns): powers of two, 1 / 2^x by its exponent
+            const float binv = -2.f * __uint_as_float(0x7F000000u - __float_as_uint(scn));
+            const float inv = own ? binv : binv * __uint_as_float(0x7F000000u - aexp);
+            if (t + 1 < t1) {
+                fetch_cols(t + 1);
+                copy_tile(t + 1);
+            }
+            const u32x4 *bp = lds + ((t - t0) & 1) * SPT * HPAGE + 2 * wn + fpos;
+            f32x16 acc[2][2];
 #pragma unroll
-        for (int u = 0; u < SPT; ++u) {
-            half8 bh[2];
-            bh[0] = __builtin_bit_cast(half8, bp[u * HPAGE]);
-            bh[1] = __builtin_bit_cast(half8, bp[u * HPAGE + 64]);
+            for (int u = 0; u < SPT; ++u) {
+                half8 bh[2];
+                bh[0] = __builtin_bit_cast(half8, bp[u * HPAGE]);
+                bh[1] = __builtin_bit_cast(half8, bp[u * HPAGE + 64]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[u][i], bh[j], u == 0 ? zero16 : acc[i][j], 0, 0, 0);
+            }
+            const uint32_t tj = (uint32_t)(t - t0);
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[u][i], bh[j], u == 0 ? zero16 : acc[i][j], 0, 0, 0);
+                for (int r = 0; r < 16; ++r) {
+                    const float f = own ? inv * rinv[slot_row(i, r)] : inv;
+                    const float e = fminf(fmaf(f, acc[i][0][r], cb[0]), fmaf(f, acc[i][1][r], cb[1]));
+                    const float key = __uint_as_float((__float_as_uint(e) & keep) | tj);
+                    b2[i][r] = __builtin_amdgcn_fmed3f(b1[i][r], b2[i][r], key);
+                    b1[i][r] = fminf(b1[i][r], key);
+                }
         }
-        const uint32_t tj = (uint32_t)(t - t0);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float e = fminf(fmaf(inv, acc[i][0][r], cb[0]), fmaf(inv, acc[i][1][r], cb[1]));
-                const float key = __uint_as_float((__float_as_uint(e) & keep) | tj);
-                b2[i][r] = __builtin_amdgcn_fmed3f(b1[i][r], b2[i][r], key);
-                b1[i][r] = fminf(b1[i][r], key);
-            }
-    }
+    };
+    if (aexp != 0u)
+        sweep(std::false_type{});
+    else
+        sweep(std::true_type{});
 
     // ---- row minimum over the workgroup, then every kept key inside the band of it ----
     __syncthreads(); // the tiles are dead from here on
@@ -338,6 +401,7 @@ int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D,
     HalfArgs a = {};
     a.A = A.pages;
     a.ascale = A.scale;
+    a.arinv = A.rinv;
     a.B = B.pages;
     a.bscale = B.scale;
     a.bhdr = B.hdr;
@@ -359,8 +423,8 @@ int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D,
     *band_dist = a.band_dist;
     *bhdr = B.hdr;
     if (M <= 0 || N <= 0) return 0;
-    const size_t tail = HT * (8 + 8 * VLQ_NN_CANDS), ring = (size_t)2 * (D / 16) * HPAGE * 16;
-    const size_t bytes = ring > tail ? ring : tail;
+    // the ring of tiles (the tail of the kernel takes HT * (8 + 8 * VLQ_NN_CANDS) bytes of it) and the rows' scales
+    const size_t bytes = (size_t)2 * (D / 16) * HPAGE * 16 + HT * 4;
     const dim3 grid((unsigned)((M + HT - 1) / HT), (unsigned)nsplit);
     auto go = [&](auto kern) -> int {
         if (bytes > 49152) { // (48 KB of dynamic LDS need no asking)

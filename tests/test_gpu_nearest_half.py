@@ -47,3 +47,59 @@ def test_nearest_centroid(kind, nt, D, k):
         if kind == "same":
             exact = got == d.min(1)
             assert np.array_equal(cell[s:s + 64][exact], d.argmin(1)[exact])
+
+
+def rows_apart(nt, D, k, seed=0):
+    """Centroids and vectors of ordinary size, and a few vectors ten million times as large among them."""
+    rng = np.random.default_rng(seed)
+    C = rng.normal(size=(k, D))
+    X = C[rng.integers(0, k, nt)] + rng.normal(scale=0.3, size=(nt, D))
+    far = np.arange(5, nt, 211)
+    X[far] *= 1e7
+    return X.astype(np.float32), C.astype(np.float32), far
+
+
+@pytest.mark.parametrize("nt,D,k", [(300, 128, 700), (1000, 32, 129), (128, 96, 4096), (129, 64, 1000)])
+@pytest.mark.parametrize("kind", ["far", "spread", "lost"])
+def test_rows_of_one_block_differ_in_size(kind, nt, D, k):
+    X, C, far = rows_apart(nt, D, k)
+    rng = np.random.default_rng(1)
+    ok = np.ones(nt, bool)
+    if kind == "spread":  # any size from 1e-6 to 1e6
+        X *= (10.0 ** rng.uniform(-6, 6, (nt, 1))).astype(np.float32)
+    elif kind == "lost":  # beside 1e23 the squares of the others vanish (and its own overflows: any cell will do)
+        X[far] = 1e23
+        X[~np.isin(np.arange(nt), far)] *= 1e-6
+        C *= 1e-6
+        ok[far] = False
+    cell = assign(X, C)
+    assert ((cell >= 0) & (cell < k)).all()
+    X64, C64 = X.astype(np.float64), C.astype(np.float64)
+    for i in np.flatnonzero(ok):
+        d = ((X64[i] - C64) ** 2).sum(1)
+        assert d[cell[i]] <= d.min() * (1 + 2 * (D + 1) * 2.0 ** -24), i
+
+
+def time_assign(X, C):
+    import paper_1901_00275_amd as vlq
+
+    Xd, Cd = torch.as_tensor(X).to(DEV), torch.as_tensor(C).to(DEV)
+    a = torch.empty(len(X), dtype=torch.int32, device=DEV)
+    best = float("inf")
+    for _ in range(4):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        vlq.vlq_kmeans(Xd, len(X), X.shape[1], len(C), 0, Cd, a, None)
+        t1.record()
+        t1.synchronize()
+        best = min(best, t0.elapsed_time(t1))
+    return best
+
+
+def test_small_rows_beside_ordinary_ones_cost_nothing():
+    """With one scale for a block, its small rows were lost and compared with every centroid one by one."""
+    X, C, far = rows_apart(60_000, 128, 16_384)
+    X[far] *= 1e-7
+    ordinary = time_assign(X, C)
+    X[::2] *= 1e-8
+    assert time_assign(X, C) < 2 * ordinary
