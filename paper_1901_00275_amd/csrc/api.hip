@@ -382,8 +382,8 @@ static int encode_impl(vlq_index *idx, const float *d_x, int64_t nb, int32_t *d_
         if (half) {
             launch_half_image(x, cnt, D, idx->mu_c, ximg, false, xn, xres, st);
             LAUNCHCHK();
-            HIPCHK((hipError_t)launch_nearest_half(ximg, (int)cnt, idx->Chalf, k, D, xn, xres, idx->cn, cand, nsplit,
-                                                   &a.band_dist, &a.bhdr, st));
+            HIPCHK((hipError_t)launch_nearest_half(ximg, (int)cnt, idx->Chalf, k, D, x, idx->C, xn, xres, idx->cn, cand,
+                                                   nsplit, &a.band_dist, &a.bhdr, st));
             a.xres = xres;
         } else {
             launch_row_norms(x, cnt, D, idx->mu_c, xn, st);
@@ -554,8 +554,8 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
             if (half) {
                 launch_half_image(x, n, D, mu_c, ximg, false, xn, xres, st);
                 LAUNCHCHK();
-                HIPCHK((hipError_t)launch_nearest_half(ximg, (int)n, cimg, k, D, xn, xres, cn, cand, nsplit, &a.band_dist,
-                                                       &a.bhdr, st));
+                HIPCHK((hipError_t)launch_nearest_half(ximg, (int)n, cimg, k, D, x, d_centroids, xn, xres, cn, cand, nsplit,
+                                                       &a.band_dist, &a.bhdr, st));
                 a.xres = xres;
             } else {
                 launch_row_norms(x, n, D, mu_c, xn, st);

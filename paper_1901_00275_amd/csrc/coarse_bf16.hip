@@ -551,29 +551,7 @@ __global__ __launch_bounds__(256) void k_cell_threshold(const float *__restrict_
     }
 }
 
-// direct ||y - c||^2 by 16 lanes (l16 = lane % 16), butterfly over the 16: same value in all of them
-__device__ __forceinline__ float sqdist16(const float *yv, const float *__restrict__ rowp, int D, int l16, bool vec)
-{
-    float acc = 0.f;
-    if (vec) {
-        for (int d = l16 * 4; d < D; d += 64) {
-            const f32x4 cv = *(const f32x4 *)(rowp + d);
-            const float t0 = yv[d] - cv.x, t1 = yv[d + 1] - cv.y, t2 = yv[d + 2] - cv.z, t3 = yv[d + 3] - cv.w;
-            acc = fmaf(t0, t0, acc);
-            acc = fmaf(t1, t1, acc);
-            acc = fmaf(t2, t2, acc);
-            acc = fmaf(t3, t3, acc);
-        }
-    } else {
-        for (int d = l16; d < D; d += 16) {
-            const float t = yv[d] - rowp[d];
-            acc = fmaf(t, t, acc);
-        }
-    }
-    return row16_sum(acc);
-}
-
-// the same sums for four rows at once (their loads in flight together)
+// sqdist16 for four rows at once (their loads in flight together)
 __device__ __forceinline__ void sqdist16x4(const float *yv, const float *const (&rowp)[4], int D, int l16, bool vec,
                                            float (&out)[4])
 {

@@ -20,6 +20,14 @@
 // one barrier per tile, and two workgroups per compute unit, so that one's selection overlaps the other's products.
 // Per tile a wave has 4 D / 16 MFMAs of 32 clocks (D = 128: 1 024) and 192 vector instructions of 4 clocks: the two
 // columns (j = 0, 1) that a lane sees of a row enter the running two smallest as one key, their smaller value.
+//
+// Crowded rows (more columns inside the band than the shortlist holds, or several of them in one lane's slot) would
+// leave the consumer whole slots or splits to compare: 65 536 rows of 512 bytes for one vector.  Where a strip has
+// enough of that, the workgroup multiplies its tiles a second time with the band known, takes the exact distance of
+// every column inside it and hands on the nearest.  Where even those are too many (a tenth of a tile's pairs: all
+// columns alike as far as fp16 sees them), the shortlists stay as they are.
+// (2^18 x 128, 16 384 centroids in groups of 16 / 64 with a spread of 0.04 |x|: 63 / 135 ms without, 3.6 / 3.7 ms with
+// the second sweep, 6.3 / 8.7 ms with two bf16 parts and no second sweep; 2.2 ms where nothing is crowded.)
 #include "common.h"
 
 #include <type_traits>
@@ -35,6 +43,13 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // Rows up to 10 binades below their block's largest keep 18 binades of their own before a component is flushed, and
 // their residual is that of the rounding alone.
 #define HALF_GAP 10
+#define PAIR_CAP 2048 // (row, column) pairs of the second sweep that wait for their exact distance
+#define PAIR_COL_BITS 25
+#define PAIR_BATCH 4  // pairs a group of 16 lanes has under way
+// From this many slots in a strip's shortlists on the strip takes the second sweep: a tile of it costs what the exact
+// distances of some 40 slots (two columns of every tile each) cost the consumer, one wave after another, and 8 to 64
+// measured alike.  A row with all columns in its shortlist is reason enough by itself.
+#define SLOTS_MAX 16
 
 size_t half_image_bytes(int64_t rows, int D)
 {
@@ -221,6 +236,8 @@ struct HalfArgs {
     const u32x4 *A, *B;
     const float *ascale, *arinv, *bscale, *bhdr;
     int M, N;
+    const float *X, *C; // the rows and columns themselves
+    bool vec;           // rows of C on 16 bytes
     const float *an, *ares, *bn;
     int nsplit, tiles_per_split;
     uint64_t *cand;
@@ -232,7 +249,11 @@ template <int SPT>
 __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
 {
     extern __shared__ u32x4 lds[]; // two tiles of B: [2][SPT][HPAGE]; the tail of the kernel reuses the front
-    float *rinv = (float *)(lds + 2 * SPT * HPAGE); // [HT] inverse scales of the rows, where every row has its own
+    float *rinv = (float *)(lds + 2 * SPT * HPAGE);               // [HT] inverse scales of the rows
+    unsigned long long *best = (unsigned long long *)(rinv + HT); // [HT] second sweep: nearest column so far
+    uint32_t *pairs = (uint32_t *)(best + HT);                    // [PAIR_CAP] row << PAIR_COL_BITS | column of the split
+    __shared__ uint8_t crowded[HT];
+    __shared__ int sh_pairs, sh_slots;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
@@ -290,13 +311,44 @@ __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
         copy_tile(t0);
     }
     if (aexp == 0u && tid < HT) rinv[tid] = a.arinv[m0 + tid]; // (read behind the first tile's barrier)
-    // OWN: every row has a scale of its own, and the keys of a row are formed with it
-    auto sweep = [&](auto OWN) {
-        constexpr bool own = decltype(OWN)::value;
+    // exact distances of the n pairs that wait, 16 lanes a pair
+    auto settle = [&](int n) {
+        const int grp = tid >> 4, l16 = tid & 15;
+        for (int p0 = 0; p0 < n; p0 += 16 * PAIR_BATCH) { // (the loads of a batch are under way together)
+            float d[PAIR_BATCH];
+            uint32_t e[PAIR_BATCH];
+#pragma unroll
+            for (int u = 0; u < PAIR_BATCH; ++u) {
+                e[u] = pairs[min(p0 + 16 * u + grp, n - 1)];
+                const int64_t row = m0 + (e[u] >> PAIR_COL_BITS), col = (int64_t)t0 * HT + (e[u] & ((1u << PAIR_COL_BITS) - 1u));
+                d[u] = sqdist16(a.X + row * (SPT * 16), a.C + col * (SPT * 16), SPT * 16, l16, a.vec);
+            }
+#pragma unroll
+            for (int u = 0; u < PAIR_BATCH; ++u)
+                if (p0 + 16 * u + grp < n && l16 == 0)
+                    atomicMin(&best[e[u] >> PAIR_COL_BITS],
+                              make_key(d[u], (uint32_t)t0 * HT + (e[u] & ((1u << PAIR_COL_BITS) - 1u))));
+        }
+    };
+    // OWN: the rows' scales are read from rinv, not one for the block.  EMIT (second sweep): b1 holds the rows' bands,
+    // and what lies inside is collected.  Returns false (to all threads) where a tile finds no room for its pairs.
+    auto sweep = [&](auto OWN, auto EMIT) -> bool {
+        constexpr bool own = decltype(OWN)::value, emit = decltype(EMIT)::value;
         for (int t = t0; t < t1; ++t) {
             // this tile has arrived (every wave waits for its own copies), and the other half of the ring is free
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
+            if (emit) {
+                const int n = sh_pairs;
+                __syncthreads(); // (read by all before the next tile adds to it)
+                if (n > PAIR_CAP) return false;
+                if (n > PAIR_CAP / 2) {
+                    settle(n);
+                    __syncthreads();
+                    if (tid == 0) sh_pairs = 0;
+                    __syncthreads();
+                }
+            }
             float cb[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) cb[j] = (int64_t)t * HT + wn + 32 * j + (lane & 31) < a.N ? cbn[j] : NO_COLUMN;
@@ -321,6 +373,33 @@ __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[u][i], bh[j], u == 0 ? zero16 : acc[i][j], 0, 0, 0);
             }
             const uint32_t tj = (uint32_t)(t - t0);
+            if constexpr (emit) {
+                uint32_t miss[2] = {0u, 0u};
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float f = inv * rinv[slot_row(i, r)];
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            miss[j] = __builtin_amdgcn_alignbit(
+                                miss[j], __float_as_uint(b1[i][r] - fmaf(f, acc[i][j][r], cb[j])), 31);
+                    }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const uint32_t col = tj * HT + wn + 32 * j + (lane & 31);
+                    uint32_t hit = (int64_t)t0 * HT + col < a.N ? ~miss[j] : 0u;
+                    while (hit) {
+                        const int b = __clz(hit); // bit 31 is the first row slot
+                        hit &= ~(0x80000000u >> b);
+                        const int rl = slot_row(b >> 4, b & 15);
+                        if (!crowded[rl]) continue; // (the products of a row with a NaN have any sign)
+                        const int at = atomicAdd(&sh_pairs, 1);
+                        if (at < PAIR_CAP) pairs[at] = ((uint32_t)rl << PAIR_COL_BITS) | col;
+                    }
+                }
+                continue;
+            }
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -332,17 +411,19 @@ __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
                     b1[i][r] = fminf(b1[i][r], key);
                 }
         }
+        return true;
     };
     if (aexp != 0u)
-        sweep(std::false_type{});
+        sweep(std::false_type{}, std::false_type{});
     else
-        sweep(std::true_type{});
+        sweep(std::true_type{}, std::false_type{});
 
     // ---- row minimum over the workgroup, then every kept key inside the band of it ----
     __syncthreads(); // the tiles are dead from here on
     unsigned *rowmin = (unsigned *)lds;                                // [HT]
     int *rowcnt = (int *)(rowmin + HT);                                // [HT]
     unsigned long long *rowcand = (unsigned long long *)(rowcnt + HT); // [HT][VLQ_NN_CANDS]
+    if (tid == 0) sh_slots = 0;
     if (tid < HT) {
         rowmin[tid] = 0xFFFFFFFFu;
         rowcnt[tid] = 0;
@@ -357,17 +438,20 @@ __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
             if (b1[i][r] < NO_KEY) atomicMin(&rowmin[slot_row(i, r)], f2ord(b1[i][r]));
     __syncthreads();
     const float rho = a.bhdr[0], big = a.bhdr[1];
+    // where the band of row rl (one with a minimum) ends
+    auto band_end = [&](int rl) {
+        const float ra = a.an[m0 + rl];
+        const float emin = __uint_as_float(__float_as_uint(ord2f(rowmin[rl])) & keep);
+        const float dmin = fmaxf(emin + ra, 0.f);
+        return emin + nn_half_band(ra, a.ares[m0 + rl], rho, big, dmin, a.band_dist, SPT * 16);
+    };
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int rl = slot_row(i, r);
-            const uint32_t mo = rowmin[rl];
-            if (mo == 0xFFFFFFFFu || m0 + rl >= a.M) continue;
-            const float ra = a.an[m0 + rl];
-            const float emin = __uint_as_float(__float_as_uint(ord2f(mo)) & keep);
-            const float dmin = fmaxf(emin + ra, 0.f);
-            const float band = emin + nn_half_band(ra, a.ares[m0 + rl], rho, big, dmin, a.band_dist, SPT * 16);
+            if (rowmin[rl] == 0xFFFFFFFFu || m0 + rl >= a.M) continue;
+            const float ra = a.an[m0 + rl], band = band_end(rl);
             const float e = __uint_as_float(__float_as_uint(b1[i][r]) & keep);
             if (!(b1[i][r] < NO_KEY) || !(e <= band)) continue;
             // the key stands for both columns of its tile; a second one inside the band may have pushed out a
@@ -380,22 +464,60 @@ __global__ __launch_bounds__(256, 2) void k_nearest_half(HalfArgs a)
                 rowcand[rl * VLQ_NN_CANDS + pos] = ((uint64_t)__float_as_uint(fmaxf(e + ra, 0.f) + 0.f) << 32) | entry;
         }
     __syncthreads();
+    uint64_t *dst = nullptr;
+    uint64_t near = 0; // high word of the split's smallest key
+    int slots = 0;
     if (tid < HT && m0 + tid < a.M) {
-        uint64_t *dst = a.cand + ((m0 + tid) * a.nsplit + split) * VLQ_NN_CANDS;
+        dst = a.cand + ((m0 + tid) * a.nsplit + split) * VLQ_NN_CANDS;
         const bool all = rowcnt[tid] > VLQ_NN_CANDS; // more than there is room for: the split's columns
         const float emin = __uint_as_float(__float_as_uint(ord2f(rowmin[tid])) & keep);
-        const uint64_t whole =
-            ((uint64_t)__float_as_uint(fmaxf(emin + a.an[m0 + tid], 0.f) + 0.f) << 32) | VLQ_NN_ALL;
+        near = (uint64_t)__float_as_uint(fmaxf(emin + a.an[m0 + tid], 0.f) + 0.f) << 32;
+        slots = all ? SLOTS_MAX : 0;
 #pragma unroll
         for (int s = 0; s < VLQ_NN_CANDS; ++s) {
             const uint64_t key = rowcand[tid * VLQ_NN_CANDS + s];
-            dst[s] = all ? (s == 0 ? whole : KEY_MAX) : key;
+            if (!all && key != KEY_MAX && ((uint32_t)key & VLQ_NN_SLOT)) ++slots;
+            dst[s] = all ? (s == 0 ? near | VLQ_NN_ALL : KEY_MAX) : key;
         }
+        if (slots) atomicAdd(&sh_slots, slots);
+    }
+    __syncthreads();
+    if (sh_slots < SLOTS_MAX || a.tiles_per_split > (1 << (PAIR_COL_BITS - 7))) return;
+
+    // ---- second sweep, for the strip's rows with slots or all columns in their shortlists ----
+    if (tid < HT) {
+        rowcnt[tid] = slots; // (read by all threads below, before the tiles overwrite it)
+        best[tid] = KEY_MAX;
+        rinv[tid] = aexp != 0u ? __uint_as_float(0x7F000000u - aexp) : a.arinv[m0 + tid];
+    }
+    if (tid == 0) sh_pairs = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int rl = slot_row(i, r);
+            b1[i][r] = rowcnt[rl] ? band_end(rl) : -INFINITY;
+        }
+    __syncthreads();
+    if (tid < HT) crowded[tid] = slots != 0;
+    fetch_cols(t0);
+    copy_tile(t0);
+    if (!sweep(std::true_type{}, std::true_type{})) return;
+    __syncthreads();
+    if (sh_pairs > PAIR_CAP) return;
+    settle(sh_pairs);
+    __syncthreads();
+    if (slots && best[tid] != KEY_MAX) { // the nearest, at the distance the split's smallest key has
+        dst[0] = near | (uint32_t)best[tid];
+#pragma unroll
+        for (int s = 1; s < VLQ_NN_CANDS; ++s) dst[s] = KEY_MAX;
     }
 }
 
-int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *an, const float *ares,
-                        const float *bn, uint64_t *cand, int nsplit, float *band_dist, const float **bhdr, hipStream_t st)
+int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *X, const float *C,
+                        const float *an, const float *ares, const float *bn, uint64_t *cand, int nsplit, float *band_dist,
+                        const float **bhdr, hipStream_t st)
 {
     const HalfImage A(Aimg, M), B(Bimg, N);
     HalfArgs a = {};
@@ -407,6 +529,9 @@ int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D,
     a.bhdr = B.hdr;
     a.M = M;
     a.N = N;
+    a.X = X;
+    a.C = C;
+    a.vec = ((uintptr_t)C) % 16 == 0;
     a.an = an;
     a.ares = ares;
     a.bn = bn;
@@ -423,8 +548,9 @@ int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D,
     *band_dist = a.band_dist;
     *bhdr = B.hdr;
     if (M <= 0 || N <= 0) return 0;
-    // the ring of tiles (the tail of the kernel takes HT * (8 + 8 * VLQ_NN_CANDS) bytes of it) and the rows' scales
-    const size_t bytes = (size_t)2 * (D / 16) * HPAGE * 16 + HT * 4;
+    // the ring of tiles (the tail of the kernel takes HT * (8 + 8 * VLQ_NN_CANDS) bytes of it), the rows' scales, and
+    // the nearest columns and the pairs of the second sweep: 73.5 KB at most, so that two workgroups share the LDS
+    const size_t bytes = (size_t)2 * (D / 16) * HPAGE * 16 + HT * (4 + 8) + PAIR_CAP * 4;
     const dim3 grid((unsigned)((M + HT - 1) / HT), (unsigned)nsplit);
     auto go = [&](auto kern) -> int {
         if (bytes > 49152) { // (48 KB of dynamic LDS need no asking)

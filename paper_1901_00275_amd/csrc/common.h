@@ -83,6 +83,30 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// ||x - row||^2 by each group of 16 lanes (l16 = lane % 16): four components per lane and step, then
+// the adder's lane-crossing sum.  Every exact evaluation of a centroid distance goes through
+// it, so that coinciding centroids get bit-identical values and ties fall to the smaller index.
+__device__ __forceinline__ float sqdist16(const float *x, const float *__restrict__ row, int D, int l16, bool vec)
+{
+    float acc = 0.f;
+    if (vec) {
+        for (int d = l16 * 4; d < D; d += 64) {
+            const f32x4 cv = *(const f32x4 *)(row + d);
+            const float t0 = x[d] - cv.x, t1 = x[d + 1] - cv.y, t2 = x[d + 2] - cv.z, t3 = x[d + 3] - cv.w;
+            acc = fmaf(t0, t0, acc);
+            acc = fmaf(t1, t1, acc);
+            acc = fmaf(t2, t2, acc);
+            acc = fmaf(t3, t3, acc);
+        }
+    } else {
+        for (int d = l16; d < D; d += 16) {
+            const float t = x[d] - row[d];
+            acc = fmaf(t, t, acc);
+        }
+    }
+    return row16_sum(acc);
+}
+
 // ||x - c||^2 by one wave: x in LDS (or any memory), c a global row.  Lanes
 // stride over the dimensions, partial sums are combined by a butterfly, so the
 // result is the same in all lanes and independent of the launch shape.
@@ -209,8 +233,10 @@ void launch_coarse_gemm_nn(const float *A, int M, const float *B, int N, int D, 
 size_t half_image_bytes(int64_t rows, int D);
 void launch_half_image(const float *X, int64_t rows, int D, const float *mu, void *img, bool header, float *norm2,
                        float *resid, hipStream_t st);
-int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *an, const float *ares,
-                        const float *bn, uint64_t *cand, int nsplit, float *band_dist, const float **bhdr, hipStream_t st);
+// X [M x D], C [N x D] are the rows and columns themselves, for the exact distances of crowded rows.
+int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *X, const float *C,
+                        const float *an, const float *ares, const float *bn, uint64_t *cand, int nsplit, float *band_dist,
+                        const float **bhdr, hipStream_t st);
 // Width of the band around the smallest distance dmin of a row a, xn = ||a||^2, res = ||a - a'||, for columns with
 // ||b - b'|| <= max(rho ||b||, big).  One value ||b||^2 - 2 <a', b'> is off by at most
 //   2 (res ||b|| + ||a'|| max(rho ||b||, big))      rounding to fp16 (Cauchy-Schwarz), ||a'|| <= 1.002 ||a||

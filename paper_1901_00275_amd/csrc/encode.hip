@@ -5,30 +5,6 @@
 #define ENC_NT 256
 #define ENC_PB_MAX 32
 
-// ||x - row||^2 by each group of 16 lanes (l16 = lane % 16): four components per lane and step, then
-// the adder's lane-crossing sum.  Every exact evaluation of a centroid distance in this file goes
-// through it, so that coinciding centroids get bit-identical values and ties fall to the smaller index.
-__device__ __forceinline__ float sqdist16(const float *x, const float *__restrict__ row, int D, int l16, bool vec)
-{
-    float acc = 0.f;
-    if (vec) {
-        for (int d = l16 * 4; d < D; d += 64) {
-            const f32x4 cv = *(const f32x4 *)(row + d);
-            const float t0 = x[d] - cv.x, t1 = x[d + 1] - cv.y, t2 = x[d + 2] - cv.z, t3 = x[d + 3] - cv.w;
-            acc = fmaf(t0, t0, acc);
-            acc = fmaf(t1, t1, acc);
-            acc = fmaf(t2, t2, acc);
-            acc = fmaf(t3, t3, acc);
-        }
-    } else {
-        for (int d = l16; d < D; d += 16) {
-            const float t = x[d] - row[d];
-            acc = fmaf(t, t, acc);
-        }
-    }
-    return row16_sum(acc);
-}
-
 // Nearest row of C [k x D] to x by direct sums of squared differences, smallest (distance, index),
 // over a set of `count` columns given by col_of(c), c = 0 .. count - 1 (columns >= k are skipped):
 // 16 lanes per row, four rows per pass.  Serves the rows whose shortlist came back incomplete.

@@ -103,3 +103,44 @@ def test_small_rows_beside_ordinary_ones_cost_nothing():
     ordinary = time_assign(X, C)
     X[::2] *= 1e-8
     assert time_assign(X, C) < 2 * ordinary
+
+
+@pytest.mark.parametrize("nt,D,k,group,spread", [
+    (1000, 128, 5000, 16, 0.04), (300, 96, 20_000, 64, 0.03), (129, 32, 3000, 250, 0.01), (70_000, 64, 2048, 40, 0.02), (3, 128, 9000, 3000, 0.001)])
+def test_crowded_groups_of_centroids(nt, D, k, group, spread):
+    """Tight groups of centroids (more of them inside the band than a shortlist holds), some coinciding, and vectors that
+    are not numbers among the others."""
+    rng = np.random.default_rng(k)
+    C = np.repeat(rng.normal(size=(k // group + 1, D)), group, 0)[:k] + spread * rng.normal(size=(k, D))
+    C[k // 2:k // 2 + 9] = C[7]
+    X = C[rng.integers(0, k, nt)] + rng.normal(scale=0.3, size=(nt, D))
+    X[nt // 3] = C[k // 2] + 1e-3
+    X, C = X.astype(np.float32), C.astype(np.float32)
+    bad = np.arange(1, nt, 97)
+    X[bad, 3] = np.nan
+    cell = assign(X, C)
+    assert ((cell >= 0) & (cell < k)).all()
+    Xd, Cd = torch.as_tensor(X).to(DEV).double(), torch.as_tensor(C).to(DEV).double()
+    for s in range(0, nt, 64):
+        d = ((Xd[s:s + 64, None] - Cd[None]) ** 2).sum(2).cpu().numpy()
+        got = d[np.arange(len(d)), cell[s:s + 64]]
+        fine = ~np.isnan(d[:, 0])
+        assert (got[fine] <= d[fine].min(1) * (1 + 2 * (D + 1) * 2.0 ** -24)).all()
+        first = fine & (got == d.min(1))
+        assert np.array_equal(cell[s:s + 64][first], d.argmin(1)[first])
+
+
+def test_crowded_codebooks_and_far_rows_take_no_more_than_a_second_product():
+    """One wave read all centroids for every such vector: 28 times as long with groups of 16, 11 times with far rows."""
+    rng = np.random.default_rng(3)
+    nt, D, k = 131_072, 128, 16_384
+    t = {}
+    for spread in (0.3, 0.04, 0.001):
+        C = np.repeat(rng.normal(size=(k // 16, D)), 16, 0) + spread * rng.normal(size=(k, D))
+        X = C[rng.integers(0, k, nt)] + rng.normal(scale=0.3, size=(nt, D))
+        t[spread] = time_assign(X.astype(np.float32), C.astype(np.float32))
+    assert t[0.04] < 5 * t[0.3] and t[0.001] < 5 * t[0.3], t
+    X, C, far = rows_apart(nt, D, k)
+    with_far = time_assign(X, C)
+    X[far] *= 1e-7
+    assert with_far < 5 * time_assign(X, C)
