@@ -15,9 +15,9 @@ __device__ __forceinline__ uint64_t exact_nearest_of(const float *x, const float
     const int sub = lane >> 4, l16 = lane & 15;
     const bool vec = (D % 4 == 0) && (((uintptr_t)C) % 16 == 0);
     uint64_t best = KEY_MAX;
-    for (int c0 = 0; c0 < count; c0 += 16) { // (four passes at a time: their loads are under way together)
+    for (int c0 = 0; c0 < count; c0 += 8) { // (two passes at a time: their loads are under way together)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 2; ++u) {
             const int c = c0 + 4 * u + sub;
             const int i = c < count ? col_of(c) : k;
             const float acc = sqdist16(x, C + (int64_t)min(i, k - 1) * D, D, l16, vec);
@@ -116,10 +116,13 @@ __device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gi
                     const int split = (c0 + src) / VLQ_NN_CANDS;
                     const int t0 = split * per, t1 = min(ntiles, t0 + per);
                     const int base = (int)((idx >> 5) & 1) * 64 + (int)(idx & 31);
-                    const bool all = idx == VLQ_NN_ALL;
-                    got = exact_nearest_of(x, a.C, a.k, a.D, lane, (t1 - t0) * (all ? VLQ_NN_TILE : 2), [=](int c) {
-                        return all ? t0 * VLQ_NN_TILE + c : (t0 + (c >> 1)) * VLQ_NN_TILE + base + 32 * (c & 1);
-                    });
+                    if (idx == VLQ_NN_ALL)
+                        got = exact_nearest_of(x, a.C, a.k, a.D, lane, (t1 - t0) * VLQ_NN_TILE,
+                                               [=](int c) { return t0 * VLQ_NN_TILE + c; });
+                    else
+                        got = exact_nearest_of(x, a.C, a.k, a.D, lane, 2 * (t1 - t0), [=](int c) {
+                            return (t0 + (c >> 1)) * VLQ_NN_TILE + base + 32 * (c & 1);
+                        });
                 }
                 bk = got < bk ? got : bk;
             }

@@ -144,3 +144,25 @@ def test_crowded_codebooks_and_far_rows_take_no_more_than_a_second_product():
     with_far = time_assign(X, C)
     X[far] *= 1e-7
     assert with_far < 5 * time_assign(X, C)
+
+
+@pytest.mark.parametrize("nt,k", [(130, 1), (130, 5), (300, 127), (130, 1300)])
+def test_all_columns_read_exactly(nt, k):
+    """Nothing separates the columns in fp16 (every row is compared with all of them): the smallest exact distance, the
+    smaller index of a tie."""
+    D = 64
+    rng = np.random.default_rng(k)
+    C = (1.0 + 1e-6 * rng.integers(-8, 9, (k, D))).astype(np.float32)
+    C[k // 2:] = C[:k - k // 2]  # each twice
+    X = (1000.0 + rng.integers(0, 3, (nt, D))).astype(np.float32)
+    X[:, 0] += np.arange(nt)
+    cell = assign(X, C)
+    # the direct sum in the order of the kernel: four components per lane, then pairs of lanes
+    t = X[:, None] - C[None]
+    acc = np.zeros((nt, k, 16))
+    for d in range(4):  # (fused: each step is rounded once, from a product that fp64 holds exactly)
+        acc = (t[:, :, d::4].astype(np.float64) ** 2 + acc).astype(np.float32)
+    for _ in range(4):
+        acc = acc[..., 0::2] + acc[..., 1::2]
+    assert acc.dtype == np.float32
+    assert np.array_equal(cell, acc[..., 0].argmin(1))
