@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from test_gpu_parity import DEV, dev, gpu_search, make_index, vlq  # noqa: F401  (vlq: fixture)
-from util import problem
+from util import Problem, problem
 
 pytestmark = pytest.mark.gpu
 
@@ -64,5 +64,59 @@ def test_coinciding_points(vlq, K, same_ids):  # noqa: F811
         d, i = d.cpu().numpy(), i.cpu().numpy()
         assert (d == d[:, :1]).all() and np.isfinite(d).all()
         assert (i == (5 if same_ids else np.arange(K))).all()
+    finally:
+        vlq.vlq_index_free(idx)
+
+
+def clusters(k, n, m, D, spread, nq, seed=0):
+    """Tight clusters far from the centroids' mean: distances are small against what the scan's table is made of."""
+    rng = np.random.default_rng(seed)
+    C = np.repeat(rng.normal(size=((k + 31) // 32, D)), 32, 0)[:k] + spread * rng.normal(size=(k, D))
+    P = spread * rng.normal(size=(m, 256, D // m))
+    Y = C[rng.integers(0, k, nq)] + spread * rng.normal(size=(nq, D))
+    return Problem("other", None, *(v.astype(np.float32) for v in (Y, C, P)), n)
+
+
+# (64, 1 024, 2 048 lists and a workgroup per query: the largest LDS image of the kernel)
+@pytest.mark.parametrize("m,D,k,n,K,N,nq,w1,w2", [
+    (64, 1024, 64, 32, 1024, 150_000, 1024, 64, 2048), (64, 1024, 64, 32, 1024, 150_000, 2, 64, 2048), (8, 128, 64, 8, 1000, 400_000, 300, 16, 100)])
+@pytest.mark.parametrize("spread", [1.0, 0.02, 1e-3])
+def test_clusters(vlq, m, D, k, n, K, N, nq, w1, w2, spread):  # noqa: F811
+    pr = clusters(k, n, m, D, spread, nq)
+    idx = make_index(vlq, pr)
+    try:
+        add(vlq, idx, pr, N, k)
+        (dg, ig), (dw, iw) = both_scans(vlq, idx, pr.Y, w1, w2, K)
+        assert np.array_equal(dg, dw) and np.array_equal(ig, iw)
+    finally:
+        vlq.vlq_index_free(idx)
+
+
+def scan_times(vlq, idx, Y, w1, w2, K):  # noqa: F811
+    """milliseconds of the 2m-lookup scan and of this one"""
+    Yd, out = dev(Y), []
+    d, i = torch.empty(len(Y), K, device=DEV), torch.empty(len(Y), K, dtype=torch.int32, device=DEV)
+    for generic in (1, 0):
+        vlq.vlq_index_set_option(idx, vlq.VLQ_OPT_SCAN_GENERIC, generic)
+        best = float("inf")
+        for _ in range(4):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            vlq.vlq_search(idx, Yd, len(Y), w1, w2, K, d, i)
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1))
+        out.append(best)
+    return out
+
+
+def test_clusters_are_not_slower(vlq):  # noqa: F811
+    """Tight clusters in long lists: too wide a bound kept more points than the buffer holds, and the scan started over."""
+    pr = clusters(64, 8, 8, 128, 0.01, 256)
+    idx = make_index(vlq, pr)
+    try:
+        add(vlq, idx, pr, 4_000_000, 64)
+        generic, wide = scan_times(vlq, idx, pr.Y, 8, 16, 1000)
+        assert wide < generic
     finally:
         vlq.vlq_index_free(idx)
