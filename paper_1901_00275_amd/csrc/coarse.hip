@@ -709,8 +709,9 @@ __global__ __launch_bounds__(SEL2_NT) void k_select_cells_reg(const float *__res
     const float wide = vw * (1.f + 1e-5f) + bandn * (rq + sq * sq) * 1.5f;
 #pragma unroll
     for (int e = 0; e < VPT; ++e) {
-        if (!(selm >> e & 1) && v[e] <= wide) {
-            const int i = e * SEL2_NT + tid;
+        const int i = e * SEL2_NT + tid;
+        // (an overflowing query's band is infinite, as are the entries past the end of the row)
+        if (!(selm >> e & 1) && i < k && v[e] <= wide) {
             if (v[e] <= vw + bandn * (rq + cn[i])) {
                 const int pos = atomicAdd(&sh_cnt, 1);
                 if (pos < SEL_CAP) keys[pos] = ((uint64_t)__float_as_uint(v[e]) << 32) | (uint32_t)i;
