@@ -963,7 +963,9 @@ static int search_impl(vlq_index *idx, const float *d_q, int32_t nq, int32_t w1,
         a.force_generic = idx->opt[VLQ_OPT_SCAN_GENERIC] != 0;
         a.lam_step = idx->lam_step;
         a.lam_zero = idx->lam_zero;
+        a.mean_len = idx->ntotal / nl;
         a.scan_label = c.slab;
+        a.redo = scan_takes_labels(a) ? c.slab : nullptr; // (nsplit <= w2; the sorted labels are not needed then)
         a.scan_g = c.sg;
         a.partial = c.partial;
         a.out_dist = d_out_dist + (int64_t)c.q0 * K;

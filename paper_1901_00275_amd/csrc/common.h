@@ -340,6 +340,8 @@ struct ScanArgs {
     const uint4 *desc; // [nq x w2] {begin, length, a, b - a} per visited sub-region, or {label, 1, a, g}: scan_takes_labels
     int packed;        // streaming scan: short lists, several per chunk of lanes
     bool force_generic; // the 2m-lookup kernel whatever the shape
+    int64_t mean_len;   // stored points per list
+    int32_t *redo;      // [nq x nsplit] the workgroups of k_scan_wide that leave their lists to a second launch, or NULL
     const int32_t *scan_label;
     const float *scan_g;
     uint64_t *partial; // [nq x nsplit x K] when nsplit > 1
@@ -352,7 +354,7 @@ bool scan_will_stream(const ScanArgs &a); // launch_scan is going to take the li
 void launch_scan_stream(const ScanArgs &a, hipStream_t st);
 bool scan_wide_supported(const ScanArgs &a);
 bool scan_takes_labels(const ScanArgs &a); // ... in their {label, 1, a, g} form
-void launch_scan_wide(const ScanArgs &a, hipStream_t st);
+void launch_scan_wide(const ScanArgs &a, bool exact, hipStream_t st);
 void launch_merge(const uint64_t *partial, int nq, int nsplit, int K, float *out_dist, int32_t *out_ids,
                   hipStream_t st);
 #define SCAN_MAX_SPLIT 16 // workgroups per query

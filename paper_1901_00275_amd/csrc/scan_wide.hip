@@ -14,15 +14,18 @@
 //    2m-lookup scan (search.hip, k_scan) in the same operations and order, read from the centroids and
 //    codewords themselves, and the K smallest (distance, id) of these are the result: the same bits as that
 //    scan's.  If more points lie within the bound than the buffer holds (masses of coinciding points), or the
-//    bound is not finite, the workgroup starts over and takes that distance for every candidate at once.
+//    bound is not finite, the workgroup leaves its lists to a second launch, which takes that distance for every
+//    candidate (a workgroup with nothing to do ends at once): point by point (EXACT) or, where lists are long, with
+//    the tables of k_scan (scan_redo_by_list).
 //    (The bound goes summand by summand: with (D + m) 2 Z^2, Z the sum of all sizes, clusters of 2 % of the distance of
 //    their centre from the mean were already taken for coinciding: 256 queries x 16 lists of 8 000 points, K = 1 000,
 //    2.6 ms, and 0.53 so; 1 024 x 2 048 lists of 125 points, m = 64, D = 1 024, K = 1 024: 105 and 35 ms.)
 //
-// Measured, 1 501 queries x 512 lists of 19 points (14.7M points), m = 8, K = 1 000: 0.387 ms against 66.7 ms of the
-// 2m-lookup scan, which builds m * 256 table entries per 19-point list and sorts its whole buffer of keys at every
-// cut.  With the K fast distances as results it would be 0.163 ms: the rest is the 1.5M points taken again, 1.5 KB
-// of centroid and codeword rows each.
+// Measured, 1 501 queries x 512 lists of 19 points (14.7M points), m = 8, K = 1 000: 0.314 ms, and 4 us for a
+// second launch that finds nothing to do, against 66.7 ms of the 2m-lookup scan, which builds m * 256 table entries per
+// 19-point list and sorts its whole buffer of keys at every cut.  Half of it are the 1.5M points taken again, 1.5 KB of centroid and codeword rows each.  (With the exact pass in
+// the same kernel 22 to 99 registers were spilled, whatever the code length: 0.387 ms; 1 024 queries x 2 048 lists, m = 64,
+// D = 1 024, K = 1 024: the call took 35 ms, 9.1 ms so.)
 #include "bounds.h"
 #include "common.h"
 
@@ -64,9 +67,12 @@ __device__ __forceinline__ void sw_subspace(const float *__restrict__ y, const f
     *B = sb;
 }
 
-template <int M> // bytes of a code (0: run-time length)
+// M: bytes of a code (0: run-time length).  EXACT: the pass over what the fast one has left, by the 2m-lookup distance
+// of every candidate; the fast distance, with its bound, only spares those that are beyond the threshold.
+template <int M, bool EXACT>
 __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_max)
 {
+    if (EXACT && !a.redo[blockIdx.x]) return;
     extern __shared__ __align__(16) unsigned char smem[];
     uint64_t *keys = (uint64_t *)smem;              // [SW_CAP] (distance, place in the concatenation), or (distance, id)
     float *T = (float *)(keys + SW_CAP);            // [m * 256]
@@ -344,9 +350,9 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
     const int room = K + (K >> 2) + 64; // how far below the buffer's size a cut of fast distances is taken
 
     constexpr int CW = M > 0 ? (M + 3) / 4 : 1;
-    int cnt = 0;
-    for (bool exact = !(slack < INFINITY);; exact = true) {
-        bool redo = false; // uniform over the workgroup
+    constexpr bool exact = EXACT;
+    bool redo = !EXACT && !(slack < INFINITY); // uniform over the workgroup
+    if (!redo) {
         if (tid == 0) {
             sh_cnt = 0;
             sh_thr = KEY_MAX;
@@ -433,65 +439,66 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
             }
         }
         __syncthreads();
-        cnt = sh_cnt;
+    }
+    if (!EXACT && !redo && sh_cnt > K) {
+        const int n = sh_cnt;
         __syncthreads();
-        if (!redo && !exact && cnt > K) {
-            redo = !select(cnt, K, false);
-            cnt = sh_cnt;
-        }
-        if (redo) continue; // (all threads are past their last use of the buffer: the barriers in select)
-        if (!exact) {
-            // the 2m-lookup distance of what is left, a group of lanes per point: lane s of it takes sub-space s
-            int L = 1;
-            while (L < m) L <<= 1; // m <= 64
-            const int per = SW_NT / L, sub = tid & (L - 1);
-            for (int d = tid; d < D; d += SW_NT) yv[d] = yq[d]; // (the tables are done with: the query itself from here on)
-            __syncthreads();
-            // first where everything lies, a thread per point (the round trips of one point follow one another, those
-            // of different points overlap); the upper half of the buffer is free
-            static_assert(SW_CAP - SW_TURN <= SW_CAP / 2, "what a cut leaves fits half the buffer");
-            for (int at = tid; at < cnt; at += SW_NT) {
-                const sw_place_t p = (sw_place_t)keys[at];
-                int lo = 0, hi = nl - 1; // first list that ends behind p
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (lend[mid] <= p)
-                        lo = mid + 1;
-                    else
-                        hi = mid;
-                }
-                const int label = (int)dq[lat[lo]].x;
-                keys[at] = ((uint64_t)(uint32_t)lat[lo] << 32) | (p + lsh[lo]);
-                keys[SW_CAP / 2 + at] = ((uint64_t)(uint32_t)a.S[label] << 32) | (uint32_t)(label / a.n);
+        redo = !select(n, K, false);
+    }
+    if (!EXACT && tid == 0) a.redo[blockIdx.x] = redo;
+    if (redo) return;
+    int cnt = sh_cnt;
+    __syncthreads();
+    if (!EXACT) {
+        // the 2m-lookup distance of what is left, a group of lanes per point: lane s of it takes sub-space s
+        int L = 1;
+        while (L < m) L <<= 1; // m <= 64
+        const int per = SW_NT / L, sub = tid & (L - 1);
+        for (int d = tid; d < D; d += SW_NT) yv[d] = yq[d]; // (the tables are done with: the query itself from here on)
+        __syncthreads();
+        // first where everything lies, a thread per point (the round trips of one point follow one another, those
+        // of different points overlap); the upper half of the buffer is free
+        static_assert(SW_CAP - SW_TURN <= SW_CAP / 2, "what a cut leaves fits half the buffer");
+        for (int at = tid; at < cnt; at += SW_NT) {
+            const sw_place_t p = (sw_place_t)keys[at];
+            int lo = 0, hi = nl - 1; // first list that ends behind p
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (lend[mid] <= p)
+                    lo = mid + 1;
+                else
+                    hi = mid;
             }
-            __syncthreads();
-            for (int c0 = 0; c0 < cnt; c0 += per) {
-                const int at = c0 + tid / L;
-                const bool live = at < cnt;
-                // (idle groups work on point 0 of the index)
-                const uint64_t where = live ? keys[at] : 0, rows = live ? keys[SW_CAP / 2 + at] : 0;
-                const uint32_t g = (uint32_t)where;
-                const uint4 d = dq[where >> 32];
-                float A = 0.f, B = 0.f;
-                if (sub < m) {
-                    const int t = a.codes[(size_t)g * m + sub];
-                    sw_subspace(yv + sub * ds, a.C + (int64_t)(uint32_t)rows * D + sub * ds,
-                                a.C + (int64_t)(uint32_t)(rows >> 32) * D + sub * ds,
-                                a.P + ((int64_t)sub * 256 + t) * ds, ds, &A, &B);
-                }
-                const float l = ((float)a.lam[g] - a.lam_zero) * a.lam_step, c = a.E[d.x];
-                const uint32_t id = (uint32_t)a.ids[g];
-                float sa = 0.f, sb = 0.f;
-                for (int s = 0; s < m; ++s) {
-                    sa += __shfl(A, s, L);
-                    sb += __shfl(B, s, L);
-                }
-                const float dist = fmaf(l, fmaf(l, c, 2.f * (sb - __uint_as_float(d.w))), sa);
-                if (live && sub == 0) keys[at] = make_key(dist, id);
-            }
-            __syncthreads();
+            const int label = (int)dq[lat[lo]].x;
+            keys[at] = ((uint64_t)(uint32_t)lat[lo] << 32) | (p + lsh[lo]);
+            keys[SW_CAP / 2 + at] = ((uint64_t)(uint32_t)a.S[label] << 32) | (uint32_t)(label / a.n);
         }
-        break;
+        __syncthreads();
+        for (int c0 = 0; c0 < cnt; c0 += per) {
+            const int at = c0 + tid / L;
+            const bool live = at < cnt;
+            // (idle groups work on point 0 of the index)
+            const uint64_t where = live ? keys[at] : 0, rows = live ? keys[SW_CAP / 2 + at] : 0;
+            const uint32_t g = (uint32_t)where;
+            const uint4 d = dq[where >> 32];
+            float A = 0.f, B = 0.f;
+            if (sub < m) {
+                const int t = a.codes[(size_t)g * m + sub];
+                sw_subspace(yv + sub * ds, a.C + (int64_t)(uint32_t)rows * D + sub * ds,
+                            a.C + (int64_t)(uint32_t)(rows >> 32) * D + sub * ds,
+                            a.P + ((int64_t)sub * 256 + t) * ds, ds, &A, &B);
+            }
+            const float l = ((float)a.lam[g] - a.lam_zero) * a.lam_step, c = a.E[d.x];
+            const uint32_t id = (uint32_t)a.ids[g];
+            float sa = 0.f, sb = 0.f;
+            for (int s = 0; s < m; ++s) {
+                sa += __shfl(A, s, L);
+                sb += __shfl(B, s, L);
+            }
+            const float dist = fmaf(l, fmaf(l, c, 2.f * (sb - __uint_as_float(d.w))), sa);
+            if (live && sub == 0) keys[at] = make_key(dist, id);
+        }
+        __syncthreads();
     }
     if (cnt > K) {
         select(cnt, next_pow2_dev(K), true);
@@ -519,24 +526,29 @@ bool scan_wide_supported(const ScanArgs &a)
     return a.sx != nullptr && a.mu != nullptr && a.desc != nullptr;
 }
 
-void launch_scan_wide(const ScanArgs &a, hipStream_t st)
+void launch_scan_wide(const ScanArgs &a, bool exact, hipStream_t st)
 {
     if (a.nq <= 0) return;
     const int lists = (a.w2 + a.nsplit - 1) / a.nsplit;
     const size_t lds = scan_wide_lds(a.m, a.D, lists); // at most 136 KB (m = 64, D = 1 024, 2 048 lists)
     auto go = [&](auto kern) {
-        if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        if (lds > 49152 && // (48 KB of dynamic LDS beside the static part need no asking)
+            hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return; // (the caller asks for the error)
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.nq * a.nsplit)), dim3(SW_NT), lds, st, a, lists);
     };
+    if (exact) { // (rare: one instance for all code lengths)
+        go(k_scan_wide<0, true>);
+        return;
+    }
     switch (a.m) {
-    case 4: go(k_scan_wide<4>); break;
-    case 8: go(k_scan_wide<8>); break;
-    case 10: go(k_scan_wide<10>); break;
-    case 12: go(k_scan_wide<12>); break;
-    case 16: go(k_scan_wide<16>); break;
-    case 20: go(k_scan_wide<20>); break;
-    case 32: go(k_scan_wide<32>); break;
-    default: go(k_scan_wide<0>); break;
+    case 4: go(k_scan_wide<4, false>); break;
+    case 8: go(k_scan_wide<8, false>); break;
+    case 10: go(k_scan_wide<10, false>); break;
+    case 12: go(k_scan_wide<12, false>); break;
+    case 16: go(k_scan_wide<16, false>); break;
+    case 20: go(k_scan_wide<20, false>); break;
+    case 32: go(k_scan_wide<32, false>); break;
+    default: go(k_scan_wide<0, false>); break;
     }
 }

@@ -993,6 +993,7 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan(ScanArgs a, int KP, int SZ)
 
     const int tid = threadIdx.x;
     const int q = blockIdx.x / a.nsplit, split = blockIdx.x - q * a.nsplit;
+    if (a.redo && !a.redo[blockIdx.x]) return;
     const int CB = SZ - KP;
     const int r0 = (int)((int64_t)a.w2 * split / a.nsplit), r1 = (int)((int64_t)a.w2 * (split + 1) / a.nsplit);
 
@@ -1006,7 +1007,8 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan(ScanArgs a, int KP, int SZ)
 
     int cur_cell = -1;
     for (int r = r0; r < r1; ++r) {
-        const int label = a.scan_label[(int64_t)q * a.w2 + r];
+        const uint4 dsc = a.redo ? a.desc[(int64_t)q * a.w2 + r] : make_uint4(0u, 0u, 0u, 0u);
+        const int label = a.redo ? (dsc.y ? (int)dsc.x : -1) : a.scan_label[(int64_t)q * a.w2 + r];
         if (label < 0) continue; // uniform over the workgroup
         const int64_t beg = a.off[label], end = a.off[label + 1];
         if (beg == end) continue;
@@ -1041,7 +1043,7 @@ __global__ __launch_bounds__(SCAN_NT) void k_scan(ScanArgs a, int KP, int SZ)
             }
         }
         const float cc = a.E[label];
-        const float g = a.scan_g[(int64_t)q * a.w2 + r];
+        const float g = a.redo ? __uint_as_float(dsc.w) : a.scan_g[(int64_t)q * a.w2 + r];
         __syncthreads();
 
         // scan the list
@@ -1127,22 +1129,31 @@ int scan_pick_nsplit(int nq, int w2, int K)
 }
 
 // Which scan: up to 128 results of 8- or 16-byte codes by k_scan_stream, every other shape by k_scan_wide; the
-// 2m-lookup scan below is for VLQ_OPT_SCAN_GENERIC and for indexes without points.
+// 2m-lookup scan above is for VLQ_OPT_SCAN_GENERIC, for indexes without points and for what k_scan_wide hands over.
 bool scan_will_stream(const ScanArgs &a)
 {
     return !a.force_generic && (scan_stream_supported(a) || scan_wide_supported(a));
 }
 bool scan_takes_labels(const ScanArgs &a) { return scan_will_stream(a) && !scan_stream_supported(a); }
+// What a workgroup of k_scan_wide leaves is taken point by point or with tables per list.  Where lists are long the
+// tables pay (256 queries x 16 lists of coinciding points, D = 128, m = 8: 0.75 ms point by point and 0.70 with tables at
+// 2 000 points a list, 3.6 and 1.1 at 16 000; m = 20: 0.77 and 0.96 at 500, 1.2 and 0.7 at 2 000; m = 64, D = 1 024: 4.8
+// and 3.9 at 500).
+static bool scan_redo_by_list(const ScanArgs &a) { return a.mean_len >= (a.m > 16 ? 256 : 1536); }
 
 void launch_scan(const ScanArgs &a, hipStream_t st)
 {
     if (a.nq <= 0) return;
     if (scan_will_stream(a)) {
-        if (scan_stream_supported(a))
+        if (scan_stream_supported(a)) {
             launch_scan_stream(a, st);
-        else
-            launch_scan_wide(a, st);
-        return;
+            return;
+        }
+        launch_scan_wide(a, false, st);
+        if (!scan_redo_by_list(a)) {
+            launch_scan_wide(a, true, st);
+            return;
+        }
     }
     int KP, SZ;
     scan_sizes(a.K, &KP, &SZ);

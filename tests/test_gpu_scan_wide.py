@@ -120,3 +120,49 @@ def test_clusters_are_not_slower(vlq):  # noqa: F811
         assert wide < generic
     finally:
         vlq.vlq_index_free(idx)
+
+
+def coinciding(vlq, pr, N, seed=0):  # noqa: F811
+    """An index whose lists hold one point many times over, under ids in any order."""
+    idx = make_index(vlq, pr)
+    at = np.arange(N)
+    vlq.vlq_index_add_encoded(idx, dev((at // pr.n % pr.k).astype(np.int32)), dev((at % pr.n).astype(np.int32)),
+                              dev(np.full(N, 100, np.uint8)), dev(np.full((N, pr.m), 7, np.uint8)),
+                              dev(np.random.default_rng(seed).permutation(N).astype(np.int32)), N)
+    vlq.vlq_index_finalize(idx)
+    return idx
+
+
+# lists around the length from which workgroups hand over to the 2m-lookup scan (1 536 points, 256 for codes of more
+# than 16 bytes), queries whose bound is not finite, split and unsplit
+@pytest.mark.parametrize("m,D,length,nq", [(8, 64, 1535, 3), (8, 64, 1537, 3), (8, 64, 2500, 1100), (20, 60, 255, 20), (20, 60, 300, 20), (5, 35, 3000, 20)])
+@pytest.mark.parametrize("nan_codeword", [False, True])
+def test_long_lists_of_coinciding_points(vlq, m, D, length, nq, nan_codeword):  # noqa: F811
+    pr = clusters(16, 4, m, D, 0.3, nq)
+    pr.Y[nq // 2, 1] = np.inf
+    pr.Y[nq // 3, 0] = np.nan
+    if nan_codeword:
+        pr.P[0, 7, 0] = np.nan
+    idx = coinciding(vlq, pr, length * 64)
+    try:
+        out = []
+        for generic in (1, 0):
+            vlq.vlq_index_set_option(idx, vlq.VLQ_OPT_SCAN_GENERIC, generic)
+            d, i = torch.empty(nq, 1000, device=DEV), torch.empty(nq, 1000, dtype=torch.int32, device=DEV)
+            vlq.vlq_search(idx, dev(pr.Y), nq, 8, 20, 1000, d, i)
+            out.append((d.cpu().numpy(), i.cpu().numpy()))
+        (dg, ig), (dw, iw) = out
+        assert np.array_equal(dg, dw, equal_nan=True) and np.array_equal(ig, iw)
+    finally:
+        vlq.vlq_index_free(idx)
+
+
+def test_coinciding_points_in_long_lists_are_not_slower(vlq):  # noqa: F811
+    """More points within the bound than the buffer holds: taken one by one they took 3.5 times the 2m-lookup scan."""
+    pr = clusters(64, 8, 8, 128, 0.3, 256)
+    idx = coinciding(vlq, pr, 64 * 8 * 16_000)
+    try:
+        generic, wide = scan_times(vlq, idx, pr.Y, 8, 16, 1000)
+        assert wide < 1.4 * generic
+    finally:
+        vlq.vlq_index_free(idx)
