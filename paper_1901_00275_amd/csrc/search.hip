@@ -1128,11 +1128,28 @@ int scan_pick_nsplit(int nq, int w2, int K)
     return ns;
 }
 
+// Many results from few lists: k_scan_wide scores all K of a workgroup a second time, each in a part of the time that
+// k_scan takes for a list's tables (1 / 170 where the rows of a sub-space are not multiples of 16 bytes, 1 / 300 for codes of
+// more than 32 bytes, else 1 / 450), and k_scan takes that time again for 300 D/m points (at most 4 800).  128 - 300
+// queries, K = 1 000, one list a workgroup, ms of k_scan_wide and k_scan: m = 20, D = 120, 1 000 points 0.63 and 0.32, 4 000:
+// 0.70 and 0.57, 16 000: 0.89 and 1.55; four lists of 1 000: 0.68 and 0.80; m = 64, D = 1 024, 1 000 points 1.68 and 0.89; two
+// lists of 4 000: 3.3 and 3.7; m = 32, D = 128, 1 000 points 0.73 and 0.53, 4 000: 0.80 and 1.12; m = 4, D = 1 024, 1 000
+// points 1.01 and 0.81, two lists: 1.72 and 2.56.  8- and 16-byte codes: k_scan_wide throughout (0.28 and 0.32, 0.44 and 1.02).
+static bool scan_few_lists(const ScanArgs &a)
+{
+    if (a.m == 8 || a.m == 16) return false;
+    const int ds = a.D / a.m, lists = (a.w2 + a.nsplit - 1) / a.nsplit;
+    const int64_t points = lists * a.mean_len, again = points < a.K ? points : a.K;
+    const int64_t per = 300 * (ds < 16 ? ds : 16); // points that cost what a list's tables cost
+    return (lists * per + points) * (ds % 4 ? 170 : a.m > 32 ? 300 : 450) < again * per;
+}
+
 // Which scan: up to 128 results of 8- or 16-byte codes by k_scan_stream, every other shape by k_scan_wide; the
-// 2m-lookup scan above is for VLQ_OPT_SCAN_GENERIC, for indexes without points and for what k_scan_wide hands over.
+// 2m-lookup scan above is for VLQ_OPT_SCAN_GENERIC, for indexes without points, for few lists and for what k_scan_wide
+// hands over.
 bool scan_will_stream(const ScanArgs &a)
 {
-    return !a.force_generic && (scan_stream_supported(a) || scan_wide_supported(a));
+    return !a.force_generic && (scan_stream_supported(a) || (scan_wide_supported(a) && !scan_few_lists(a)));
 }
 bool scan_takes_labels(const ScanArgs &a) { return scan_will_stream(a) && !scan_stream_supported(a); }
 // What a workgroup of k_scan_wide leaves is taken point by point or with tables per list.  Where lists are long the

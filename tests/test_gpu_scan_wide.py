@@ -166,3 +166,22 @@ def test_coinciding_points_in_long_lists_are_not_slower(vlq):  # noqa: F811
         assert wide < 1.4 * generic
     finally:
         vlq.vlq_index_free(idx)
+
+
+# around the lines of the choice: one list a workgroup and several, few and many points in it, rows of a sub-space on 16
+# bytes and not
+@pytest.mark.parametrize("m,D,length,w2,K", [
+    (20, 120, 190, 4, 1000), (20, 120, 1000, 4, 1000), (20, 120, 16_000, 4, 1000), (20, 120, 1000, 16, 1000), (20, 120, 1000, 4, 10),
+    (64, 256, 1000, 4, 1000), (32, 128, 1000, 4, 1000), (32, 128, 4000, 4, 1000), (5, 35, 1000, 4, 500), (8, 128, 1000, 4, 1000)])
+def test_many_results_from_few_lists(vlq, m, D, length, w2, K):  # noqa: F811
+    """The second scoring of all K outweighs a list's tables: twice the time of the 2m-lookup scan, which it was."""
+    pr = clusters(16, 4, m, D, 0.3, 256)
+    idx = make_index(vlq, pr)
+    try:
+        add(vlq, idx, pr, length * 64, 16)
+        (dg, ig), (dw, iw) = both_scans(vlq, idx, pr.Y, 4, w2, K)
+        assert np.array_equal(dg, dw) and np.array_equal(ig, iw)
+        generic, chosen = scan_times(vlq, idx, pr.Y, 4, w2, K)
+        assert chosen < 1.25 * generic
+    finally:
+        vlq.vlq_index_free(idx)
