@@ -485,7 +485,7 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
     int shift = 62;
     while (shift > 0 && ((int64_t)1 << (62 - shift)) < nt) --shift;
 
-    if (lloyd_lanes_supported(D, k)) { // small codebooks of few dimensions: both halves in one pass
+    if (lloyd_lanes_supported(nt, D, k)) { // small codebooks of few dimensions: both halves in one pass
         DevBuf small;
         uint64_t *part;
         uint32_t *amax;

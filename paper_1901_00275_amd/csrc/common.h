@@ -387,7 +387,7 @@ void launch_encode_finish(const EncodeArgs &a, hipStream_t st);
 void launch_absmax(const float *X, int64_t count, uint32_t *out_bits, hipStream_t st);
 void launch_kmeans_accumulate(const float *X, int64_t nb, int D, const int32_t *assign, const uint32_t *absmax_bits,
                               int shift, long long *sums, int32_t *cnt, hipStream_t st);
-bool lloyd_lanes_supported(int D, int k);
+bool lloyd_lanes_supported(int64_t nt, int D, int k);
 size_t lloyd_lanes_words(int64_t nt, int D, int k); // 64-bit words of `part`
 // One iteration (update), or assignment and counts alone; assign and counts may be NULL (train.hip).
 void launch_lloyd_lanes(const float *X, int64_t nt, int D, int k, float *C, const uint32_t *absmax_bits, int shift,

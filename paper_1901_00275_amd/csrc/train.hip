@@ -251,11 +251,18 @@ __global__ __launch_bounds__(256) void k_lloyd_reduce(const unsigned long long *
     }
 }
 
-// Codebooks whose image fits a workgroup's share of LDS (256 centroids of 16 dimensions: 35 KB); more dimensions
-// or centroids go to the matrix cores, whose shortlist costs less per pair.
-bool lloyd_lanes_supported(int D, int k)
+// Codebooks whose image fits a workgroup's share of LDS (256 centroids of 16 dimensions: 35 KB).  A lane walks all k
+// centroids, so an iteration takes that walk's time however few vectors there are; up to 32 768 vectors (64 of 256 compute
+// units at work) the contraction of the general path is faster from some k on, which depends on the length of the walk.
+// Ten iterations of 3 000 vectors, ms of the general path and of this one: D = 16, k = 300 0.86 and 0.85, 380 0.85 and 1.02,
+// 481 0.95 and 1.24; D = 12, k = 330 0.86 and 0.80, 430 0.91 and 1.02, 630 0.99 and 1.44; D = 8, k = 850 1.09 and 1.02, 910 0.97
+// and 1.06; D = 6, k = 800 1.08 and 0.98, 950 0.99 and 1.12; D = 4, k = 1 638 1.11 and 1.03.  At 33 000 vectors: D = 16, k = 380
+// 1.72 and 1.09, D = 6, k = 950 2.12 and 1.14.
+bool lloyd_lanes_supported(int64_t nt, int D, int k)
 {
-    return (D == 4 || D == 6 || D == 8 || D == 12 || D == 16) && (int64_t)k * (D + 1) * 8 <= LLOYD_LDS;
+    if (D != 4 && D != 6 && D != 8 && D != 12 && D != 16) return false;
+    if ((int64_t)k * (D + 1) * 8 > LLOYD_LDS) return false;
+    return nt > 32768 || D == 4 || k <= (D == 16 ? 304 : D == 12 ? 360 : 880);
 }
 
 static int lloyd_blocks(int64_t nt)
@@ -273,8 +280,9 @@ void launch_lloyd_lanes(const float *X, int64_t nt, int D, int k, float *C, cons
     const int vec = ((uintptr_t)X) % 16 == 0;
     const size_t lds = (size_t)k * (D + 1) * 8;
     auto go = [&](auto kern) {
-        if (lds > 49152) // (48 KB of dynamic LDS need no asking)
-            (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (lds > 49152 && // (48 KB of dynamic LDS need no asking)
+            hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+            return; // (the caller asks for the error)
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(LLOYD_NT), lds, st, X, nt, k, (const float *)C, absmax_bits,
                            shift, update ? 1 : 0, vec, (unsigned long long *)part, assign);
     };

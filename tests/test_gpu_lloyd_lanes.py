@@ -13,6 +13,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("nt,D,k,off", [
     (1, 16, 1, 0), (511, 16, 7, 0), (513, 12, 33, 1), (300_001, 16, 256, 0), (5_000, 16, 481, 0), (5_000, 16, 482, 0),
     (4_097, 6, 255, 1), (9_000, 4, 1_638, 0), (9_000, 8, 257, 3),
+    # both sides of the choice between the one pass and the contraction
+    (32_768, 16, 305, 0), (32_769, 16, 305, 0), (700, 16, 304, 0), (700, 12, 360, 0), (700, 12, 361, 0), (900, 8, 880, 0), (900, 6, 881, 0),
+    (40_000, 16, 481, 0), (33_000, 8, 910, 0),
 ])
 def test_one_pass_iteration(nt, D, k, off):
     import paper_1901_00275_amd as vlq
@@ -51,3 +54,24 @@ def test_one_pass_iteration(nt, D, k, off):
     for c in np.unique(cell):
         want[c] = X64[cell == c].mean(0)
     assert (np.abs(Cd.cpu().numpy() - want) <= 2.0 ** -24 * np.abs(want) * (1 + 1e-6) + 1e-9).all()
+
+
+def test_few_vectors_and_many_centroids_take_no_longer():
+    """A lane's walk over 630 centroids outlasts the contraction when only a few workgroups have vectors (1.45 times)."""
+    import paper_1901_00275_amd as vlq
+
+    def ms(nt, D, k):
+        X, C0 = torch.randn(nt, D, device=DEV), torch.randn(k, D, device=DEV)
+        best = float("inf")
+        for _ in range(5):
+            C = C0.clone()
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            vlq.vlq_kmeans(X, nt, D, k, 20, C, None, None)
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1))
+        return best
+
+    # D = 13 has no one-pass form: the same contraction, one dimension more
+    assert ms(3_000, 12, 630) < 1.2 * ms(3_000, 13, 630)
