@@ -41,3 +41,45 @@ VLQ_HD float scan_wide_slack(float R2, float Y2, float Q2, float e2, float L, in
                       2.f * (k + 1.f) * Y * Q + (k + 4.f) * (R + Q) * (R + Q) + 2.f * L * (k + 1.f) * e * Q + 3.f * M2;
     return 1.01f * 5.9604645e-8f * sum + (float)(D + m + 16) * 4.7e-38f;
 }
+
+// ---- the encoder's fp16 product (coarse_half.hip) ----
+// Exponent of the power of two that brings mx to [2^14, 2^15); at most 2^+-60, so that the product of two inverse scales
+// stays in range (beyond that the squared norms of the rows overflow or vanish in fp32 as well).
+VLQ_HD int half_exponent(float mx)
+{
+    uint32_t bits;
+    __builtin_memcpy(&bits, &mx, 4);
+    const int ex = mx > 0.f ? 14 - ((int)(bits >> 23) - 127) : 0;
+    return ex < -60 ? -60 : (ex > 60 ? 60 : ex);
+}
+// Rows up to this many binades below their block's largest keep 18 binades of their own before a component is flushed, and
+// their residual is that of the rounding alone; beyond, every row of the block gets a scale of its own.
+#define HALF_GAP 10
+// A column's residual counts relative to its norm up to this share, beyond it as it is (the two words of the header).
+#define HALF_REL_MAX 5e-4f
+// Bits of a key that hold the tile, and what planting them costs: a key moves by less than 2^(bits - 23) of its own size,
+// and a key e = d - ||a||^2 is at most ||a||^2 + d in size; minimum and candidate both carry it.
+VLQ_HD int half_idx_bits(int tiles)
+{
+    int bits = 1;
+    while ((1 << bits) < tiles) ++bits;
+    return bits;
+}
+VLQ_HD float half_band_dist(int bits) { return 2.5f * ldexpf(1.f, bits - 23); }
+
+// Width of the band around the smallest distance dmin of a row a, xn = ||a||^2, res = ||a - a'||, for columns with
+// ||b - b'|| <= max(rho ||b||, big).  One value ||b||^2 - 2 <a', b'> is off by at most
+//   2 (res ||b|| + ||a'|| max(rho ||b||, big))      rounding to fp16 (Cauchy-Schwarz), ||a'|| <= 1.002 ||a||
+//   + 4 D 2^-24 s^2                                 fp32 accumulation of D products (twice D 2^-24 |a||b|) and the norms'
+//                                                   own rounding, |a|, |b| <= s
+// and a comparison involves two.  ||b|| <= ||a|| + sqrt(d) <= s for the columns that matter: their distance exceeds dmin by
+// no more than the values' error, for which s has a tenth to spare (and the term in big).  A row that lost more than 2^-9
+// of its norm (squares at the ends of fp32's range) gets every column.
+VLQ_HD float nn_half_band(float xn, float res, float rho, float big, float dmin, float band_dist, int D)
+{
+    const float na = sqrtf(xn);
+    if (!(res <= 0x1p-9f * na)) return INFINITY;
+    const float s = 1.1f * (na + sqrtf(dmin)) + 1.5f * sqrtf(na * big);
+    return 4.f * ((res + 1.01f * rho * na) * s + 1.01f * na * big) + 8.f * (float)(D + 8) * 0x1p-24f * s * s +
+           band_dist * (xn + dmin);
+}

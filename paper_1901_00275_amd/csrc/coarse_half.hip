@@ -40,9 +40,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 #define HALF_NORMAL 6.103515625e-5f // 2^-14: smaller halves are written as zero
 #define NO_COLUMN 3e38f // "norm" of columns past the end: finite, so that index bits can be planted in the key
 #define NO_KEY 1e38f    // from here on a key counts as absent
-// Rows up to 10 binades below their block's largest keep 18 binades of their own before a component is flushed, and
-// their residual is that of the rounding alone.
-#define HALF_GAP 10
 #define PAIR_CAP 2048 // (row, column) pairs of the second sweep that wait for their exact distance
 #define PAIR_COL_BITS 25
 #define PAIR_BATCH 4  // pairs a group of 16 lanes has under way
@@ -80,13 +77,6 @@ __global__ void k_half_header(float *hdr)
     if (threadIdx.x < 2) hdr[threadIdx.x] = 0.f;
 }
 
-// Exponent that brings mx to [2^14, 2^15); at most 2^+-60, so that the product of two inverse scales stays in range
-// (beyond that the squared norms of the rows overflow or vanish in fp32 as well)
-__device__ __forceinline__ int half_exponent(float mx)
-{
-    const int ex = mx > 0.f ? 14 - ((int)(__float_as_uint(mx) >> 23) - 127) : 0;
-    return max(-60, min(60, ex));
-}
 __device__ __forceinline__ float pow2f(int ex) { return __uint_as_float((uint32_t)(127 + ex) << 23); }
 
 // One workgroup per block of 128 rows, a thread per (row, chunk of 8 values), SPT times: one pass over X gives the
@@ -170,8 +160,8 @@ __global__ __launch_bounds__(256) void k_half_image(const float *__restrict__ X,
         if (!own && !hdr && row < rows && nrm < pow2f(14 - HALF_GAP)) apart = 1;
         if (hdr) {
             const bool ok = res < INFINITY && n2 > 0.f; // (a non-finite row's products never count)
-            float rel = ok && res <= 5e-4f * nrm ? res / nrm * 1.0001f : 0.f;
-            float big = ok && !(res <= 5e-4f * nrm) ? res * inv : 0.f;
+            float rel = ok && res <= HALF_REL_MAX * nrm ? res / nrm * 1.0001f : 0.f;
+            float big = ok && !(res <= HALF_REL_MAX * nrm) ? res * inv : 0.f;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) {
                 rel = fmaxf(rel, __shfl_xor(rel, o, 64));
@@ -539,12 +529,8 @@ int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D,
     a.nsplit = nsplit;
     const int ntiles = (N + HT - 1) / HT;
     a.tiles_per_split = (ntiles + nsplit - 1) / nsplit;
-    int bits = 1;
-    while ((1 << bits) < a.tiles_per_split) ++bits;
-    a.idx_bits = bits;
-    // planting the index moves a key by less than 2^(bits - 23) of its own size, and a key
-    // e = d - ||a||^2 is at most ||a||^2 + d in size; minimum and candidate both carry it
-    a.band_dist = 2.5f * ldexpf(1.f, bits - 23);
+    a.idx_bits = half_idx_bits(a.tiles_per_split);
+    a.band_dist = half_band_dist(a.idx_bits);
     *band_dist = a.band_dist;
     *bhdr = B.hdr;
     if (M <= 0 || N <= 0) return 0;

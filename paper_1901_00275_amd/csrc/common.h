@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/vlq.h"
+#include "bounds.h"
 
 #define VLQ_WAVE 64
 
@@ -229,7 +230,7 @@ void launch_coarse_gemm_nn(const float *A, int M, const float *B, int N, int D, 
 // The same shortlist on the fp16 matrix cores (coarse_half.hip), for the dimensions of coarse_bf16_supported.  Both
 // operands are first rewritten by launch_half_image (minus mu) into an image of half_image_bytes(rows, D) bytes, which
 // also gives the rows' squared norms and residual norms (each may be NULL); the columns' image needs its header.
-// The band the consumer has to apply is nn_half_band with *bhdr and *band_dist; the return value is 0 or a hipError_t.
+// The band the consumer has to apply is nn_half_band (bounds.h) with *bhdr and *band_dist; the return value is 0 or a hipError_t.
 size_t half_image_bytes(int64_t rows, int D);
 void launch_half_image(const float *X, int64_t rows, int D, const float *mu, void *img, bool header, float *norm2,
                        float *resid, hipStream_t st);
@@ -237,23 +238,6 @@ void launch_half_image(const float *X, int64_t rows, int D, const float *mu, voi
 int launch_nearest_half(const void *Aimg, int M, const void *Bimg, int N, int D, const float *X, const float *C,
                         const float *an, const float *ares, const float *bn, uint64_t *cand, int nsplit, float *band_dist,
                         const float **bhdr, hipStream_t st);
-// Width of the band around the smallest distance dmin of a row a, xn = ||a||^2, res = ||a - a'||, for columns with
-// ||b - b'|| <= max(rho ||b||, big).  One value ||b||^2 - 2 <a', b'> is off by at most
-//   2 (res ||b|| + ||a'|| max(rho ||b||, big))      rounding to fp16 (Cauchy-Schwarz), ||a'|| <= 1.002 ||a||
-//   + 4 D 2^-24 s^2                                 fp32 accumulation of D products (twice D 2^-24 |a||b|) and the norms'
-//                                                   own rounding, |a|, |b| <= s
-// and a comparison involves two.  ||b|| <= ||a|| + sqrt(d) <= s for the columns that matter: their distance exceeds dmin by
-// no more than the values' error, for which s has a tenth to spare (and the term in big).  A row that lost more than 2^-9 of its norm
-// (a tiny row beside a huge one) gets every column.
-__device__ __forceinline__ float nn_half_band(float xn, float res, float rho, float big, float dmin, float band_dist, int D)
-{
-    const float na = sqrtf(xn);
-    if (!(res <= 0x1p-9f * na)) return INFINITY;
-    const float s = 1.1f * (na + sqrtf(dmin)) + 1.5f * sqrtf(na * big);
-    return 4.f * ((res + 1.01f * rho * na) * s + 1.01f * na * big) + 8.f * (float)(D + 8) * 0x1p-24f * s * s +
-           band_dist * (xn + dmin);
-}
-
 // Operands of the search's sweeps on the bf16 matrix cores (coarse_bf16.hip): launch_split_bf16 rewrites
 // rows into an image of coarse_bf16_image_bytes(rows, D) bytes (bf16 hi/lo pairs in the order the product kernel
 // reads them).  mu (optional, [D]) is subtracted from every row before the split.

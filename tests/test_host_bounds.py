@@ -1,56 +1,18 @@
 """Arithmetic that kernels rely on (csrc/bounds.h), compiled for the host and checked there."""
-import ctypes
-import os
-import subprocess
-
 import numpy as np
 import pytest
 
-CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1901_00275_amd", "csrc")
-
-SOURCE = r"""
-#include "bounds.h"
-// The last turns of a workgroup whose lists hold `total` points: 0 if the places handed out are exactly those up to
-// `total` and the loop ends, else what went wrong.
-extern "C" int last_turns(long long total)
-{
-    const sw_place_t t = (sw_place_t)total;
-    const long long first = total / SW_TURN > 2 ? (total / SW_TURN - 2) * SW_TURN : 0;
-    long long next = first;
-    int turns = 0;
-    for (sw_place_t turn = (sw_place_t)first; turn < t; turn += SW_TURN) {
-        if (++turns > 4) return 1;
-        for (int wave = 0; wave < SW_NT / 64; ++wave) {
-            const sw_place_t base = sw_wave_base(turn, wave);
-            for (int u = 0; u < SW_U; ++u)
-                for (int lane = 0; lane < 64; ++lane) {
-                    const sw_place_t p = sw_place(base, u, lane);
-                    if (p < t && (long long)p != next++) return 2;
-                }
-        }
-    }
-    return next == total ? 0 : 3;
-}
-extern "C" float slack(float R2, float Y2, float Q2, float e2, float L, int D, int m)
-{
-    return scan_wide_slack(R2, Y2, Q2, e2, L, D, m);
-}
-"""
+import host_bounds
 
 
 @pytest.fixture(scope="module")
-def host(tmp_path_factory):
-    d = tmp_path_factory.mktemp("host")
-    src, so = d / "bounds.cpp", d / "bounds.so"
-    src.write_text(SOURCE)
-    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
-    return ctypes.CDLL(str(so))
+def host():
+    return host_bounds.lib()
 
 
 # an index holds up to 2^31 - 1 points: the places behind its last turn need 32 bits
 @pytest.mark.parametrize("total", [1, 2047, 2048, 2049, 10_000, 2**31 - 4097, 2**31 - 2049, 2**31 - 2048, 2**31 - 2047, 2**31 - 1])
 def test_places_up_to_the_largest_index(host, total):
-    host.last_turns.argtypes = [ctypes.c_longlong]
     assert host.last_turns(total) == 0
 
 
@@ -81,8 +43,6 @@ def total(v):
 @pytest.mark.parametrize("D,m", [(8, 8), (128, 8), (96, 16), (100, 20), (1024, 64)])
 def test_fast_distance_within_slack(host, kind, D, m):
     """The one-table distance and the 2m-lookup distance of the scan, both emulated in fp32 operation by operation."""
-    host.slack.restype = ctypes.c_float
-    host.slack.argtypes = [ctypes.c_float] * 5 + [ctypes.c_int] * 2
     rng = np.random.default_rng(D + m + len(kind))
     n, ds = 400, D // m
     scale = {"tight": 0.02}.get(kind, 0.5)
