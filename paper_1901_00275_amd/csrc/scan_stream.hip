@@ -369,7 +369,7 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
 }
 
 
-// Shapes served by this kernel; everything else takes the generic kernel.
+// Shapes served by this kernel; the others go to k_scan_wide or k_scan (scan_will_stream).
 bool scan_stream_supported(const ScanArgs &a)
 {
     return (a.m == 8 || a.m == 16) && a.K <= SS_KP && a.sx != nullptr && a.mu != nullptr && a.desc != nullptr &&
