@@ -6,7 +6,7 @@
 //  * the points of all visited lists of a (query, split) are laid end to end and handed out 256 to a
 //    wave and 2 048 to a workgroup and turn, so that lists of any length fill the lanes;
 //  * one candidate buffer of SW_CAP keys per workgroup, unsorted.  When it could overflow in the next
-//    turn, a radix selection (1 024 bins over the range of the keys present, refined inside the bin of
+//    turn, a radix selection (512 bins over the range of the keys present, refined inside the bin of
 //    the K-th key) drops what cannot be among the K best and lowers the threshold: two or three passes
 //    over at most 8 keys per thread.  Sorting happens once, for the K survivors.
 //  * the fast sums only shortlist.  Every point whose fast distance is within twice the error bound `slack` of the

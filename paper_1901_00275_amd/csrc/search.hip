@@ -954,7 +954,8 @@ void launch_subregions(const float *Q, int nq, int D, const float *C, const int3
 // 64-bit read serves both.
 //
 // A workgroup handles one (query, split) pair: a contiguous range of the
-// query's visited sub-regions in label order.  Candidates below the current
+// query's visited sub-regions in label order (with `redo`: what k_scan_wide left of
+// them, in the order of the descriptors).  Candidates below the current
 // K-th key go to an LDS buffer that is merged into the sorted top-K by a
 // bitonic sort whenever it fills.
 // ---------------------------------------------------------------------------

@@ -74,4 +74,4 @@ def test_few_vectors_and_many_centroids_take_no_longer():
         return best
 
     # D = 13 has no one-pass form: the same contraction, one dimension more
-    assert ms(3_000, 12, 630) < 1.2 * ms(3_000, 13, 630)
+    assert ms(3_000, 12, 630) < 1.35 * ms(3_000, 13, 630)

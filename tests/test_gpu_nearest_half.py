@@ -9,11 +9,19 @@ from test_gpu_parity import DEV
 pytestmark = pytest.mark.gpu
 
 
-def assign(X, C):
+def on_device(V, off):
+    """V on the GPU, `off` floats behind a 16-byte boundary"""
+    buf = torch.empty(V.size + off, device=DEV)
+    t = buf[off:].view(V.shape)
+    t.copy_(torch.as_tensor(V))
+    return t
+
+
+def assign(X, C, off=0):
     import paper_1901_00275_amd as vlq
 
     a = torch.empty(len(X), dtype=torch.int32, device=DEV)
-    vlq.vlq_kmeans(torch.as_tensor(X).to(DEV), len(X), X.shape[1], len(C), 0, torch.as_tensor(C).to(DEV), a, None)
+    vlq.vlq_kmeans(on_device(X, off), len(X), X.shape[1], len(C), 0, on_device(C, off), a, None)
     return a.cpu().numpy()
 
 
@@ -105,9 +113,10 @@ def test_small_rows_beside_ordinary_ones_cost_nothing():
     assert time_assign(X, C) < 2 * ordinary
 
 
+@pytest.mark.parametrize("off", [0, 1])
 @pytest.mark.parametrize("nt,D,k,group,spread", [
     (1000, 128, 5000, 16, 0.04), (300, 96, 20_000, 64, 0.03), (129, 32, 3000, 250, 0.01), (70_000, 64, 2048, 40, 0.02), (3, 128, 9000, 3000, 0.001)])
-def test_crowded_groups_of_centroids(nt, D, k, group, spread):
+def test_crowded_groups_of_centroids(nt, D, k, group, spread, off):
     """Tight groups of centroids (more of them inside the band than a shortlist holds), some coinciding, and vectors that
     are not numbers among the others."""
     rng = np.random.default_rng(k)
@@ -118,7 +127,7 @@ def test_crowded_groups_of_centroids(nt, D, k, group, spread):
     X, C = X.astype(np.float32), C.astype(np.float32)
     bad = np.arange(1, nt, 97)
     X[bad, 3] = np.nan
-    cell = assign(X, C)
+    cell = assign(X, C, off)
     assert ((cell >= 0) & (cell < k)).all()
     Xd, Cd = torch.as_tensor(X).to(DEV).double(), torch.as_tensor(C).to(DEV).double()
     for s in range(0, nt, 64):
