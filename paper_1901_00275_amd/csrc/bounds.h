@@ -70,8 +70,9 @@ VLQ_HD float half_band_dist(int bits) { return 2.5f * ldexpf(1.f, bits - 23); }
 // Width of the band around the smallest distance dmin of a row a, xn = ||a||^2, res = ||a - a'||, for columns with
 // ||b - b'|| <= max(rho ||b||, big).  One value ||b||^2 - 2 <a', b'> is off by at most
 //   2 (res ||b|| + ||a'|| max(rho ||b||, big))      rounding to fp16 (Cauchy-Schwarz), ||a'|| <= 1.002 ||a||
-//   + 4 D 2^-24 s^2                                 fp32 accumulation of D products (twice D 2^-24 |a||b|) and the norms'
-//                                                   own rounding, |a|, |b| <= s
+//   + 4 D 2^-24 s^2                                 fp32 accumulation of D products onto half the column's norm (D roundings
+//                                                   of at most ||b||^2 / 2 + |a||b|, doubled: 3 D 2^-24 s^2) and the
+//                                                   norms' own rounding, |a|, |b| <= s
 // and a comparison involves two.  ||b|| <= ||a|| + sqrt(d) <= s for the columns that matter: their distance exceeds dmin by
 // no more than the values' error, for which s has a tenth to spare (and the term in big).  A row that lost more than 2^-9
 // of its norm (squares at the ends of fp32's range) gets every column.

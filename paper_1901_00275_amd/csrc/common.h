@@ -213,7 +213,7 @@ void launch_coarse_gemm_full(const float *A, int M, const float *B, int N, int D
 #define VLQ_NN_ALL 0xFFFFFFFFu
 #define VLQ_NN_TILE 128
 // The fp16 product's keys carry the distance of the best column they stand for in the high word, and in the low word
-// a column c, for c and c + 32; or VLQ_NN_SLOT | slot, for the slot's columns of the split; or VLQ_NN_ALL, for all
+// a column c, for c, c + 16, c + 32 and c + 48; or VLQ_NN_SLOT | slot, for the slot's columns of the split; or VLQ_NN_ALL, for all
 // columns of the split.
 #define VLQ_NN_SLOT 0x80000000u
 // Width of the band around the smallest distance d of a row a:

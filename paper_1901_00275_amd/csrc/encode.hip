@@ -106,22 +106,24 @@ __device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gi
                 uint64_t got;
                 if (!a.bhdr) {
                     got = make_key(sqdist16(x, a.C + (int64_t)idx * a.D, a.D, l16, vec), idx);
-                } else if (!(idx & VLQ_NN_SLOT)) { // columns idx and idx + 32, by the even and the odd groups of 16 lanes
-                    const uint32_t i = idx + 32 * ((lane >> 4) & 1);
+                } else if (!(idx & VLQ_NN_SLOT)) { // columns idx + 16 j, a group of 16 lanes each
+                    const uint32_t i = idx + 16 * (lane >> 4);
                     const float d = sqdist16(x, a.C + (int64_t)min(i, (uint32_t)a.k - 1) * a.D, a.D, l16, vec);
                     got = i < (uint32_t)a.k ? make_key(d, i) : KEY_MAX;
-                    const uint64_t other = shfl_xor_u64(got, 16);
+                    uint64_t other = shfl_xor_u64(got, 16);
+                    got = other < got ? other : got;
+                    other = shfl_xor_u64(got, 32);
                     got = other < got ? other : got;
                 } else {
                     const int split = (c0 + src) / VLQ_NN_CANDS;
                     const int t0 = split * per, t1 = min(ntiles, t0 + per);
-                    const int base = (int)((idx >> 5) & 1) * 64 + (int)(idx & 31);
+                    const int base = (int)((idx >> 4) & 1) * 64 + (int)(idx & 15);
                     if (idx == VLQ_NN_ALL)
                         got = exact_nearest_of(x, a.C, a.k, a.D, lane, (t1 - t0) * VLQ_NN_TILE,
                                                [=](int c) { return t0 * VLQ_NN_TILE + c; });
                     else
-                        got = exact_nearest_of(x, a.C, a.k, a.D, lane, 2 * (t1 - t0), [=](int c) {
-                            return (t0 + (c >> 1)) * VLQ_NN_TILE + base + 32 * (c & 1);
+                        got = exact_nearest_of(x, a.C, a.k, a.D, lane, 4 * (t1 - t0), [=](int c) {
+                            return (t0 + (c >> 2)) * VLQ_NN_TILE + base + 16 * (c & 3);
                         });
                 }
                 bk = got < bk ? got : bk;
@@ -189,8 +191,8 @@ __global__ __launch_bounds__(NC_NT) void k_nearest_cells(EncodeArgs a)
             hard = hard || (mask != 0 && (idx & VLQ_NN_SLOT));
             mask &= mask - 1;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const uint32_t i = on ? idx + 32 * j : 0u;
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t i = on ? idx + 16 * j : 0u;
                 const float d = sqdist16(x, a.C + (int64_t)min(i, (uint32_t)a.k - 1) * D, D, l16, true);
                 if (on && i < (uint32_t)a.k) {
                     const uint64_t ek = make_key(d, i);

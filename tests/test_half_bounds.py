@@ -140,6 +140,28 @@ def test_accumulation_is_covered(D):
     assert worst > 1e-3
 
 
+@pytest.mark.parametrize("D", [32, 64, 96, 128])
+def test_accumulation_onto_the_norm_is_covered(D):
+    """The kernel's own order: half the norm first, the products added to it."""
+    host = host_bounds.lib()
+    rng = np.random.default_rng(D + 1)
+    worst = 0.0
+    for trial in range(50):
+        a = round_half(np.abs(rng.normal(size=(1, D))) + 1, 11)
+        b = round_half(np.abs(rng.normal(size=(64, D))) + 1, 11)
+        if trial % 2:  # all of one sign: the partial sums grow to |b|^2 / 2 + |a||b|
+            a = -a
+        acc = (0.5 * norm2(b)).astype(f32)
+        for d in range(D):
+            acc = (acc - a[0, d] * b[:, d]).astype(f32)
+        err = np.abs(2.0 * acc.astype(np.float64) - ((b ** 2).sum(1) - 2 * (b @ a[0]))).max()
+        d = ((a - b) ** 2).sum(1).min()
+        band = host.half_band((a ** 2).sum(), 0, 0, 0, d, 0, D)
+        assert 2 * err <= band
+        worst = max(worst, 2 * err / band)
+    assert worst > 1e-3
+
+
 def test_lossy_columns_are_covered():
     """A column that lost `big` of itself moves a product by up to |a'| big, twice in each of two values."""
     host = host_bounds.lib()
