@@ -83,7 +83,7 @@ struct vlq_index {
     float lam_step, lam_zero;
     double lam_step_d;
     // codebooks and graph
-    float *C = nullptr, *P = nullptr, *E = nullptr;
+    float *C = nullptr, *P = nullptr, *Pt = nullptr, *E = nullptr;
     int32_t *S = nullptr;
     // Distances do not depend on the origin, the rounding error of an inner product does: the
     // contractions and the scan's tables work relative to the mean of the centroids.
@@ -176,7 +176,7 @@ extern "C" void vlq_index_free(vlq_index_t *idx)
 {
     if (!idx) return;
     (void)hipDeviceSynchronize();
-    void *ptrs[] = {idx->C, idx->cn, idx->P, idx->E, idx->S, idx->st_label, idx->st_ids, idx->st_lam,
+    void *ptrs[] = {idx->C, idx->cn, idx->P, idx->Pt, idx->E, idx->S, idx->st_label, idx->st_ids, idx->st_lam,
                     idx->st_codes, idx->off, idx->ids, idx->codes, idx->lam, idx->sx, idx->ws,
                     idx->Cimg, idx->Chalf, idx->flags, idx->mu, idx->mu_c, idx->Cc};
     for (void *p : ptrs)
@@ -283,11 +283,14 @@ extern "C" int vlq_build_index(const vlq_params_t *params, const float *d_centro
         HIPCHK(hipMalloc(&idx->mu, (size_t)D * 4));
         HIPCHK(hipMalloc(&idx->mu_c, (size_t)D * 4));
         HIPCHK(hipMalloc(&idx->P, (size_t)256 * D * 4));
+        HIPCHK(hipMalloc(&idx->Pt, (size_t)256 * D * 4));
         HIPCHK(hipMalloc(&idx->S, (size_t)k * n * 4));
         HIPCHK(hipMalloc(&idx->E, (size_t)k * n * 4));
         HIPCHK(hipMalloc(&idx->off, ((size_t)k * n + 1) * 8));
         HIPCHK(hipMemcpyAsync(idx->C, d_centroids, (size_t)k * D * 4, hipMemcpyDeviceToDevice, st));
         HIPCHK(hipMemcpyAsync(idx->P, d_pq, (size_t)256 * D * 4, hipMemcpyDeviceToDevice, st));
+        launch_transpose_codewords(idx->P, m, D / m, idx->Pt, st);
+        LAUNCHCHK();
         HIPCHK(hipMemsetAsync(idx->off, 0, ((size_t)k * n + 1) * 8, st));
         launch_col_means(idx->C, k, D, idx->mu, idx->mu_c, st);
         LAUNCHCHK();
@@ -316,7 +319,6 @@ extern "C" int vlq_build_index(const vlq_params_t *params, const float *d_centro
         HIPCHK(hipStreamSynchronize(st));
         return VLQ_OK;
     };
-    (void)m;
     rc = body();
     if (rc) {
         char keep[sizeof(g_err)];
@@ -949,6 +951,7 @@ static int search_impl(vlq_index *idx, const float *d_q, int32_t nq, int32_t w1,
         a.S = idx->S;
         a.E = idx->E;
         a.P = idx->P;
+        a.Pt = idx->Pt;
         a.off = idx->off;
         a.ids = idx->ids;
         a.codes = idx->codes;

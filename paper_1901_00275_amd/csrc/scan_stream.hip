@@ -110,7 +110,7 @@ template <int M, bool PACKED>
 __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint4 *__restrict__ desc)
 {
     // all LDS is static: the table sits at a fixed address, which folds into the lookups' offsets
-    __shared__ float T[M * 256];
+    __shared__ __align__(16) float T[M * 256];
     __shared__ uint64_t keys[SS_NW * SS_WSZ];
     __shared__ float yv[VLQ_MAX_DIM];
     __shared__ unsigned long long sh_thr;              // upper bound of the K-th smallest key of the workgroup
@@ -135,13 +135,7 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
     if (tid < SS_NW) sh_q[tid] = KEY_MAX;
     __syncthreads();
     // the query's table: T[p][t] = 2 <(y - mu)^p, P[p][t]>
-    for (int idx = tid; idx < M * 256; idx += SS_NT) {
-        const float *w = a.P + (int64_t)idx * ds;
-        const float *yp = yv + (idx >> 8) * ds;
-        float s = 0.f;
-        for (int d = 0; d < ds; ++d) s = fmaf(yp[d], w[d], s);
-        T[idx] = 2.f * s;
-    }
+    for (int e = tid * 4; e < M * 256; e += SS_NT * 4) *(f32x4 *)(T + e) = table_entries(a.Pt, yv, ds, e);
     __syncthreads();
 
     // Merge of this wave's candidates into its sorted list.  Publishes two upper bounds of
@@ -368,6 +362,17 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
     }
 }
 
+
+__global__ void k_transpose_codewords(const float *__restrict__ P, int ds, float *__restrict__ Pt)
+{
+    const float *p = P + (int64_t)blockIdx.x * 256 * ds;
+    for (int d = 0; d < ds; ++d) Pt[((int64_t)blockIdx.x * ds + d) * 256 + threadIdx.x] = p[threadIdx.x * ds + d];
+}
+
+void launch_transpose_codewords(const float *P, int m, int ds, float *Pt, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_transpose_codewords, dim3((unsigned)m), dim3(256), 0, st, P, ds, Pt);
+}
 
 // Shapes served by this kernel; the others go to k_scan_wide or k_scan (scan_will_stream).
 bool scan_stream_supported(const ScanArgs &a)

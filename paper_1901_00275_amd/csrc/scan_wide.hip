@@ -170,29 +170,13 @@ __global__ __launch_bounds__(SW_NT, 4) void k_scan_wide(ScanArgs a, int lists_ma
         sh_red[2][wave] = cmax;
     }
     // T[p][t] = 2 <(y - mu)^p, P[p][t]>
-    for (int idx = tid; idx < m * 256; idx += SW_NT) {
-        const float *w = a.P + (int64_t)idx * ds;
-        const float *yp = yv + (idx >> 8) * ds;
-        float s = 0.f, wn = 0.f;
-        if ((ds & 3) == 0) {
-            for (int d = 0; d < ds; d += 4) {
-                const f32x4 wv = *(const f32x4 *)(w + d);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    s = fmaf(yp[d + x], wv[x], s);
-                    wn = fmaf(wv[x], wv[x], wn);
-                }
-            }
-        } else {
-            for (int d = 0; d < ds; ++d) {
-                s = fmaf(yp[d], w[d], s);
-                wn = fmaf(w[d], w[d], wn);
-            }
-        }
-        T[idx] = 2.f * s;
+    for (int e = tid * 4; e < m * 256; e += SW_NT * 4) {
+        f32x4 w2;
+        *(f32x4 *)(T + e) = table_entries(a.Pt, yv, ds, e, &w2);
+        float wn = fmaxf(fmaxf(w2.x, w2.y), fmaxf(w2.z, w2.w));
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) wn = fmaxf(wn, __shfl_xor(wn, o, 64));
-        if (lane == 0) atomicMax(&sh_wmax[idx >> 8], (int)__float_as_uint(wn)); // (a wave's 64 entries are of one p)
+        if (lane == 0) atomicMax(&sh_wmax[e >> 8], (int)__float_as_uint(wn)); // (a wave's 256 entries are of one p)
     }
     __syncthreads();
     // how far the fast distance can be from the 2m-lookup one
