@@ -26,17 +26,23 @@
 // table lives in LDS.  Waves take whole lists from a shared counter; a wave
 // issues all loads of up to 8 chunks of 64 points before it consumes the first,
 // and enough waves are resident per compute unit to cover the memory latency.
-// K-selection: every wave keeps its own sorted K-best list and a candidate
-// buffer in LDS and merges them alone; the waves share one monotonically
-// decreasing upper bound of the K-th best key; the eight lists are merged once
-// at the end, ids are resolved and the result is ordered by (distance, id).
+// K-selection: every wave keeps the keys that passed, unordered, in LDS and prunes them alone when their number has
+// grown by 128: the cut is found by bisection with ballot counts over keys in registers.  The waves share one
+// monotonically decreasing upper bound of the K-th best key; at the end what lies below it (K keys and a few more) is
+// ordered once, by counting.  Before, sorted lists were merged in LDS (bitonic networks, 35 stages a merge, a tree of
+// merges and a sort of the result): with few points a query that took more of the LDS pipe than the table lookups
+// (10 000 queries of 4 900 points, K = 100: 20 500 of 27 000 clocks a workgroup, 9 400 now; the scan 452 -> 360 us), and
+// with many it was in the lookups' way (10 000 queries, 1 024 lists of 238 points, m = 16: 8.7 -> 8.3 ms; 512 of 480, m = 8:
+// 4.94 -> 4.90).
 #include "common.h"
 
 #define SS_NT 512
 #define SS_NW 8
 #define SS_CH 8      // chunks of 64 points loaded ahead per wave
-#define SS_KP 128    // per-wave sorted list (K <= 128)
-#define SS_WSZ 256   // per-wave keys: list + candidate buffer
+#define SS_KP 128    // results at most (K <= 128)
+#define SS_WSZ 256   // keys a wave holds
+#define SS_NEW 128   // candidates taken up between two prunings
+#define SS_LEFT (SS_NW * SS_KP) // keys left at the end at most: K a wave
 #define SS_GL 16     // packed form: lists taken at a time
 #define SS_PCH 4     // packed form: chunks loaded ahead
 
@@ -44,63 +50,36 @@ typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
-// Wave-private merge of the candidate buffer wk[SS_KP .. SS_WSZ) (unsorted, padded with KEY_MAX) into
-// the sorted list wk[0 .. SS_KP): the candidates are sorted in descending order, which makes the whole
-// array one bitonic sequence; a single compare-exchange stage against the list leaves the SS_KP
-// smallest keys (still bitonic) in the list's place, and a bitonic merge orders them.  About half
-// the LDS traffic of sorting all SS_WSZ keys.  (LDS operations of one wave complete in issue
-// order, so no workgroup barrier is needed.)
-// bitonic sequence of SS_KP keys -> ascending (one wave, one comparator per lane and stage)
-__device__ __forceinline__ void wave_bitonic_merge(volatile lds_u64 *wk, int lane)
+// smallest value of the wave, uniform: rows of 16 through the lane-crossing operands, then the four rows
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
 {
-    for (int j = SS_KP >> 1; j > 0; j >>= 1) {
-        const int l = ((lane & ~(j - 1)) << 1) | (lane & (j - 1));
-        const int r = l | j;
-        const uint64_t x = wk[l], y = wk[r];
-        if (x > y) {
-            wk[l] = y;
-            wk[r] = x;
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
+#define VLQ_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, true))
+    VLQ_DPP_MIN(0xB1);  // quad_perm [1, 0, 3, 2]
+    VLQ_DPP_MIN(0x4E);  // quad_perm [2, 3, 0, 1]
+    VLQ_DPP_MIN(0x141); // row_half_mirror
+    VLQ_DPP_MIN(0x140); // row_mirror
+#undef VLQ_DPP_MIN
+    const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+    return min(min(a, b), min(c, d));
 }
 
-__device__ __forceinline__ void wave_merge_candidates(volatile lds_u64 *wk, int lane)
+// A bound with `need` or more of the wave's values below it (exactly so many unless values repeat), by bisection with
+// ballot counts: o[] are the values (at least `need` of them in [lo, hi], the smaller ones none), the bound is uniform.
+__device__ __forceinline__ uint32_t wave_cut(const uint32_t (&o)[SS_WSZ / 64], uint32_t lo, uint32_t hi, int need)
 {
-    static_assert(SS_KP == 128 && SS_WSZ == 256, "one comparator per lane and stage");
-    volatile lds_u64 *c = wk + SS_KP;
-    for (int k = 2; k <= SS_KP; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const int l = ((lane & ~(j - 1)) << 1) | (lane & (j - 1));
-            const int r = l | j;
-            const uint64_t x = c[l], y = c[r];
-            if ((x < y) == ((l & k) == 0)) { // descending
-                c[l] = y;
-                c[r] = x;
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+        int c = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int i = lane + 64 * h;
-        const uint64_t x = wk[i], y = c[i];
-        if (y < x) wk[i] = y;
+        for (int j = 0; j < SS_WSZ / 64; ++j) c += __popcll(__ballot(o[j] < mid));
+        if (c == need) return mid;
+        if (c < need)
+            lo = mid;
+        else
+            hi = mid - 1;
     }
-    __builtin_amdgcn_wave_barrier();
-    wave_bitonic_merge(wk, lane);
-}
-
-// Two sorted lists a, b of SS_KP keys each -> the SS_KP smallest of both, sorted, in a (one wave).
-__device__ __forceinline__ void wave_merge_lists(volatile lds_u64 *a, volatile lds_u64 *b, int lane)
-{
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int i = lane + 64 * h;
-        const uint64_t x = a[i], y = b[SS_KP - 1 - i];
-        if (y < x) a[i] = y;
-    }
-    __builtin_amdgcn_wave_barrier();
-    wave_bitonic_merge(a, lane);
+    return lo + 1;
 }
 
 // PACKED: the lists are short (a few tens of points): a wave takes SS_GL lists at a time and lays
@@ -111,10 +90,13 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
 {
     // all LDS is static: the table sits at a fixed address, which folds into the lookups' offsets
     __shared__ __align__(16) float T[M * 256];
-    __shared__ uint64_t keys[SS_NW * SS_WSZ];
+    __shared__ __align__(16) uint64_t keys[SS_NW * SS_WSZ];
     __shared__ float yv[VLQ_MAX_DIM];
     __shared__ unsigned long long sh_thr;              // upper bound of the K-th smallest key of the workgroup
-    __shared__ unsigned long long sh_q[SS_NW];         // every wave's ceil(K/8)-th key
+    __shared__ unsigned long long sh_q[SS_NW];         // every wave's bound with ceil(K/8) of its keys below it
+    __shared__ int sh_cnt[SS_NW], sh_ties;
+    __shared__ int sh_slot[SS_KP];                     // results that claim a place
+    __shared__ uint64_t sh_out[SS_KP];                 // the results in order
     __shared__ int sh_next;                            // next list to hand out
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -124,40 +106,81 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
     const int K = a.K, D = a.D, ds = D / M;
     const int KQ = (K + SS_NW - 1) / SS_NW;
     volatile lds_u64 *wk = (volatile lds_u64 *)(keys + wave * SS_WSZ);
-    int wcnt = 0;
+    int wcnt = 0, wlimit = SS_NEW; // keys held; how many may be before the next pruning
 
     for (int d = tid; d < D; d += SS_NT) yv[d] = a.Q[(int64_t)q * D + d] - a.mu[d];
-    for (int i = lane; i < SS_WSZ; i += 64) wk[i] = KEY_MAX;
     if (tid == 0) {
         sh_thr = KEY_MAX;
         sh_next = r0;
     }
     if (tid < SS_NW) sh_q[tid] = KEY_MAX;
+    if (tid < SS_KP) sh_slot[tid] = 0;
+    if (tid == 0) sh_ties = 0;
     __syncthreads();
     // the query's table: T[p][t] = 2 <(y - mu)^p, P[p][t]>
     for (int e = tid * 4; e < M * 256; e += SS_NT * 4) *(f32x4 *)(T + e) = table_entries(a.Pt, yv, ds, e);
     __syncthreads();
 
-    // Merge of this wave's candidates into its sorted list.  Publishes two upper bounds of
-    // the K-th smallest key of the whole workgroup: the wave's own K-th key, and the largest
-    // of all waves' ceil(K/8)-th keys (8 * ceil(K/8) >= K keys lie at or below it).
-    auto merge_wave = [&]() {
-        for (int i = SS_KP + wcnt + lane; i < SS_WSZ; i += 64) wk[i] = KEY_MAX;
-        __builtin_amdgcn_wave_barrier();
-        wave_merge_candidates(wk, lane);
-        for (int i = K + lane; i < SS_KP; i += 64) wk[i] = KEY_MAX;
-        __builtin_amdgcn_wave_barrier();
+    // Pruning of the wave's keys to its K smallest (of equal distances the first positions).  Publishes two
+    // upper bounds of the K-th smallest key of the whole workgroup: the wave's own, and the largest of all waves' bounds
+    // with ceil(K/8) keys below them (8 * ceil(K/8) >= K keys lie below it).  No order is needed for either, so the keys
+    // stay in registers and the bounds are found by bisection with ballot counts.  (Sorting them in LDS cost 35 stages
+    // a time; with short scans that kept the LDS pipe busy, not the table lookups.)
+    auto prune = [&]() {
+        uint64_t bound = sh_thr, k[SS_WSZ / 64];
+        uint32_t o[SS_WSZ / 64], lo = 0xFFFFFFFFu, hi = 0xFFFFFFFFu; // hi: the complement of the largest
+        int cnt = 0;
+#pragma unroll
+        for (int j = 0; j < SS_WSZ / 64; ++j) {
+            k[j] = lane + 64 * j < wcnt ? wk[lane + 64 * j] : KEY_MAX;
+            const bool in = k[j] < bound;
+            o[j] = in ? (uint32_t)(k[j] >> 32) : 0xFFFFFFFFu; // (no key has this high word)
+            cnt += __popcll(__ballot(in));
+            lo = min(lo, o[j]);
+            if (in) hi = min(hi, ~o[j]);
+        }
+        lo = wave_min_u32(lo);
+        hi = ~wave_min_u32(hi);
+        if (cnt > K) {
+            const uint32_t cut = wave_cut(o, lo, hi, K);
+            uint64_t own = (uint64_t)cut << 32;
+            int below = 0;
+#pragma unroll
+            for (int j = 0; j < SS_WSZ / 64; ++j) below += __popcll(__ballot(o[j] < cut));
+            if (below > K) { // equal distances at the cut
+                uint32_t t[SS_WSZ / 64];
+                int less = 0;
+#pragma unroll
+                for (int j = 0; j < SS_WSZ / 64; ++j) {
+                    less += __popcll(__ballot(o[j] < cut - 1));
+                    t[j] = o[j] == cut - 1 ? (uint32_t)k[j] : 0xFFFFFFFFu;
+                }
+                own = ((uint64_t)(cut - 1) << 32) | wave_cut(t, 0u, 0xFFFFFFFEu, K - less);
+            }
+            bound = own < bound ? own : bound;
+            hi = min(hi, (uint32_t)(own >> 32));
+        }
         wcnt = 0;
-        if (lane == 0) sh_q[wave] = wk[KQ - 1];
+#pragma unroll
+        for (int j = 0; j < SS_WSZ / 64; ++j) {
+            const bool in = k[j] < bound;
+            const uint64_t mask = __ballot(in);
+            if (in) wk[wcnt + __popcll(mask & ((1ull << lane) - 1ull))] = k[j];
+            wcnt += __popcll(mask);
+        }
+        wlimit = min(wcnt + SS_NEW, SS_WSZ);
+        if (cnt >= KQ) {
+            const uint32_t q = wave_cut(o, lo, hi, KQ);
+            if (lane == 0) sh_q[wave] = (uint64_t)q << 32;
+        }
         __builtin_amdgcn_wave_barrier();
-        uint64_t bound = 0;
+        uint64_t all = 0;
 #pragma unroll
         for (int w = 0; w < SS_NW; ++w) {
             const uint64_t t = ((volatile lds_u64 *)sh_q)[w];
-            bound = t > bound ? t : bound;
+            all = t > all ? t : all;
         }
-        const uint64_t own = wk[K - 1];
-        bound = own < bound ? own : bound;
+        bound = all < bound ? all : bound;
         if (lane == 0 && bound != KEY_MAX) atomicMin(&sh_thr, (unsigned long long)bound);
         __builtin_amdgcn_wave_barrier();
     };
@@ -185,15 +208,15 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
             pass = pass && key < thr;
             mask = __ballot(pass);
             int np = __popcll(mask);
-            if (np && wcnt + np > SS_WSZ - SS_KP) {
-                merge_wave();
+            if (np && wcnt + np > wlimit) {
+                prune();
                 thr = sh_thr;
                 thr_f = thr == KEY_MAX ? INFINITY : ord2f((uint32_t)(thr >> 32));
                 pass = pass && key < thr;
                 mask = __ballot(pass);
                 np = __popcll(mask);
             }
-            if (pass) wk[SS_KP + wcnt + __popcll(mask & ((1ull << lane) - 1ull))] = key;
+            if (pass) wk[wcnt + __popcll(mask & ((1ull << lane) - 1ull))] = key;
             wcnt += np;
         }
     };
@@ -310,58 +333,137 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
     }
     }
 
-    // ---- merge the eight wave lists; resolve ids; order by (distance, id) ----
-    // Every wave's list is sorted: a tree of three rounds merges them pairwise, each merge keeping
-    // the SS_KP smallest keys of its two lists (one wave per merge, no sorting).
-    merge_wave();
-    const int KP = next_pow2_dev(K);
+    // ---- the K smallest of all waves' keys; ids; order by (distance, id) ----
+    // What is left below the last bound (K keys and a few more) goes to one array, distances and positions apart; a key's
+    // place is the number of smaller distances, counted by one to four lanes a key.
+    prune();
+    __syncthreads();
+    thr = sh_thr;
+    uint64_t left[SS_WSZ / 64];
+    int mine = 0;
 #pragma unroll
-    for (int step = SS_NW / 2; step >= 1; step >>= 1) {
-        __syncthreads();
-        if (wave < step) wave_merge_lists(wk, (volatile lds_u64 *)(keys + (wave + step) * SS_WSZ), lane);
+    for (int j = 0; j < SS_WSZ / 64; ++j) {
+        left[j] = lane + 64 * j < wcnt ? wk[lane + 64 * j] : KEY_MAX;
+        mine += __popcll(__ballot(left[j] < thr));
+    }
+    if (lane == 0) sh_cnt[wave] = mine;
+    __syncthreads(); // (all keys are in registers)
+    uint32_t *od = (uint32_t *)keys;                // [SS_LEFT + 16] ordered distances
+    uint32_t *op = od + SS_LEFT + 16;               // [SS_LEFT] positions
+    uint32_t *to = (uint32_t *)T, *tp = to + SS_LEFT; // [SS_LEFT] those of equal distance (the table is dead)
+    static_assert(M * 256 >= 2 * SS_LEFT, "they take the table's place");
+    int at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < SS_NW; ++w) {
+        const int c = sh_cnt[w];
+        at += w < wave ? c : 0;
+        total += c;
+    }
+#pragma unroll
+    for (int j = 0; j < SS_WSZ / 64; ++j) {
+        const bool in = left[j] < thr;
+        const uint64_t mask = __ballot(in);
+        if (in) {
+            const int i = at + __popcll(mask & ((1ull << lane) - 1ull));
+            od[i] = (uint32_t)(left[j] >> 32);
+            op[i] = (uint32_t)left[j];
+        }
+        at += __popcll(mask);
+    }
+    if (tid < 16) od[total + tid] = 0xFFFFFFFFu; // up to a multiple of 16
+    __syncthreads();
+    const int gs = total <= SS_NT / 4 ? 2 : (total <= SS_NT / 2 ? 1 : 0); // 2^gs lanes a key
+    const int per = (total + (4 << gs) - 1) >> (2 + gs), g = tid & ((1 << gs) - 1); // quadruples a lane goes through
+    auto over_group = [&](int c) {
+        if (gs >= 1) c += __builtin_amdgcn_update_dpp(0, c, 0xB1, 0xF, 0xF, true);
+        if (gs == 2) c += __builtin_amdgcn_update_dpp(0, c, 0x4E, 0xF, 0xF, true);
+        return c;
+    };
+    int place[SS_LEFT / SS_NT]; // of the keys tid >> gs, + 512
+#pragma unroll
+    for (int e = 0; e < SS_LEFT / SS_NT; ++e) {
+        place[e] = K;
+        if (e * SS_NT >= total) break; // uniform
+        const int i = e * SS_NT + (tid >> gs);
+        const uint32_t o = od[min(i, total - 1)];
+        int c = 0;
+#pragma unroll 4
+        for (int j = 0; j < per; ++j) {
+            const u32x4_t v = *(const u32x4_t *)(od + 4 * (g * per + j));
+            c += (v.x < o) + (v.y < o) + (v.z < o) + (v.w < o);
+        }
+        place[e] = over_group(c);
+        if (i < total && g == 0 && place[e] < K) atomicAdd(&sh_slot[place[e]], 1);
     }
     __syncthreads();
-    // The first wave resolves the ids of the K survivors and orders them by (distance, id): the list is
-    // in (distance, position) order, so only keys of equal distance can move (a wave-private sort).
-    if (wave != 0) return;
-    {
-        uint64_t mine[2];
+    // a place that one key claims is settled; equal distances claim the same one and go on a list
+    int tied[SS_LEFT / SS_NT];
+    bool any = false;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = lane + 64 * h;
-            const uint64_t key = i < K ? wk[i] : KEY_MAX;
-            mine[h] = key != KEY_MAX ? ((key & 0xFFFFFFFF00000000ull) | (uint32_t)a.ids[(uint32_t)key]) : KEY_MAX;
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) wk[lane + 64 * h] = mine[h];
-        __builtin_amdgcn_wave_barrier();
-        for (int k = 2; k <= KP; k <<= 1)
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const int l = ((lane & ~(j - 1)) << 1) | (lane & (j - 1));
-                const int r = l | j;
-                if (r < KP) {
-                    const uint64_t x = wk[l], y = wk[r];
-                    if ((x > y) == ((l & k) == 0)) {
-                        wk[l] = y;
-                        wk[r] = x;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
+    for (int e = 0; e < SS_LEFT / SS_NT; ++e) {
+        tied[e] = -1;
+        const int i = e * SS_NT + (tid >> gs);
+        if (i < total && g == 0 && place[e] < K) {
+            if (sh_slot[place[e]] == 1) {
+                sh_out[place[e]] = ((uint64_t)od[i] << 32) | (uint32_t)a.ids[op[i]];
+            } else {
+                tied[e] = atomicAdd(&sh_ties, 1);
+                to[tied[e]] = od[i];
+                tp[tied[e]] = op[i];
+                any = true;
             }
+        }
     }
-    if (a.nsplit > 1) {
-        uint64_t *dst = a.partial + ((int64_t)q * a.nsplit + split) * K;
-        for (int i = lane; i < K; i += 64) dst[i] = wk[i];
-    } else {
-        for (int i = lane; i < K; i += 64) {
-            const uint64_t key = wk[i];
-            const bool ok = key != KEY_MAX;
-            a.out_dist[(int64_t)q * K + i] = ok ? ord2f((uint32_t)(key >> 32)) : INFINITY;
-            a.out_ids[(int64_t)q * K + i] = ok ? (int32_t)(uint32_t)key : -1;
+    if (__syncthreads_or(any)) {
+        // the first positions of a distance are taken, and ordered by id
+        const int nt = sh_ties;
+        if (tid < 4 && nt + tid < SS_LEFT) to[nt + tid] = 0xFFFFFFFFu; // (read four at a time)
+        __syncthreads();
+        // entries of the list with distance o and x below v (or x == v and an earlier entry than `own`)
+        auto before = [&](uint32_t o, uint32_t v, int own) {
+            int c = 0;
+#pragma unroll 4
+            for (int j = 0; j < nt; j += 4) {
+                const u32x4_t d = *(const u32x4_t *)(to + j), x = *(const u32x4_t *)(tp + j);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c += d[u] == o && (x[u] < v || (x[u] == v && j + u < own));
+            }
+            return c;
+        };
+        uint32_t o[SS_LEFT / SS_NT], id[SS_LEFT / SS_NT];
+#pragma unroll
+        for (int e = 0; e < SS_LEFT / SS_NT; ++e) {
+            if (tied[e] < 0) continue;
+            const uint32_t p = tp[tied[e]];
+            o[e] = to[tied[e]];
+            const bool in = place[e] + before(o[e], p, 0) < K;
+            id[e] = in ? (uint32_t)a.ids[p] : 0u;
+            if (!in) place[e] = K;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < SS_LEFT / SS_NT; ++e) {
+            if (tied[e] < 0) continue;
+            tp[tied[e]] = id[e];
+            if (place[e] == K) to[tied[e]] = 0xFFFFFFFFu;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < SS_LEFT / SS_NT; ++e)
+            if (tied[e] >= 0 && place[e] < K)
+                sh_out[place[e] + before(o[e], id[e], tied[e])] = ((uint64_t)o[e] << 32) | id[e];
+        __syncthreads();
+    }
+    for (int i = tid; i < K; i += SS_NT) {
+        const uint64_t key = i < total ? sh_out[i] : KEY_MAX;
+        if (a.nsplit > 1) {
+            a.partial[((int64_t)q * a.nsplit + split) * K + i] = key;
+        } else {
+            a.out_dist[(int64_t)q * K + i] = i < total ? ord2f((uint32_t)(key >> 32)) : INFINITY;
+            a.out_ids[(int64_t)q * K + i] = i < total ? (int32_t)(uint32_t)key : -1;
         }
     }
 }
-
 
 __global__ void k_transpose_codewords(const float *__restrict__ P, int ds, float *__restrict__ Pt)
 {
