@@ -905,20 +905,12 @@ __global__ __launch_bounds__(1024) void k_small_cells(const float *__restrict__ 
         sh_g = 0;
     }
     __syncthreads();
-    if (tid < 64) { // one wave: the w-th smallest of the minima, bit by bit from the top (ballot counts)
+    if (tid < 64) { // one wave: the w-th smallest of the minima
         uint32_t u[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) u[e] = mins[lane + 64 * e];
-        uint32_t result = 0;
-        if (w > G) result = 0xFFFFFFFEu; // fewer groups than cells wanted: every group is looked at
-        else
-            for (int bit = 31; bit >= 0; --bit) {
-                const uint32_t trial = result | (1u << bit);
-                int below = 0;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) below += __popcll(__ballot(u[e] < trial));
-                if (below < w) result = trial;
-            }
+        // (fewer groups than cells wanted: every group is looked at)
+        const uint32_t result = w > G ? 0xFFFFFFFEu : wave_kth(u, w);
         if (lane == 0) sh_tau = result;
     }
     __syncthreads();

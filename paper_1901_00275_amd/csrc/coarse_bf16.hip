@@ -464,13 +464,7 @@ __global__ __launch_bounds__(256) void k_cell_threshold(const float *__restrict_
             const float gv = grow[min(lane + 64 * e, G - 1)];
             u[e] = lane + 64 * e < G ? f2ord(gv) : 0xFFFFFFFFu;
         }
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t trial = result | (1u << bit);
-            int below = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) below += __popcll(__ballot(u[e] < trial)); // (a filler is below nothing)
-            if (below < want) result = trial;
-        }
+        result = wave_kth(u, want);
     } else if (G <= 4096) { // small batches have many column splits: still in registers
         uint32_t u[64];
 #pragma unroll
@@ -489,11 +483,8 @@ __global__ __launch_bounds__(256) void k_cell_threshold(const float *__restrict_
                 m2 = min(m2, max(m1, u[e]));
                 m1 = min(m1, u[e]);
             }
-            uint32_t bound = 0;
-            for (int bit = 31; bit >= 0; --bit) {
-                const uint32_t trial = bound | (1u << bit);
-                if (__popcll(__ballot(m1 < trial)) + __popcll(__ballot(m2 < trial)) < want) bound = trial;
-            }
+            const uint32_t m[2] = {m1, m2};
+            const uint32_t bound = wave_kth(m, want);
             int keep = 0;
 #pragma unroll
             for (int e = 0; e < 64; ++e) keep += u[e] <= bound;
@@ -513,24 +504,11 @@ __global__ __launch_bounds__(256) void k_cell_threshold(const float *__restrict_
                 uint32_t v[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] = lane + 64 * e < total ? mine[lane + 64 * e] : 0xFFFFFFFFu;
-                for (int bit = 31; bit >= 0; --bit) {
-                    const uint32_t trial = result | (1u << bit);
-                    int below = 0;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) below += __popcll(__ballot(v[e] < trial));
-                    if (below < want) result = trial;
-                }
+                result = wave_kth(v, want);
                 pruned = true;
             }
         }
-        if (!pruned)
-            for (int bit = 31; bit >= 0; --bit) {
-                const uint32_t trial = result | (1u << bit);
-                int below = 0;
-#pragma unroll
-                for (int e = 0; e < 64; ++e) below += __popcll(__ballot(u[e] < trial));
-                if (below < want) result = trial;
-            }
+        if (!pruned) result = wave_kth(u, want);
     } else {
         for (int i = lane; i < G; i += 64) mine[i] = f2ord(grow[i]);
         for (int bit = 31; bit >= 0; --bit) {

@@ -75,6 +75,59 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
     return v;
 }
 
+// smallest value of the wave, uniform: rows of 16 through the lane-crossing operands, then the four rows
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
+{
+#define VLQ_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, true))
+    VLQ_DPP_MIN(0xB1);  // quad_perm [1, 0, 3, 2]
+    VLQ_DPP_MIN(0x4E);  // quad_perm [2, 3, 0, 1]
+    VLQ_DPP_MIN(0x141); // row_half_mirror
+    VLQ_DPP_MIN(0x140); // row_mirror
+#undef VLQ_DPP_MIN
+    const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+    return min(min(a, b), min(c, d));
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return ~wave_min_u32(~v); }
+
+// A bound with `need` or more of a wave's values below it (exactly so many unless values repeat), by bisection with
+// ballot counts: o[] are the values (at least `need` of them in [lo, hi], the smaller ones none), the bound is uniform.
+// It ends as soon as the count fits, after 8 - 14 rounds of a few hundred spread values; a search bit by bit from the top
+// takes all 32.
+template <int N>
+__device__ __forceinline__ uint32_t wave_cut(const uint32_t (&o)[N], uint32_t lo, uint32_t hi, int need)
+{
+    while (lo < hi) {
+        const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+        int c = 0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) c += __popcll(__ballot(o[j] < mid));
+        if (c == need) return mid;
+        if (c < need)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return lo + 1;
+}
+
+// The need-th smallest of a wave's values (1-based); 0xFFFFFFFF stands for no value, at least `need` are there.
+template <int N>
+__device__ __forceinline__ uint32_t wave_kth(const uint32_t (&o)[N], int need)
+{
+    uint32_t lo = 0xFFFFFFFFu, hi = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        lo = min(lo, o[j]);
+        hi = max(hi, o[j] == 0xFFFFFFFFu ? 0u : o[j]);
+    }
+    const uint32_t cut = wave_cut(o, wave_min_u32(lo), wave_max_u32(hi), need);
+    uint32_t v = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) v = max(v, o[j] < cut ? o[j] : 0u);
+    return wave_max_u32(v);
+}
+
 // Orders the LDS traffic of one wave across its lanes: what any lane wrote before is what every lane reads behind.
 // The hardware keeps the order of a wave's LDS operations by itself; the compiler has to be told.
 __device__ __forceinline__ void wave_lds_order()

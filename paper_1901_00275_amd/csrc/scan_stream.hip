@@ -50,38 +50,6 @@ typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 
-// smallest value of the wave, uniform: rows of 16 through the lane-crossing operands, then the four rows
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
-{
-#define VLQ_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, true))
-    VLQ_DPP_MIN(0xB1);  // quad_perm [1, 0, 3, 2]
-    VLQ_DPP_MIN(0x4E);  // quad_perm [2, 3, 0, 1]
-    VLQ_DPP_MIN(0x141); // row_half_mirror
-    VLQ_DPP_MIN(0x140); // row_mirror
-#undef VLQ_DPP_MIN
-    const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
-    const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
-    return min(min(a, b), min(c, d));
-}
-
-// A bound with `need` or more of the wave's values below it (exactly so many unless values repeat), by bisection with
-// ballot counts: o[] are the values (at least `need` of them in [lo, hi], the smaller ones none), the bound is uniform.
-__device__ __forceinline__ uint32_t wave_cut(const uint32_t (&o)[SS_WSZ / 64], uint32_t lo, uint32_t hi, int need)
-{
-    while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo + 1) >> 1);
-        int c = 0;
-#pragma unroll
-        for (int j = 0; j < SS_WSZ / 64; ++j) c += __popcll(__ballot(o[j] < mid));
-        if (c == need) return mid;
-        if (c < need)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    return lo + 1;
-}
-
 // PACKED: the lists are short (a few tens of points): a wave takes SS_GL lists at a time and lays
 // their points end to end over its lanes, so that a chunk of 64 lanes holds several lists; each
 // lane finds its list from the running lengths and carries its own a, b - a.
