@@ -769,7 +769,7 @@ extern "C" int vlq_index_finalize(vlq_index_t *idx, void *stream)
     std::vector<int64_t> hoff; // host copy of the offsets, fetched only if the third tier is needed
     for (int round = 0; round < 1 << 20; ++round) {
         HIPCHK(hipMemsetAsync(n_long, 0, 4, st));
-        launch_list_sort(idx->off, nl, m, idx->ids, idx->codes, idx->lam, longs, n_long, MAX_LONG, st);
+        launch_list_sort(idx->off, nl, m, idx->ids, idx->codes, idx->lam, N, longs, n_long, MAX_LONG, st);
         LAUNCHCHK();
         int32_t hn = 0;
         HIPCHK(hipMemcpyAsync(&hn, n_long, 4, hipMemcpyDeviceToHost, st));
@@ -817,7 +817,7 @@ extern "C" int vlq_index_finalize(vlq_index_t *idx, void *stream)
     }
     if (N > 0) {
         launch_list_static(idx->off, nl, idx->p.n_edges, idx->p.d, m, idx->C, idx->S, idx->P, idx->mu, idx->codes,
-                           idx->lam, idx->lam_step_d, idx->lam_zero, idx->sx, st);
+                           idx->lam, idx->lam_step_d, idx->lam_zero, N, idx->sx, st);
         LAUNCHCHK();
     }
     HIPCHK(hipStreamSynchronize(st));

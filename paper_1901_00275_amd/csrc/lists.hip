@@ -216,6 +216,10 @@ void launch_list_scatter(const int32_t *label, const int32_t *st_ids, const uint
 // SORT_MAX points in LDS; longer unsorted lists are reported to the host.
 #define SORT_MAX 1024
 
+#define LS_SHORT 16 // mean points a list up to which 16 lanes serve one
+// SHORT: 64 lists a workgroup, those of up to 16 points without LDS keys or barriers (2 M points in 524 288 lists, a
+// workgroup each: 1.90 -> 0.23 ms)
+template <bool SHORT>
 __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ off, int64_t nl, int m,
                                                   int32_t *__restrict__ ids, uint8_t *__restrict__ codes,
                                                   uint8_t *__restrict__ lam, int32_t *__restrict__ long_lists,
@@ -226,10 +230,9 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
     uint8_t *pay = (uint8_t *)(keys + SORT_MAX);  // [SORT_MAX * (m + 1)]
     __shared__ int unsorted;
     const int tid = threadIdx.x;
-    const int64_t l = blockIdx.x;
-    const int64_t beg = off[l];
-    const int64_t len = off[l + 1] - beg;
+    auto sort_list = [&](int64_t l, int64_t beg, int64_t len) {
     if (len <= 1) return;
+    __syncthreads(); // (the list before has been read)
     if (tid == 0) unsorted = 0;
     __syncthreads();
     for (int64_t i = tid; i + 1 < len; i += 64)
@@ -257,15 +260,71 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
         lam[beg + i] = pay[len * m + src];
         for (int p = 0; p < m; ++p) codes[(beg + i) * m + p] = pay[src * m + p];
     }
+    };
+    if (!SHORT) {
+        const int64_t l = blockIdx.x, beg = off[l];
+        sort_list(l, beg, off[l + 1] - beg);
+        return;
+    }
+    const int64_t l0 = (int64_t)blockIdx.x * 64;
+    const int64_t mybeg = off[min(l0 + tid, nl)], mylen = off[min(l0 + tid + 1, nl)] - mybeg;
+    // up to 16 points: 16 lanes a list, four lists at a time, a point's place counted over the group
+    uint64_t todo = __ballot(mylen > 1 && mylen <= 16);
+    while (todo) {
+        int src[4]; // (uniform)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            src[u] = todo ? __ffsll((unsigned long long)todo) - 1 : -1;
+            todo &= todo - 1;
+        }
+        const int sub = tid >> 4, l16 = tid & 15;
+        const int from = sub == 0 ? src[0] : (sub == 1 ? src[1] : (sub == 2 ? src[2] : src[3]));
+        const int llen = __shfl((int)mylen, max(from, 0), 64), len = from >= 0 ? llen : 0;
+        const int64_t beg = ((int64_t)__shfl((int)(mybeg >> 32), max(from, 0), 64) << 32) |
+                            (uint32_t)__shfl((int)(uint32_t)mybeg, max(from, 0), 64);
+        const bool on = l16 < len;
+        const uint32_t id = on ? (uint32_t)ids[beg + l16] : 0xFFFFFFFFu;
+        const int next = __shfl_down((int)id, 1, 16);
+        const uint64_t falls = __ballot(l16 + 1 < len && (int)id > next);
+        if (!falls) continue;
+        int place = 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const uint32_t o = (uint32_t)__shfl((int)id, 16 * sub + j, 64);
+            place += o < id || (o == id && j < l16);
+        }
+        uint8_t *pg = pay + sub * 16 * (m + 1); // the group's codes and lambdas, as they were
+        if (on) {
+            for (int p = 0; p < m; ++p) pg[l16 * m + p] = codes[(beg + l16) * m + p];
+            pg[16 * m + l16] = lam[beg + l16];
+        }
+        wave_lds_order();
+        if (on && place != l16 && ((falls >> (16 * sub)) & 0xFFFFull)) { // (a list that is in order stays)
+            ids[beg + place] = (int32_t)id;
+            lam[beg + place] = pg[16 * m + l16];
+            for (int p = 0; p < m; ++p) codes[(beg + place) * m + p] = pg[l16 * m + p];
+        }
+        wave_lds_order();
+    }
+    for (uint64_t more = __ballot(mylen > 16); more; more &= more - 1) {
+        const int from = __ffsll((unsigned long long)more) - 1;
+        const int64_t beg = off[l0 + from];
+        sort_list(l0 + from, beg, off[l0 + from + 1] - beg);
+    }
 }
 void launch_list_sort(const int64_t *off, int64_t nl, int m, int32_t *ids, uint8_t *codes, uint8_t *lam,
-                      int32_t *long_lists, int32_t *n_long, int max_long, hipStream_t st)
+                      int64_t N, int32_t *long_lists, int32_t *n_long, int max_long, hipStream_t st)
 {
     if (nl <= 0) return;
     const size_t smem = (size_t)SORT_MAX * 8 + (size_t)SORT_MAX * (m + 1);
-    (void)hipFuncSetAttribute((const void *)k_list_sort, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    hipLaunchKernelGGL(k_list_sort, dim3((unsigned)nl), dim3(64), smem, st, off, nl, m, ids, codes, lam, long_lists,
-                       n_long, max_long);
+    auto go = [&](auto kern, unsigned grid) {
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64), smem, st, off, nl, m, ids, codes, lam, long_lists, n_long, max_long);
+    };
+    if (N <= LS_SHORT * nl)
+        go(k_list_sort<true>, (unsigned)((nl + 63) / 64));
+    else
+        go(k_list_sort<false>, (unsigned)nl);
 }
 
 // Second tier: the lists the 64-thread pass reported (more than SORT_MAX points), one
@@ -378,47 +437,80 @@ void launch_long_list_sort_at(int64_t beg, int64_t len, int m, int32_t *ids, uin
 // Summed in fp64 and rounded once.  One 64-thread workgroup per list: the edge length c is formed
 // by the whole wave, then lanes stride over the points, every lane walking the D coordinates of its
 // point (centroid rows come from L1/L2, the same for all lanes).
-__global__ __launch_bounds__(64) void k_list_static(const int64_t *__restrict__ off, int n, int D, int m,
-                                                    const float *__restrict__ C, const int32_t *__restrict__ S,
-                                                    const float *__restrict__ P, const float *__restrict__ mu,
-                                                    const uint8_t *__restrict__ codes,
-                                                    const uint8_t *__restrict__ lam, double lam_step, float lam_zero,
-                                                    float *__restrict__ sx)
+// LPL lanes a list: a wave for lists of many points; 16 lanes, four lists a wave, where lists are short (2 M points in
+// 524 288 lists: a wave each left 60 of 64 lanes idle: 3.34 -> 0.90 ms).  Sums in the same order either way: the squared
+// edge is added up as 64 lanes do it, a point's terms one after the other.
+template <int LPL>
+__global__ __launch_bounds__(256) void k_list_static(const int64_t *__restrict__ off, int64_t nl, int n, int D, int m,
+                                                     const float *__restrict__ C, const int32_t *__restrict__ S,
+                                                     const float *__restrict__ P, const float *__restrict__ mu,
+                                                     const uint8_t *__restrict__ codes,
+                                                     const uint8_t *__restrict__ lam, double lam_step, float lam_zero,
+                                                     int vec, float *__restrict__ sx)
 {
-    const int64_t l = blockIdx.x;
+    const int64_t l = (int64_t)blockIdx.x * (256 / LPL) + threadIdx.x / LPL;
+    const int lane = threadIdx.x % LPL;
+    if (l >= nl) return; // (whole groups of LPL lanes)
     const int64_t beg = off[l], end = off[l + 1];
     if (beg == end) return;
     const int i = (int)(l / n);
     const float *ci = C + (int64_t)i * D;
     const float *sj = C + (int64_t)S[l] * D;
-    double c = 0.0;
-    for (int d = threadIdx.x; d < D; d += 64) {
-        const double e = (double)sj[d] - (double)ci[d];
-        c = fma(e, e, c);
+    double part[64 / LPL]; // of the lanes lane, lane + LPL, .. of 64
+#pragma unroll
+    for (int u = 0; u < 64 / LPL; ++u) {
+        part[u] = 0.0;
+        for (int d = lane + LPL * u; d < D; d += 64) {
+            const double e = (double)sj[d] - (double)ci[d];
+            part[u] = fma(e, e, part[u]);
+        }
     }
-    c = wave_sum_f64(c);
+#pragma unroll
+    for (int o = 32 / LPL; o > 0; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < o; ++u) part[u] += part[u + o];
+    double c = part[0];
+#pragma unroll
+    for (int o = LPL / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
     const int ds = D / m;
-    for (int64_t t = beg + threadIdx.x; t < end; t += 64) {
+    for (int64_t t = beg + lane; t < end; t += LPL) {
         const double lh = ((double)lam[t] - (double)lam_zero) * lam_step;
         double q2n = 0.0, q12 = 0.0;
+        auto term = [&](float cf, float sf, float mf, float wf) {
+            const double cv = (double)cf, wv = (double)wf;
+            const double q1 = (cv - (double)mf) + lh * ((double)sf - cv);
+            q2n = fma(wv, wv, q2n);
+            q12 = fma(q1, wv, q12);
+        };
         for (int p = 0; p < m; ++p) {
             const float *w = P + ((int64_t)p * 256 + codes[t * m + p]) * ds;
-            for (int d = 0; d < ds; ++d) {
-                const int g = p * ds + d;
-                const double cv = (double)ci[g], wv = (double)w[d];
-                const double q1 = (cv - (double)mu[g]) + lh * ((double)sj[g] - cv);
-                q2n = fma(wv, wv, q2n);
-                q12 = fma(q1, wv, q12);
+            if (vec) { // ds a multiple of four, rows on 16 bytes
+#pragma unroll 4
+                for (int d = 0; d < ds; d += 4) {
+                    const int g = p * ds + d;
+                    const f32x4 c4 = *(const f32x4 *)(ci + g), s4 = *(const f32x4 *)(sj + g), m4 = *(const f32x4 *)(mu + g);
+                    const f32x4 w4 = *(const f32x4 *)(w + d);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) term(c4[e], s4[e], m4[e], w4[e]);
+                }
+            } else {
+                for (int d = 0; d < ds; ++d) term(ci[p * ds + d], sj[p * ds + d], mu[p * ds + d], w[d]);
             }
         }
         sx[t] = (float)(q2n + 2.0 * q12 + (lh * lh - lh) * c);
     }
 }
+
 void launch_list_static(const int64_t *off, int64_t nl, int n, int D, int m, const float *C, const int32_t *S,
                         const float *P, const float *mu, const uint8_t *codes, const uint8_t *lam, double lam_step,
-                        float lam_zero, float *sx, hipStream_t st)
+                        float lam_zero, int64_t N, float *sx, hipStream_t st)
 {
     if (nl <= 0) return;
-    hipLaunchKernelGGL(k_list_static, dim3((unsigned)nl), dim3(64), 0, st, off, n, D, m, C, S, P, mu, codes, lam,
-                       lam_step, lam_zero, sx);
+    const int vec = (D / m) % 4 == 0 && (((uintptr_t)C | (uintptr_t)P | (uintptr_t)mu) % 16) == 0;
+    if (N <= LS_SHORT * nl)
+        hipLaunchKernelGGL(k_list_static<16>, dim3((unsigned)((nl + 15) / 16)), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu,
+                           codes, lam, lam_step, lam_zero, vec, sx);
+    else
+        hipLaunchKernelGGL(k_list_static<64>, dim3((unsigned)((nl + 3) / 4)), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu,
+                           codes, lam, lam_step, lam_zero, vec, sx);
 }
