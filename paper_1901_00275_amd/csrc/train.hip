@@ -7,7 +7,7 @@
 // order in which the atomics land: x is scaled by 2^shift / s, s = the smallest power of two
 // >= max |x| over the sample, shift = 62 - ceil(log2(points)); the sum of all members cannot
 // overflow and the resolution is s * 2^-shift (2^-38 s for 16 M points).
-#include "common.h"
+#include "codeword.h"
 
 // One atomic per workgroup at most, and only if the workgroup has something larger to report than what is
 // there already: an atomic per wave on the one address took 0.20 ms for a sample of 16 MB.
@@ -223,6 +223,118 @@ __global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restric
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) out[i] = img[i];
 }
 
+// The same iteration for up to 256 centroids with the nearest one from the matrix cores (codeword.h), 64 vectors a
+// wave.  262 144 x 16 against 256 centroids: 73 us with the lanes' walk over the centroids, 46 so (66 with
+// the centroids read from their rows): the products 14, the rest loads and the LDS additions of the sums.
+#define LLOYD_CT 272 // floats a component: the four that a wave reads at once start 16 banks apart
+template <int DS>
+__global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__restrict__ X, int64_t nt, int k,
+                                                             const float *__restrict__ C,
+                                                             const uint32_t *__restrict__ absmax_bits, int shift, int want_sums,
+                                                             int vec, unsigned long long *__restrict__ part,
+                                                             int32_t *__restrict__ assign)
+{
+    extern __shared__ unsigned long long img[]; // [k][DS + 1]
+    __shared__ __align__(16) float half[256];
+    __shared__ float ct[DS * LLOYD_CT]; // the centroids component by component
+    __shared__ float mu[DS];
+    __shared__ int sh_cmax;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) img[i] = 0;
+    if (tid == 0) sh_cmax = 0;
+    __syncthreads();
+    if (tid < 256) {
+#pragma unroll
+        for (int d = 0; d < DS; ++d) ct[d * LLOYD_CT + tid] = tid < k ? C[(int64_t)tid * DS + d] : 0.f;
+    }
+    __syncthreads();
+    for (int d = wave; d < DS; d += LLOYD_NT / 64) { // the point: the mean of the finite values (any point would do)
+        float s = 0.f;
+        for (int t = lane; t < 256; t += 64) {
+            const float v = ct[d * LLOYD_CT + t];
+            s += fabsf(v) < INFINITY ? v : 0.f;
+        }
+        s = wave_sum(s) / (float)k;
+        if (lane == 0) mu[d] = fabsf(s) < INFINITY ? s : 0.f;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        float h = 0.f;
+        bool there = tid < k; // (a centroid with a component that is not finite is nobody's nearest)
+#pragma unroll
+        for (int d = 0; d < DS; ++d) {
+            const float c = ct[d * LLOYD_CT + tid], v = c - mu[d];
+            there = there && fabsf(c) < INFINITY;
+            h = fmaf(v, v, h);
+        }
+        half[tid] = there ? 0.5f * h : CODEWORD_NONE;
+        if (there) atomicMax(&sh_cmax, (int)__float_as_uint(h < INFINITY ? sqrtf(h) : INFINITY));
+        if (!there)
+#pragma unroll
+            for (int d = 0; d < DS; ++d) ct[d * LLOYD_CT + tid] = mu[d]; // (at the largest "norm", and never the nearest)
+    }
+    __syncthreads();
+    const float cmax = __uint_as_float((uint32_t)sh_cmax);
+    const double f = ldexp(1.0, shift) / scale_of(*absmax_bits);
+    const int64_t stride = (int64_t)gridDim.x * LLOYD_NT;
+    for (int64_t row0 = (int64_t)blockIdx.x * LLOYD_NT + wave * 64; row0 < nt; row0 += stride) {
+        auto row_of = [&](int v) { return X + min(row0 + v, nt - 1) * DS; };
+        auto exact = [&](int v, int t) {
+            float r[DS], w[DS];
+            if (!(half[t] < CODEWORD_NONE)) return INFINITY;
+            load_row<DS>(row_of(v), vec, r);
+#pragma unroll
+            for (int d = 0; d < DS; ++d) w[d] = ct[d * LLOYD_CT + t];
+            return lloyd_dist<DS>(r, w);
+        };
+        auto all = [&](int v) {
+            uint64_t key = KEY_MAX;
+            for (int t = lane; t < k; t += 64) {
+                const float s = exact(v, t);
+                const uint64_t tk = make_key(s, (uint32_t)t);
+                if (s < INFINITY && tk < key) key = tk;
+            }
+            key = wave_min_u64(key);
+            return key == KEY_MAX ? 0 : (int)(uint32_t)key;
+        };
+        auto walk = [&]() {
+            float r[DS], best = INFINITY;
+            load_row<DS>(row_of(lane), vec, r);
+            int b = 0;
+            for (int t = 0; t < k; ++t) {
+                float w[DS];
+#pragma unroll
+                for (int d = 0; d < DS; ++d) w[d] = ct[d * LLOYD_CT + t];
+                const float s = half[t] < CODEWORD_NONE ? lloyd_dist<DS>(r, w) : INFINITY;
+                if (s < best) {
+                    best = s;
+                    b = t;
+                }
+            }
+            return b;
+        };
+        const int bt = nearest_codeword64<DS>(ct, LLOYD_CT, k, half, cmax, lane, [&](int d) { return mu[d]; },
+                                              [&](int v, int d) { return row_of(v)[d]; }, exact, all, walk);
+        const int64_t row = row0 + lane;
+        if (row < nt) {
+            unsigned long long *row_img = img + bt * (DS + 1);
+            if (want_sums) {
+                float r[DS];
+                load_row<DS>(X + row * DS, vec, r);
+#pragma unroll
+                for (int d = 0; d < DS; ++d)
+                    if (__float_as_uint(r[d]) << 1 < 0xFF000000u) // finite
+                        atomicAdd(&row_img[d], (unsigned long long)llrint((double)r[d] * f));
+            }
+            atomicAdd(&row_img[DS], 1ull);
+            if (assign) assign[row] = bt;
+        }
+    }
+    __syncthreads();
+    unsigned long long *out = part + (int64_t)blockIdx.x * k * (DS + 1);
+    for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) out[i] = img[i];
+}
+
 // One workgroup per centroid: the D sums and the count over all images; with C the centroid moves to
 // the mean of its members (one without members stays), with counts the number of members is written.
 __global__ __launch_bounds__(256) void k_lloyd_reduce(const unsigned long long *__restrict__ part, int blocks, int k,
@@ -286,12 +398,16 @@ void launch_lloyd_lanes(const float *X, int64_t nt, int D, int k, float *C, cons
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(LLOYD_NT), lds, st, X, nt, k, (const float *)C, absmax_bits,
                            shift, update ? 1 : 0, vec, (unsigned long long *)part, assign);
     };
+    // The products' fixed cost (norms, direct distances of four centroids a vector) against the walk, ten iterations of
+    // 262 144 vectors, us: D = 16, k = 256 780 and 1 112; D = 6, k = 256 599 and 1 129; D = 4, k = 256 459 and 470; D = 8, k = 64
+    // 390 and 341; D = 12, k = 40 434 and 376.
+    const bool cores = k <= 256 && k * D >= 1536;
     switch (D) {
     case 4: go(k_lloyd_lanes<4>); break;
-    case 6: go(k_lloyd_lanes<6>); break;
-    case 8: go(k_lloyd_lanes<8>); break;
-    case 12: go(k_lloyd_lanes<12>); break;
-    default: go(k_lloyd_lanes<16>); break;
+    case 6: cores ? go(k_lloyd_cores<6>) : go(k_lloyd_lanes<6>); break;
+    case 8: cores ? go(k_lloyd_cores<8>) : go(k_lloyd_lanes<8>); break;
+    case 12: cores ? go(k_lloyd_cores<12>) : go(k_lloyd_lanes<12>); break;
+    default: cores ? go(k_lloyd_cores<16>) : go(k_lloyd_lanes<16>); break;
     }
     if (update || counts)
         hipLaunchKernelGGL(k_lloyd_reduce, dim3((unsigned)k), dim3(256), 0, st, (const unsigned long long *)part, blocks, k,
