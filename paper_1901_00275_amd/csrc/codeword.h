@@ -37,7 +37,9 @@ __device__ __forceinline__ void load_row(const float *w, bool vec, float (&r)[DS
     }
 }
 
-// half[256]: ||W_t||^2 / 2 of the codewords, CODEWORD_NONE beyond k; cmax: largest norm, infinite where one is not finite.
+// half[256]: ||W_t||^2 / 2 of the codewords, CODEWORD_NONE for those that do not count (beyond k, or with a component that
+// is not finite); cmax: largest norm of the others, infinite where a squared norm overflows.  Then the products say nothing
+// (the direct distances to such a codeword may be finite all the same), and every vector is compared directly.
 #define CODEWORD_NONE 3e38f
 #define CODEWORD_OPEN 12
 // Wt: the codewords component by component, `stride` floats a component, 16 ceil(k / 16) of them readable (codeword by
@@ -49,6 +51,7 @@ template <int DS, typename Mu, typename X, typename Exact, typename All, typenam
 __device__ __forceinline__ int nearest_codeword64(const float *Wt, int stride, int k, const float *half, float cmax, int lane, Mu mu, X x,
                                                   Exact exact, All all, Walk walk)
 {
+    if (!(cmax < INFINITY)) return walk();
     constexpr int KS = (DS + 3) / 4, NB = 4; // blocks of 16 vectors
     const int col = lane & 15, grp = lane >> 4;
     float xb[NB][KS], b1[NB], b2[NB], band[NB];

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
             there = there && fabsf(c) < INFINITY;
             h = fmaf(v, v, h);
         }
-        half[tid] = there ? 0.5f * h : CODEWORD_NONE;
+        half[tid] = there ? 0.5f * h : CODEWORD_NONE; // (the half of a finite sum of squares is smaller, an overflowed one infinite)
         if (there) atomicMax(&sh_cmax, (int)__float_as_uint(h < INFINITY ? sqrtf(h) : INFINITY));
         if (!there)
 #pragma unroll
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
         auto row_of = [&](int v) { return X + min(row0 + v, nt - 1) * DS; };
         auto exact = [&](int v, int t) {
             float r[DS], w[DS];
-            if (!(half[t] < CODEWORD_NONE)) return INFINITY;
+            if (half[t] == CODEWORD_NONE) return INFINITY;
             load_row<DS>(row_of(v), vec, r);
 #pragma unroll
             for (int d = 0; d < DS; ++d) w[d] = ct[d * LLOYD_CT + t];
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
                 float w[DS];
 #pragma unroll
                 for (int d = 0; d < DS; ++d) w[d] = ct[d * LLOYD_CT + t];
-                const float s = half[t] < CODEWORD_NONE ? lloyd_dist<DS>(r, w) : INFINITY;
+                const float s = half[t] != CODEWORD_NONE ? lloyd_dist<DS>(r, w) : INFINITY;
                 if (s < best) {
                     best = s;
                     b = t;

@@ -50,3 +50,57 @@ def test_assignment(D, nt, k, kind):
         if kind == "same":
             assert np.array_equal(a[s:s + 4096][first], d.argmin(1)[first])
         assert (a[s:s + 4096][~fine] == 0).all()
+
+
+def direct(X, C):
+    """The direct distances in fp32, operation by operation (a product of two fp32 numbers is exact in fp64)."""
+    f32, D = np.float32, X.shape[1]
+    with np.errstate(over="ignore", invalid="ignore"):
+        t = (X[:, None] - C[None]).astype(np.float64)
+        q = 4 if D % 4 == 0 else 1
+        v = []
+        for p in range(0, D, q):
+            acc = np.zeros(t.shape[:2], f32)
+            for d in range(p, p + q):
+                acc = (t[..., d] * t[..., d] + acc).astype(f32)
+            v.append(acc)
+        s = v[0] + v[1]
+        for i in range(2, len(v), 2):
+            s = s + (v[i] + v[i + 1] if i + 1 < len(v) else v[i])
+    return s
+
+
+def nearest(X, C):
+    """The first centroid at the smallest direct distance; 0 where none is at a finite one."""
+    a = []
+    for s in range(0, len(X), 512):
+        d = direct(X[s:s + 512], C)
+        d[~np.isfinite(d)] = np.inf
+        a.append(np.where(np.isfinite(d.min(1)), d.argmin(1), 0))
+    return np.concatenate(a)
+
+
+def assigned(X, C):
+    import paper_1901_00275_amd as vlq
+
+    nt, D = X.shape
+    a = torch.empty(nt, dtype=torch.int32, device=DEV)
+    vlq.vlq_kmeans(torch.as_tensor(X).to(DEV), nt, D, len(C), 0, torch.as_tensor(C).to(DEV), a, None)
+    return a.cpu().numpy()
+
+
+@pytest.mark.parametrize("D,k", [(6, 256), (8, 256), (12, 200), (16, 256), (16, 97)])
+@pytest.mark.parametrize("kind", ["1e20", "1e23", "1e38", "beside"])
+def test_norms_that_overflow(D, k, kind):
+    """Finite centroids whose squared norms overflow fp32, and vectors beside one of them."""
+    rng = np.random.default_rng(D + k)
+    C, X = rng.normal(size=(k, D)), rng.normal(size=(2100, D)) * 1.2
+    if kind == "beside":
+        C[k // 3] = 3e19
+        X[::7] = 3e19 * (1 + 1e-3 * rng.normal(size=X[::7].shape))
+    else:
+        C[k // 3, 1] = float(kind)
+    C, X = C.astype(np.float32), X.astype(np.float32)
+    want = nearest(X, C)
+    assert len(np.unique(want)) > k // 2 and (kind != "beside" or (want[::7] == k // 3).all())
+    assert np.array_equal(assigned(X, C), want)
