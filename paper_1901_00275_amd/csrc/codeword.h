@@ -17,8 +17,12 @@
 // How far the second smallest value has to lie above the smallest, in halves of squared distances, for a vector of norm x
 // and codewords of norms up to c: twice the error of a value (DS + 2 roundings of at most c^2 / 2 + x c, and the norm's
 // own DS of c^2 / 2), what the direct distances (DS + 1 roundings of (x + c)^2 each) can differ by, and the rounding of the
-// differences (one of (x + c)^2 in each value).
-__device__ __forceinline__ float codeword_band(int ds, float x, float c) { return 4.f * (float)(ds + 8) * 0x1p-24f * (x + c) * (x + c); }
+// differences (one of (x + c)^2 in each value).  Below the normal range roundings are no longer relative to the values: up to
+// 2^-126 an operation, where the matrix cores flush, times the 2 (3 DS + 4) operations of two values and two distances.
+__device__ __forceinline__ float codeword_band(int ds, float x, float c)
+{
+    return 4.f * (float)(ds + 8) * 0x1p-24f * (x + c) * (x + c) + 0x1p-119f;
+}
 
 // a row of DS floats, in 16-byte pieces where `vec` says that it lies on 16 bytes
 template <int DS>

@@ -104,3 +104,12 @@ def test_norms_that_overflow(D, k, kind):
     want = nearest(X, C)
     assert len(np.unique(want)) > k // 2 and (kind != "beside" or (want[::7] == k // 3).all())
     assert np.array_equal(assigned(X, C), want)
+
+
+@pytest.mark.parametrize("D,k", [(6, 256), (8, 200), (12, 200), (16, 256)])
+@pytest.mark.parametrize("scale", [2.0 ** -72, 2.0 ** -68, 2.0 ** -64, 2.0 ** -61, 2.0 ** -57])
+def test_squares_below_the_normal_range(D, k, scale):
+    """Squared distances that fp32 holds with a few bits only: roundings no longer relative to the values."""
+    rng = np.random.default_rng(D + k)
+    C, X = (rng.normal(size=(k, D)) * scale).astype(np.float32), (rng.normal(size=(4100, D)) * 1.2 * scale).astype(np.float32)
+    assert np.array_equal(assigned(X, C), nearest(X, C))
