@@ -14,13 +14,19 @@
 // Vectors and codewords are taken relative to a point among the codewords (`mu`; each difference is rounded once, relative to
 // itself), so that the error does not grow with their distance from the origin.
 //
-// How far the second smallest value has to lie above the smallest, in halves of squared distances, for a vector of norm x
-// and codewords of norms up to c: twice the error of a value (DS + 2 roundings of at most c^2 / 2 + x c, and the norm's
-// own DS of c^2 / 2), what the direct distances (DS + 1 roundings of (x + c)^2 each) can differ by, and the rounding of the
-// differences (one of (x + c)^2 in each value).  Below the normal range roundings are no longer relative to the values: up to
-// 2^-126 an operation, where the matrix cores flush, times the 2 (3 DS + 4) operations of two values and two distances.
-__device__ __forceinline__ float codeword_band(int ds, float x, float c)
+// How far the second smallest value has to lie above the smallest, v, in halves of squared distances, for a vector of squared
+// norm xn = x^2 and codewords of norms up to c: twice the error of a value (DS + 2 roundings of at most c^2 / 2 + x c, and
+// the norm's own DS of c^2 / 2), what the direct distances (DS + 1 roundings of (x + c)^2 each) can differ by, and the
+// rounding of the differences (one of (x + c)^2 in each value).  Below the normal range roundings are no longer relative to
+// the values: up to 2^-126 an operation, where the matrix cores flush, times the 2 (3 DS + 4) operations of two values and
+// two distances.
+// c is the largest norm that matters, not the largest there is (with that, one codeword at 30 times the usual norm left 9 % of
+// the vectors undecided, at 100 times 64 %): d being the distance of v's codeword, its norm is at most x + d, and
+// s = x + sqrt(2 v + x^2) differs from that by the root of v's error, 4e-3 s at most.  A codeword beyond 1.1 s is 0.09 s
+// farther from the vector than d: it is not the nearest, whatever its value.
+__device__ __forceinline__ float codeword_band(int ds, float xn, float v, float cmax)
 {
+    const float x = sqrtf(xn), s = x + sqrtf(fmaxf(fmaf(2.f, v, xn), 0.f)), c = fminf(cmax, 1.1f * s);
     return 4.f * (float)(ds + 8) * 0x1p-24f * (x + c) * (x + c) + 0x1p-119f;
 }
 
@@ -58,7 +64,7 @@ __device__ __forceinline__ int nearest_codeword64(const float *Wt, int stride, i
     if (!(cmax < INFINITY)) return walk();
     constexpr int KS = (DS + 3) / 4, NB = 4; // blocks of 16 vectors
     const int col = lane & 15, grp = lane >> 4;
-    float xb[NB][KS], b1[NB], b2[NB], band[NB];
+    float xb[NB][KS], b1[NB], b2[NB], xs[NB];
     int four[NB];
     float ms[KS];
 #pragma unroll
@@ -75,7 +81,7 @@ __device__ __forceinline__ int nearest_codeword64(const float *Wt, int stride, i
         }
         xn += __shfl_xor(xn, 16, 64);
         xn += __shfl_xor(xn, 32, 64);
-        band[i] = codeword_band(DS, sqrtf(xn), cmax);
+        xs[i] = xn;
         b1[i] = b2[i] = INFINITY;
         four[i] = 0;
     }
@@ -121,7 +127,7 @@ __device__ __forceinline__ int nearest_codeword64(const float *Wt, int stride, i
             at = p1 < b1[i] ? pa : at;
             b1[i] = fminf(b1[i], p1);
         }
-        const bool clear = b2[i] - b1[i] > band[i]; // (false for values that are not numbers)
+        const bool clear = b2[i] - b1[i] > codeword_band(DS, xs[i], b1[i], cmax); // (false for values that are not numbers)
         // (where two are equal the lanes may name different fours, but then it is not clear)
         const int t = 4 * at + grp;
         const float d = exact(16 * i + col, min(t, k - 1));

@@ -248,14 +248,35 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
         for (int d = 0; d < DS; ++d) ct[d * LLOYD_CT + tid] = tid < k ? C[(int64_t)tid * DS + d] : 0.f;
     }
     __syncthreads();
-    for (int d = wave; d < DS; d += LLOYD_NT / 64) { // the point: the mean of the finite values (any point would do)
-        float s = 0.f;
-        for (int t = lane; t < 256; t += 64) {
-            const float v = ct[d * LLOYD_CT + t];
-            s += fabsf(v) < INFINITY ? v : 0.f;
+    // The point: component by component a value with three to five eighths of the centroids below it.  (The mean would do as
+    // well, but for a centroid far from the others, which takes it along.)
+    for (int d = wave; d < DS; d += LLOYD_NT / 64) {
+        uint32_t o[4], lo = 0xFFFFFFFFu, hi = 0;
+        int there = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float v = ct[d * LLOYD_CT + lane + 64 * j];
+            const bool in = lane + 64 * j < k && fabsf(v) < INFINITY;
+            there += __popcll(__ballot(in));
+            o[j] = in ? f2ord(v) : 0xFFFFFFFFu;
+            lo = min(lo, o[j]);
+            hi = max(hi, in ? o[j] : 0u);
         }
-        s = wave_sum(s) / (float)k;
-        if (lane == 0) mu[d] = fabsf(s) < INFINITY ? s : 0.f;
+        lo = wave_min_u32(lo);
+        hi = wave_max_u32(hi);
+        while (lo < hi) {
+            const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+            int below = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) below += __popcll(__ballot(o[j] < mid));
+            if (8 * below > 5 * there) {
+                hi = mid - 1;
+                continue;
+            }
+            lo = mid;
+            if (8 * below >= 3 * there) break;
+        }
+        if (lane == 0) mu[d] = there ? ord2f(lo) : 0.f;
     }
     __syncthreads();
     if (tid < 256) {

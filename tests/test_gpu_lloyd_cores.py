@@ -113,3 +113,49 @@ def test_squares_below_the_normal_range(D, k, scale):
     rng = np.random.default_rng(D + k)
     C, X = (rng.normal(size=(k, D)) * scale).astype(np.float32), (rng.normal(size=(4100, D)) * 1.2 * scale).astype(np.float32)
     assert np.array_equal(assigned(X, C), nearest(X, C))
+
+
+@pytest.mark.parametrize("D,k", [(6, 256), (8, 200), (12, 200), (16, 256), (16, 96)])
+@pytest.mark.parametrize("far,times", [(1, 30.0), (1, 100.0), (1, 1e6), (1, 1e15), (30, 100.0), (200, 1e4), (3, -1.0)])
+def test_far_centroids(D, k, far, times):
+    """Centroids far from the others (times -1: all else in one point), and vectors near them, between and beyond."""
+    rng = np.random.default_rng(D + k + far)
+    C, X = rng.normal(size=(k, D)), rng.normal(size=(4100, D)) * 1.2
+    if times < 0:
+        C[far:] = C[k - 1] + 1e-3 * rng.normal(size=C[far:].shape)
+    else:
+        C[: min(far, k // 2)] *= times
+    near = rng.integers(0, max(1, min(far, k // 2)), 600)
+    X[:200] = C[near[:200]] * (1 + 1e-3 * rng.normal(size=(200, D)))
+    X[200:400] = C[near[200:400]] * rng.uniform(0.45, 0.55, (200, 1))
+    X[400:600] = C[near[400:600]] * rng.uniform(1, 3, (200, 1))
+    C, X = C.astype(np.float32), X.astype(np.float32)
+    assert np.array_equal(assigned(X, C), nearest(X, C))
+
+
+def test_a_far_centroid_costs_nothing():
+    """One centroid at 30 to 10^15 times the norm of the others: not every vector is compared with all centroids."""
+    import paper_1901_00275_amd as vlq
+
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    X = torch.randn(262_144, 16, generator=g, device=DEV)
+    base, a = X[:256].contiguous(), torch.empty(262_144, dtype=torch.int32, device=DEV)
+
+    def time_of(C):
+        best = np.inf
+        for _ in range(8):
+            s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            s.record()
+            vlq.vlq_kmeans(X, 262_144, 16, 256, 0, C, a, None)
+            e.record()
+            e.synchronize()
+            best = min(best, s.elapsed_time(e))
+        return best
+
+    plain = time_of(base)
+    for times in (30.0, 100.0, 1e6, 1e15):
+        C = base.clone()
+        C[77] *= times
+        assert time_of(C) < 1.25 * plain, times
