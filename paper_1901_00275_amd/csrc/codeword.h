@@ -49,9 +49,14 @@ __device__ __forceinline__ void load_row(const float *w, bool vec, float (&r)[DS
 
 // half[256]: ||W_t||^2 / 2 of the codewords, CODEWORD_NONE for those that do not count (beyond k, or with a component that
 // is not finite); cmax: largest norm of the others, infinite where a squared norm overflows.  Then the products say nothing
-// (the direct distances to such a codeword may be finite all the same), and every vector is compared directly.
+// (the direct distances to such a codeword may be finite all the same), and nor do they where all coincide or their squares
+// are below the normal range: every vector is compared directly.
 #define CODEWORD_NONE 3e38f
-#define CODEWORD_OPEN 12
+// Undecided vectors of a wave up to which they are compared one by one, all lanes a vector, instead of every lane walking all
+// codewords.  One pass over 262 144 vectors, k = 256, at 12 / 24 / 36 / 50, us: D = 16, whole-number vectors 134 / 125 / 121 /
+// 124, a sixteenth of the codewords there twice 141 / 124 / 124 / 125, groups of eight close codewords 161 / 161 / 161 / 192;
+// D = 8, those groups 135 / 136 / 157 / 169.
+#define CODEWORD_OPEN 24
 // Wt: the codewords component by component, `stride` floats a component, 16 ceil(k / 16) of them readable (codeword by
 // codeword a wave's load touched 64 places, and those loads took three times as long as the products).
 // mu(d): component d of the point.  x(v, d): component d of the wave's vector v (0 .. 63).  exact(v, t): direct distance of vector v to codeword t, by any lane.
@@ -61,7 +66,7 @@ template <int DS, typename Mu, typename X, typename Exact, typename All, typenam
 __device__ __forceinline__ int nearest_codeword64(const float *Wt, int stride, int k, const float *half, float cmax, int lane, Mu mu, X x,
                                                   Exact exact, All all, Walk walk)
 {
-    if (!(cmax < INFINITY)) return walk();
+    if (!(cmax < INFINITY && cmax > 0x1p-50f)) return walk();
     constexpr int KS = (DS + 3) / 4, NB = 4; // blocks of 16 vectors
     const int col = lane & 15, grp = lane >> 4;
     float xb[NB][KS], b1[NB], b2[NB], xs[NB];

@@ -139,6 +139,49 @@ __device__ __forceinline__ float lloyd_dist(const float (&r)[DS], const float *w
     return s;
 }
 
+// the nearest of k centroids to the lane's vector, the first of equal ones; 0 where no distance is finite
+template <int DS>
+__device__ __forceinline__ int walk_centroids(const float *C, int k, const float (&r)[DS])
+{
+    // never written while the kernel runs: the constant address space takes the scalar path
+    const cfloat *w = (const cfloat *)(uintptr_t)C;
+    constexpr int CB = DS >= 12 ? 2 : (DS >= 6 ? 4 : 8); // centroids per batch of uniform loads
+    float best = INFINITY;
+    int bt = 0;
+    float wc[CB * DS], wn[CB * DS];
+    const int kb = k - k % CB;
+    if (kb > 0) {
+#pragma unroll
+        for (int i = 0; i < CB * DS; ++i) wc[i] = w[i];
+    }
+    for (int t = 0; t < kb; t += CB) {
+        const int tn = t + CB < kb ? t + CB : t;
+#pragma unroll
+        for (int i = 0; i < CB * DS; ++i) wn[i] = w[tn * DS + i];
+#pragma unroll
+        for (int u = 0; u < CB; ++u) {
+            const float s = lloyd_dist<DS>(r, wc + u * DS);
+            if (s < best) {
+                best = s;
+                bt = t + u;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < CB * DS; ++i) wc[i] = wn[i];
+    }
+    for (int t = kb; t < k; ++t) {
+        float wt[DS];
+#pragma unroll
+        for (int d = 0; d < DS; ++d) wt[d] = w[t * DS + d];
+        const float s = lloyd_dist<DS>(r, wt);
+        if (s < best) {
+            best = s;
+            bt = t;
+        }
+    }
+    return bt;
+}
+
 template <int DS>
 __global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restrict__ X, int64_t nt, int k,
                                                           const float *__restrict__ C,
@@ -151,9 +194,6 @@ __global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restric
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) img[i] = 0;
     __syncthreads();
     const double f = ldexp(1.0, shift) / scale_of(*absmax_bits);
-    // never written while the kernel runs: the constant address space takes the scalar path
-    const cfloat *w = (const cfloat *)(uintptr_t)C;
-    constexpr int CB = DS >= 12 ? 2 : (DS >= 6 ? 4 : 8); // centroids per batch of uniform loads
     const int64_t stride = (int64_t)gridDim.x * LLOYD_NT;
     for (int64_t base = (int64_t)blockIdx.x * LLOYD_NT; base < nt; base += stride) { // (uniform trip count)
         const int64_t row = base + tid;
@@ -173,39 +213,7 @@ __global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restric
 #pragma unroll
             for (int d = 0; d < DS; ++d) r[d] = x[d];
         }
-        float best = INFINITY;
-        int bt = 0;
-        float wc[CB * DS], wn[CB * DS];
-        const int kb = k - k % CB;
-        if (kb > 0) {
-#pragma unroll
-            for (int i = 0; i < CB * DS; ++i) wc[i] = w[i];
-        }
-        for (int t = 0; t < kb; t += CB) {
-            const int tn = t + CB < kb ? t + CB : t;
-#pragma unroll
-            for (int i = 0; i < CB * DS; ++i) wn[i] = w[tn * DS + i];
-#pragma unroll
-            for (int u = 0; u < CB; ++u) {
-                const float s = lloyd_dist<DS>(r, wc + u * DS);
-                if (s < best) {
-                    best = s;
-                    bt = t + u;
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < CB * DS; ++i) wc[i] = wn[i];
-        }
-        for (int t = kb; t < k; ++t) {
-            float wt[DS];
-#pragma unroll
-            for (int d = 0; d < DS; ++d) wt[d] = w[t * DS + d];
-            const float s = lloyd_dist<DS>(r, wt);
-            if (s < best) {
-                best = s;
-                bt = t;
-            }
-        }
+        const int bt = walk_centroids<DS>(C, k, r);
         if (live) {
             unsigned long long *row_img = img + bt * (DS + 1);
             if (want_sums) {
@@ -319,20 +327,9 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
             return key == KEY_MAX ? 0 : (int)(uint32_t)key;
         };
         auto walk = [&]() {
-            float r[DS], best = INFINITY;
+            float r[DS];
             load_row<DS>(row_of(lane), vec, r);
-            int b = 0;
-            for (int t = 0; t < k; ++t) {
-                float w[DS];
-#pragma unroll
-                for (int d = 0; d < DS; ++d) w[d] = ct[d * LLOYD_CT + t];
-                const float s = half[t] != CODEWORD_NONE ? lloyd_dist<DS>(r, w) : INFINITY;
-                if (s < best) {
-                    best = s;
-                    b = t;
-                }
-            }
-            return b;
+            return walk_centroids<DS>(C, k, r);
         };
         const int bt = nearest_codeword64<DS>(ct, LLOYD_CT, k, half, cmax, lane, [&](int d) { return mu[d]; },
                                               [&](int v, int d) { return row_of(v)[d]; }, exact, all, walk);

@@ -133,29 +133,45 @@ def test_far_centroids(D, k, far, times):
     assert np.array_equal(assigned(X, C), nearest(X, C))
 
 
-def test_a_far_centroid_costs_nothing():
-    """One centroid at 30 to 10^15 times the norm of the others: not every vector is compared with all centroids."""
+def time_of(X, C):
     import paper_1901_00275_amd as vlq
 
+    best, a = np.inf, torch.empty(len(X), dtype=torch.int32, device=DEV)
+    for _ in range(8):
+        s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        s.record()
+        vlq.vlq_kmeans(X, len(X), X.shape[1], len(C), 0, C, a, None)
+        e.record()
+        e.synchronize()
+        best = min(best, s.elapsed_time(e))
+    return best
+
+
+def vectors():
     g = torch.Generator(device=DEV)
     g.manual_seed(1)
-    X = torch.randn(262_144, 16, generator=g, device=DEV)
-    base, a = X[:256].contiguous(), torch.empty(262_144, dtype=torch.int32, device=DEV)
+    return torch.randn(262_144, 16, generator=g, device=DEV)
 
-    def time_of(C):
-        best = np.inf
-        for _ in range(8):
-            s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            torch.cuda.synchronize()
-            s.record()
-            vlq.vlq_kmeans(X, 262_144, 16, 256, 0, C, a, None)
-            e.record()
-            e.synchronize()
-            best = min(best, s.elapsed_time(e))
-        return best
 
-    plain = time_of(base)
+def test_a_far_centroid_costs_nothing():
+    """One centroid at 30 to 10^15 times the norm of the others: not every vector is compared with all centroids."""
+    X = vectors()
+    base = X[:256].clone()
+    plain = time_of(X, base)
     for times in (30.0, 100.0, 1e6, 1e15):
         C = base.clone()
         C[77] *= times
-        assert time_of(C) < 1.25 * plain, times
+        assert time_of(X, C) < 1.25 * plain, times
+
+
+@pytest.mark.parametrize("kind", ["overflow", "coinciding"])
+def test_codebooks_without_use_for_the_products(kind):
+    """A centroid whose norm overflows, and one centroid 256 times: no slower than the walk alone, which takes 264 centroids."""
+    X = vectors()
+    C = X[:256].clone()
+    if kind == "overflow":
+        C[3] = 1e21
+    else:
+        C[:] = X[0]
+    assert time_of(X, C) < 1.2 * time_of(X, X[:264].clone())
