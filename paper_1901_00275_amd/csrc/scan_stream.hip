@@ -153,6 +153,11 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
         __builtin_amdgcn_wave_barrier();
     };
 
+    // The distance a key below the bound has at most.  Bounds go one past the keys they are found from: behind infinite
+    // distances that would be the pattern of a NaN, to which no distance compares.
+    auto distance_bound = [](uint64_t bound) {
+        return bound >= 0xFF80000000000000ull ? INFINITY : ord2f((uint32_t)(bound >> 32));
+    };
     uint64_t thr = KEY_MAX;
     float thr_f = INFINITY;
     // one chunk of 64 points: m table reads per point, the distance, and the candidates that pass
@@ -179,7 +184,7 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
             if (np && wcnt + np > wlimit) {
                 prune();
                 thr = sh_thr;
-                thr_f = thr == KEY_MAX ? INFINITY : ord2f((uint32_t)(thr >> 32));
+                thr_f = distance_bound(thr);
                 pass = pass && key < thr;
                 mask = __ballot(pass);
                 np = __popcll(mask);
@@ -214,7 +219,7 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
 #pragma unroll
             for (int i = 0; i < SS_GL; ++i) ends[i] = __builtin_amdgcn_readlane(end, i);
             thr = sh_thr;
-            thr_f = thr == KEY_MAX ? INFINITY : ord2f((uint32_t)(thr >> 32));
+            thr_f = distance_bound(thr);
             for (int base = 0; base < total; base += 64 * SS_PCH) {
                 uint32_t cw[SS_PCH][M / 4];
                 uint32_t lb[SS_PCH], gp[SS_PCH];
@@ -267,7 +272,7 @@ __global__ __launch_bounds__(SS_NT, 4) void k_scan_stream(ScanArgs a, const uint
         const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc((void *)(a.lam + beg), 0, len, 0x00020000);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(a.sx + beg), 0, len * 4, 0x00020000);
         thr = sh_thr;
-        thr_f = thr == KEY_MAX ? INFINITY : ord2f((uint32_t)(thr >> 32));
+        thr_f = distance_bound(thr);
         for (int base = 0; base < len; base += 64 * SS_CH) {
             // ---- all loads of up to SS_CH chunks ----
             uint32_t cw[SS_CH][M / 4];
