@@ -44,3 +44,30 @@ def test_indices_stay_in_range(vlq, D, k):  # noqa: F811
             assert ((got[1] >= -1) & (got[1] < 20_000)).all()
     finally:
         vlq.vlq_index_free(idx)
+
+
+@pytest.mark.parametrize("D,k,nq", [(128, 4096, 1), (128, 4100, 5), (32, 16_384, 9), (60, 65_536, 2), (64, 5000, 64)])
+def test_every_nan_takes_the_same_cells(vlq, D, k, nq):  # noqa: F811
+    """A query of NaNs in a small batch, of the usual pattern and of the largest there is: the first cells, whatever the pattern."""
+    rng = np.random.default_rng(k + D)
+    n, m, w1, w2, K = 4, D // 4, 8, 20, 10
+    C = rng.normal(size=(k, D)).astype(np.float32)
+    pr = Problem("other", None, C[:nq].copy(), C, (0.3 * rng.normal(size=(m, 256, 4))).astype(np.float32), n)
+    idx = make_index(vlq, pr)
+    try:
+        add(vlq, idx, pr, 20_000, k)
+
+        def cells_of(Y):
+            d, i = torch.empty(nq, K, device=DEV), torch.empty(nq, K, dtype=torch.int32, device=DEV)
+            cells, cd = torch.empty(nq, w1, dtype=torch.int32, device=DEV), torch.empty(nq, w1, device=DEV)
+            sub, ss = torch.empty(nq, w2, dtype=torch.int32, device=DEV), torch.empty(nq, w2, device=DEV)
+            vlq.vlq_search_debug(idx, dev(Y), nq, w1, w2, K, d, i, cells, cd, sub, ss)
+            return cells.cpu().numpy()
+
+        usual, ones = pr.Y.copy(), pr.Y.copy()
+        usual[nq // 2] = np.nan
+        ones[nq // 2] = np.array(0x7FFFFFFF, np.uint32).view(np.float32)
+        got = cells_of(usual)
+        assert np.array_equal(got[nq // 2], np.arange(w1)) and np.array_equal(got, cells_of(ones))
+    finally:
+        vlq.vlq_index_free(idx)
