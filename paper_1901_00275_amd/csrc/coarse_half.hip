@@ -179,7 +179,8 @@ __global__ __launch_bounds__(256) void k_half_image(const float *__restrict__ X,
         if (row < rows && resid) resid[row] = res * inv;
         if (!own && !hdr && row < rows && nrm < pow2f(14 - HALF_GAP)) apart = 1;
         if (hdr) {
-            const bool ok = res < INFINITY && n2 > 0.f; // (a non-finite row's products never count)
+            // (the products of a row whose norm overflows or is no number never count, whatever the image lost of it)
+            const bool ok = res < INFINITY && n2 > 0.f && n2 * inv * inv < INFINITY;
             float rel = ok && res <= HALF_REL_MAX * nrm ? res / nrm * 1.0001f : 0.f;
             float big = ok && !(res <= HALF_REL_MAX * nrm) ? res * inv : 0.f;
 #pragma unroll

@@ -2,8 +2,10 @@
 whose scale is too far from the columns' for the norm to go into the products, centroids whose norm overflows."""
 import numpy as np
 import pytest
+import torch
 
 from test_gpu_nearest_half import assign
+from test_gpu_parity import DEV
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +53,35 @@ def test_columns_that_do_not_count(D, k):
     cell = assign(X, C)
     assert not np.isin(cell, [5, k - 1]).any()
     check(X, C, cell)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("v", [1e20, 1e24, 1e37])
+def test_columns_that_do_not_count_cost_nothing(D, v):
+    """The same pair in a column block of its own: the other columns' shortlists stay short."""
+    import paper_1901_00275_amd as vlq
+
+    g = torch.Generator(device=DEV)
+    g.manual_seed(2)
+    k, nt = 64 * 128 + 2, 20_000
+    C = torch.randn(k, D, generator=g, device=DEV)
+    X = C[torch.randint(0, k - 2, (nt,), generator=g, device=DEV)] + 0.5 * torch.randn(nt, D, generator=g, device=DEV)
+    cell = torch.empty(nt, dtype=torch.int32, device=DEV)
+
+    def time_of():
+        best = np.inf
+        for _ in range(4):
+            s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            s.record()
+            vlq.vlq_kmeans(X, nt, D, k, 0, C, cell, None)
+            e.record()
+            e.synchronize()
+            best = min(best, s.elapsed_time(e))
+        return best
+
+    plain, want = time_of(), cell.clone()
+    near = want < k - 2  # (vectors that were nearest to one of the pair go elsewhere)
+    C[k - 2, 7], C[k - 1, 7] = v, -v
+    assert time_of() < 2 * plain
+    assert torch.equal(cell[near], want[near]) and (cell < k - 2).all()
