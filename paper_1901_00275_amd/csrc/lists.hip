@@ -216,29 +216,21 @@ void launch_list_scatter(const int32_t *label, const int32_t *st_ids, const uint
 // SORT_MAX points in LDS; longer unsorted lists are reported to the host.
 #define SORT_MAX 1024
 
-#define LS_SHORT 16 // mean points a list up to which 16 lanes serve one
-// SHORT: 64 lists a workgroup, those of up to 16 points without LDS keys or barriers (2 M points in 524 288 lists, a
-// workgroup each: 1.90 -> 0.23 ms)
-template <bool SHORT>
-__global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ off, int64_t nl, int m,
-                                                  int32_t *__restrict__ ids, uint8_t *__restrict__ codes,
-                                                  uint8_t *__restrict__ lam, int32_t *__restrict__ long_lists,
-                                                  int32_t *__restrict__ n_long, int max_long)
+// one list, by a workgroup of 64 threads; keys [SORT_MAX], pay [SORT_MAX (m + 1)] and unsorted in LDS
+__device__ __forceinline__ void sort_list(const int64_t *__restrict__ off, int64_t l, int m, int32_t *__restrict__ ids,
+                                          uint8_t *__restrict__ codes, uint8_t *__restrict__ lam,
+                                          int32_t *__restrict__ long_lists, int32_t *__restrict__ n_long, int max_long,
+                                          uint64_t *keys, uint8_t *pay, int *unsorted, int tid)
 {
-    extern __shared__ unsigned char smem[];
-    uint64_t *keys = (uint64_t *)smem;            // [SORT_MAX]
-    uint8_t *pay = (uint8_t *)(keys + SORT_MAX);  // [SORT_MAX * (m + 1)]
-    __shared__ int unsorted;
-    const int tid = threadIdx.x;
-    auto sort_list = [&](int64_t l, int64_t beg, int64_t len) {
+    const int64_t beg = off[l], len = off[l + 1] - beg;
     if (len <= 1) return;
     __syncthreads(); // (the list before has been read)
-    if (tid == 0) unsorted = 0;
+    if (tid == 0) *unsorted = 0;
     __syncthreads();
     for (int64_t i = tid; i + 1 < len; i += 64)
-        if (ids[beg + i] > ids[beg + i + 1]) unsorted = 1;
+        if (ids[beg + i] > ids[beg + i + 1]) *unsorted = 1;
     __syncthreads();
-    if (!unsorted) return;
+    if (!*unsorted) return;
     if (len > SORT_MAX) {
         if (tid == 0) {
             const int p = atomicAdd(n_long, 1);
@@ -260,15 +252,57 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
         lam[beg + i] = pay[len * m + src];
         for (int p = 0; p < m; ++p) codes[(beg + i) * m + p] = pay[src * m + p];
     }
-    };
-    if (!SHORT) {
-        const int64_t l = blockIdx.x, beg = off[l];
-        sort_list(l, beg, off[l + 1] - beg);
+}
+
+// A workgroup per list; with `work`, the lists on it (n_work[0] of them, handed out through n_work[1]).
+__global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ off, int m, int32_t *__restrict__ ids,
+                                                  uint8_t *__restrict__ codes, uint8_t *__restrict__ lam,
+                                                  int32_t *__restrict__ long_lists, int32_t *__restrict__ n_long,
+                                                  int max_long, const int32_t *__restrict__ work,
+                                                  int32_t *__restrict__ n_work)
+{
+    extern __shared__ unsigned char smem[];
+    uint64_t *keys = (uint64_t *)smem;            // [SORT_MAX]
+    uint8_t *pay = (uint8_t *)(keys + SORT_MAX);  // [SORT_MAX * (m + 1)]
+    __shared__ int unsorted;
+    const int tid = threadIdx.x;
+    if (!work) {
+        sort_list(off, blockIdx.x, m, ids, codes, lam, long_lists, n_long, max_long, keys, pay, &unsorted, tid);
         return;
     }
+    const int n = n_work[0];
+    for (;;) {
+        int i = 0;
+        if (tid == 0) i = atomicAdd(&n_work[1], 1);
+        i = __builtin_amdgcn_readfirstlane(i); // (the workgroup is one wave)
+        if (i >= n) return;
+        sort_list(off, work[i], m, ids, codes, lam, long_lists, n_long, max_long, keys, pay, &unsorted, tid);
+    }
+}
+
+// Lists of few points: 64 of them a workgroup, those of up to 16 points sorted by 16 lanes each, those of up to LS_FEW by the wave,
+// without keys in LDS or barriers (2 M points in 524 288 lists, a workgroup each: 1.90 -> 0.23 ms); longer ones go on the
+// worklist.  (Sorted here as well, one after the other, the lists of a crowded cell, which lie next to each other, kept one
+// wave busy: 2 M points in 2 560 of 1 M lists, finalisation 2.0 -> 6.7 ms.)
+#define LS_SHORT 16 // mean points a list up to which that is done
+#define LS_FEW 64
+__global__ __launch_bounds__(64) void k_list_sort_few(const int64_t *__restrict__ off, int64_t nl, int m,
+                                                      int32_t *__restrict__ ids, uint8_t *__restrict__ codes,
+                                                      uint8_t *__restrict__ lam, int32_t *__restrict__ work,
+                                                      int32_t *__restrict__ n_work)
+{
+    extern __shared__ unsigned char smem[]; // [4][16 (m + 1)], or [64 (m + 1)]
+    const int tid = threadIdx.x;
     const int64_t l0 = (int64_t)blockIdx.x * 64;
     const int64_t mybeg = off[min(l0 + tid, nl)], mylen = off[min(l0 + tid + 1, nl)] - mybeg;
-    // up to 16 points: 16 lanes a list, four lists at a time, a point's place counted over the group
+    const uint64_t more = __ballot(mylen > LS_FEW);
+    if (more) {
+        int at = 0;
+        if (tid == 0) at = atomicAdd(&n_work[0], __popcll(more));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (mylen > LS_FEW) work[at + __popcll(more & ((1ull << tid) - 1ull))] = (int32_t)(l0 + tid);
+    }
+    // four lists at a time, a point's place counted over the group
     uint64_t todo = __ballot(mylen > 1 && mylen <= 16);
     while (todo) {
         int src[4]; // (uniform)
@@ -293,7 +327,7 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
             const uint32_t o = (uint32_t)__shfl((int)id, 16 * sub + j, 64);
             place += o < id || (o == id && j < l16);
         }
-        uint8_t *pg = pay + sub * 16 * (m + 1); // the group's codes and lambdas, as they were
+        uint8_t *pg = smem + sub * 16 * (m + 1); // the group's codes and lambdas, as they were
         if (on) {
             for (int p = 0; p < m; ++p) pg[l16 * m + p] = codes[(beg + l16) * m + p];
             pg[16 * m + l16] = lam[beg + l16];
@@ -306,25 +340,54 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
         }
         wave_lds_order();
     }
-    for (uint64_t more = __ballot(mylen > 16); more; more &= more - 1) {
-        const int from = __ffsll((unsigned long long)more) - 1;
+    // one list at a time
+    for (uint64_t left = __ballot(mylen > 16 && mylen <= LS_FEW); left; left &= left - 1) {
+        const int from = __ffsll((unsigned long long)left) - 1;
         const int64_t beg = off[l0 + from];
-        sort_list(l0 + from, beg, off[l0 + from + 1] - beg);
+        const int len = (int)(off[l0 + from + 1] - beg);
+        const bool on = tid < len;
+        const uint32_t id = on ? (uint32_t)ids[beg + tid] : 0xFFFFFFFFu;
+        const int next = __shfl_down((int)id, 1, 64);
+        if (!__ballot(tid + 1 < len && (int)id > next)) continue;
+        int place = 0;
+        for (int j = 0; j < len; ++j) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)id, j);
+            place += o < id || (o == id && j < tid);
+        }
+        if (on) {
+            for (int p = 0; p < m; ++p) smem[tid * m + p] = codes[(beg + tid) * m + p];
+            smem[LS_FEW * m + tid] = lam[beg + tid];
+        }
+        wave_lds_order();
+        if (on) {
+            ids[beg + place] = (int32_t)id;
+            lam[beg + place] = smem[LS_FEW * m + tid];
+            for (int p = 0; p < m; ++p) codes[(beg + place) * m + p] = smem[tid * m + p];
+        }
+        wave_lds_order();
     }
 }
+
+bool lists_are_short(int64_t nl, int64_t N) { return N <= LS_SHORT * nl; }
+
 void launch_list_sort(const int64_t *off, int64_t nl, int m, int32_t *ids, uint8_t *codes, uint8_t *lam,
-                      int64_t N, int32_t *long_lists, int32_t *n_long, int max_long, hipStream_t st)
+                      int64_t N, int32_t *long_lists, int32_t *n_long, int max_long, int32_t *work, int32_t *n_work,
+                      hipStream_t st)
 {
     if (nl <= 0) return;
     const size_t smem = (size_t)SORT_MAX * 8 + (size_t)SORT_MAX * (m + 1);
-    auto go = [&](auto kern, unsigned grid) {
-        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64), smem, st, off, nl, m, ids, codes, lam, long_lists, n_long, max_long);
-    };
-    if (N <= LS_SHORT * nl)
-        go(k_list_sort<true>, (unsigned)((nl + 63) / 64));
-    else
-        go(k_list_sort<false>, (unsigned)nl);
+    (void)hipFuncSetAttribute((const void *)k_list_sort, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (!lists_are_short(nl, N)) {
+        hipLaunchKernelGGL(k_list_sort, dim3((unsigned)nl), dim3(64), smem, st, off, m, ids, codes, lam, long_lists, n_long,
+                           max_long, (const int32_t *)nullptr, (int32_t *)nullptr);
+        return;
+    }
+    hipLaunchKernelGGL(k_list_sort_few, dim3((unsigned)((nl + 63) / 64)), dim3(64), (size_t)LS_FEW * (m + 1), st, off, nl, m,
+                       ids, codes, lam, work, n_work);
+    const int64_t most = N / (LS_FEW + 1); // lists on the worklist; more workgroups than run at once are of no use
+    if (most > 0)
+        hipLaunchKernelGGL(k_list_sort, dim3((unsigned)(most < 4096 ? most : 4096)), dim3(64), smem, st, off, m, ids, codes, lam,
+                           long_lists, n_long, max_long, (const int32_t *)work, n_work);
 }
 
 // Second tier: the lists the 64-thread pass reported (more than SORT_MAX points), one

@@ -12,15 +12,38 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("m", [5, 8, 16])
 @pytest.mark.parametrize("k,n,N,long", [(7, 3, 40, 0), (100, 8, 3000, 17), (100, 8, 9000, 1500), (33, 4, 2000, 0), (5, 4, 5000, 300)])
 def test_lists_are_in_order_of_id(m, k, n, N, long):
+    def lists(rng):
+        cell, edge = rng.integers(0, k, N), rng.integers(0, n, N)
+        if long:
+            cell[:long], edge[:long] = 1, 2
+        return cell, edge
+
+    check(m, k, n, N, lists, np.random.default_rng(k + N + m))
+
+
+@pytest.mark.parametrize("m", [1, 6, 8, 64])
+@pytest.mark.parametrize("k", [500, 300, 120])  # 4.3 points a list, 7.2 and 18
+@pytest.mark.parametrize("sizes", [[2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 66, 127, 300, 1023, 1024, 1025, 1500], [64] * 100, [65] * 100, [17] * 64 + [64] * 64])
+def test_crowded_cells(m, k, sizes):
+    """Lists of every size class next to each other, among many of few points or none."""
+    n, N = 8, 17_000
+
+    def lists(rng):
+        label = np.repeat(np.arange(len(sizes)) + 5, sizes)
+        label = np.concatenate([label, rng.integers(len(sizes) + 9, k * n, N - len(label))])
+        rng.shuffle(label)
+        return label // n, label % n
+
+    check(m, k, n, N, lists, np.random.default_rng(m + k + len(sizes)))
+
+
+def check(m, k, n, N, lists, rng):
     import paper_1901_00275_amd as vlq
 
-    rng = np.random.default_rng(k + N + m)
     D = 4 * m
     C = torch.tensor(rng.normal(size=(k, D)), dtype=torch.float32, device=DEV)
     P = torch.tensor(rng.normal(size=(m, 256, 4)), dtype=torch.float32, device=DEV)
-    cell, edge = rng.integers(0, k, N), rng.integers(0, n, N)
-    if long:
-        cell[:long], edge[:long] = 1, 2
+    cell, edge = lists(rng)
     ids = rng.permutation(5 * N)[:N]
     ids[: N // 10] = ids[N // 10 - 1]  # some ids repeat
     lam, codes = rng.integers(0, 256, N), rng.integers(0, 256, (N, m))
@@ -49,3 +72,40 @@ def test_lists_are_in_order_of_id(m, k, n, N, long):
         s, e = off[l], off[l + 1]
         mine = np.flatnonzero(label == l)
         assert np.array_equal(rec(oid[s:e], olam[s:e], ocode[s:e]), rec(ids[mine], lam[mine].astype(np.uint8), codes[mine].astype(np.uint8)))
+
+
+def finalise_time(k, n, cell, edge):
+    """Milliseconds of vlq_index_finalize over points in these lists, in random order."""
+    import time
+
+    import paper_1901_00275_amd as vlq
+
+    m, N = 8, len(cell)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(k)
+    C, P = torch.randn(k, 32, generator=g, device=DEV), torch.randn(m, 256, 4, generator=g, device=DEV)
+    idx = vlq.vlq_build_index(vlq.vlq_params_t(32, k, n, m, 0.0, 0.0), C, P)
+    try:
+        lam = torch.full((N,), 100, dtype=torch.uint8, device=DEV)
+        codes = torch.randint(0, 256, (N, m), generator=g, device=DEV, dtype=torch.uint8)
+        vlq.vlq_index_add_encoded(idx, cell, edge, lam, codes, None, N)
+        best = np.inf
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            vlq.vlq_index_finalize(idx)
+            best = min(best, time.perf_counter() - t)
+    finally:
+        vlq.vlq_index_free(idx)
+    return best * 1e3
+
+
+def test_crowded_cells_of_an_empty_index_are_no_slower():
+    """Two million points in 40 cells: with 16 384 cells (few points a list on average) and with 1 000 (many)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    n, N = 64, 2_000_000
+    cell = torch.randint(0, 40, (N,), generator=g, device=DEV, dtype=torch.int32)
+    edge = torch.randint(0, n, (N,), generator=g, device=DEV, dtype=torch.int32)
+    empty = finalise_time(16_384, n, cell[:1000], edge[:1000])
+    assert finalise_time(16_384, n, cell, edge) < 1.5 * finalise_time(1000, n, cell, edge) + empty
