@@ -497,21 +497,23 @@ void launch_long_list_sort_at(int64_t beg, int64_t len, int m, int32_t *ids, uin
 // inner products taken relative to a fixed vector mu (the scan's table is 2 <y - mu, q2>, so mu drops
 // out of the distance; what it removes is the part of both inner products that grows with the
 // distance of the data from the origin and would cancel between them in fp32).
-// Summed in fp64 and rounded once.  One 64-thread workgroup per list: the edge length c is formed
-// by the whole wave, then lanes stride over the points, every lane walking the D coordinates of its
-// point (centroid rows come from L1/L2, the same for all lanes).
-// LPL lanes a list: a wave for lists of many points; 16 lanes, four lists a wave, where lists are short (2 M points in
-// 524 288 lists: a wave each left 60 of 64 lanes idle: 3.34 -> 0.90 ms).  Sums in the same order either way: the squared
-// edge is added up as 64 lanes do it, a point's terms one after the other.
-template <int LPL>
+// Summed in fp64 and rounded once.  LPL lanes a list: the edge length c is formed by them together, then they stride over
+// the points, every lane walking the D coordinates of its point (the lanes of a list read the same centroid rows and mean:
+// with a list a wave its number is uniform, and the rows come through scalar loads).  A wave a list where lists hold many points;
+// 16 lanes, four lists a wave, where they are short (2 M points in 524 288 lists: a wave each left 60 of 64 lanes idle:
+// 3.34 -> 0.90 ms).  Sums in the same order either way: the squared edge is added up as 64 lanes do it, a point's
+// terms one after the other.  VEC: D/m a multiple of four, rows on 16 bytes.
+template <int LPL, bool VEC>
 __global__ __launch_bounds__(256) void k_list_static(const int64_t *__restrict__ off, int64_t nl, int n, int D, int m,
                                                      const float *__restrict__ C, const int32_t *__restrict__ S,
                                                      const float *__restrict__ P, const float *__restrict__ mu,
                                                      const uint8_t *__restrict__ codes,
                                                      const uint8_t *__restrict__ lam, double lam_step, float lam_zero,
-                                                     int vec, float *__restrict__ sx)
+                                                     float *__restrict__ sx)
 {
-    const int64_t l = (int64_t)blockIdx.x * (256 / LPL) + threadIdx.x / LPL;
+    int own = threadIdx.x / LPL;
+    if (LPL == 64) own = __builtin_amdgcn_readfirstlane(own);
+    const int64_t l = (int64_t)blockIdx.x * (256 / LPL) + own;
     const int lane = threadIdx.x % LPL;
     if (l >= nl) return; // (whole groups of LPL lanes)
     const int64_t beg = off[l], end = off[l + 1];
@@ -547,7 +549,7 @@ __global__ __launch_bounds__(256) void k_list_static(const int64_t *__restrict__
         };
         for (int p = 0; p < m; ++p) {
             const float *w = P + ((int64_t)p * 256 + codes[t * m + p]) * ds;
-            if (vec) { // ds a multiple of four, rows on 16 bytes
+            if (VEC) {
 #pragma unroll 4
                 for (int d = 0; d < ds; d += 4) {
                     const int g = p * ds + d;
@@ -569,11 +571,13 @@ void launch_list_static(const int64_t *off, int64_t nl, int n, int D, int m, con
                         float lam_zero, int64_t N, float *sx, hipStream_t st)
 {
     if (nl <= 0) return;
-    const int vec = (D / m) % 4 == 0 && (((uintptr_t)C | (uintptr_t)P | (uintptr_t)mu) % 16) == 0;
-    if (N <= LS_SHORT * nl)
-        hipLaunchKernelGGL(k_list_static<16>, dim3((unsigned)((nl + 15) / 16)), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu,
-                           codes, lam, lam_step, lam_zero, vec, sx);
+    const bool vec = (D / m) % 4 == 0 && (((uintptr_t)C | (uintptr_t)P | (uintptr_t)mu) % 16) == 0;
+    auto go = [&](auto kern, int lists) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((nl + lists - 1) / lists)), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu, codes,
+                           lam, lam_step, lam_zero, sx);
+    };
+    if (lists_are_short(nl, N))
+        vec ? go(k_list_static<16, true>, 16) : go(k_list_static<16, false>, 16);
     else
-        hipLaunchKernelGGL(k_list_static<64>, dim3((unsigned)((nl + 3) / 4)), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu,
-                           codes, lam, lam_step, lam_zero, vec, sx);
+        vec ? go(k_list_static<64, true>, 4) : go(k_list_static<64, false>, 4);
 }
