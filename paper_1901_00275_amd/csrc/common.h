@@ -476,11 +476,12 @@ void launch_list_scatter(const int32_t *label, const int32_t *st_ids, const uint
 // s_x of every stored point (see scan_stream.hip)
 void launch_list_static(const int64_t *off, int64_t nl, int n, int D, int m, const float *C, const int32_t *S,
                         const float *P, const float *mu, const uint8_t *codes, const uint8_t *lam, double lam_step,
-                        float lam_zero, int64_t N, float *sx, hipStream_t st);
+                        float lam_zero, int64_t N, const int32_t *work, int32_t *n_work, float *sx, hipStream_t st);
 void launch_list_sort(const int64_t *off, int64_t nl, int m, int32_t *ids, uint8_t *codes, uint8_t *lam,
                       int64_t N, int32_t *long_lists, int32_t *n_long, int max_long, int32_t *work, int32_t *n_work,
                       hipStream_t st);
-bool lists_are_short(int64_t nl, int64_t N); // few points a list: work [nl] and n_work [0 .. 1], cleared, are used
+// few points a list: launch_list_sort fills work [nl] (n_work [3], cleared), launch_list_static reads it
+bool lists_are_short(int64_t nl, int64_t N);
 // second tier of the per-list sort: the reported lists of up to list_sort_mid_max(m) points (0: tier unavailable)
 int list_sort_mid_max(int m);
 void launch_list_sort_mid(const int64_t *off, int m, const int32_t *in_lists, int n_in, int32_t *ids, uint8_t *codes,

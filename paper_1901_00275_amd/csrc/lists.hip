@@ -254,7 +254,8 @@ __device__ __forceinline__ void sort_list(const int64_t *__restrict__ off, int64
     }
 }
 
-// A workgroup per list; with `work`, the lists on it (n_work[0] of them, handed out through n_work[1]).
+// A workgroup per list; with `work`, the lists on it (n_work[0] of them, handed out through n_work[1] after the first of each
+// workgroup: where there are none, thousands of workgroups would queue for the one address).
 __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ off, int m, int32_t *__restrict__ ids,
                                                   uint8_t *__restrict__ codes, uint8_t *__restrict__ lam,
                                                   int32_t *__restrict__ long_lists, int32_t *__restrict__ n_long,
@@ -271,12 +272,10 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
         return;
     }
     const int n = n_work[0];
-    for (;;) {
-        int i = 0;
-        if (tid == 0) i = atomicAdd(&n_work[1], 1);
-        i = __builtin_amdgcn_readfirstlane(i); // (the workgroup is one wave)
-        if (i >= n) return;
+    for (int i = blockIdx.x; i < n;) {
         sort_list(off, work[i], m, ids, codes, lam, long_lists, n_long, max_long, keys, pay, &unsorted, tid);
+        if (tid == 0) i = (int)gridDim.x + atomicAdd(&n_work[1], 1);
+        i = __builtin_amdgcn_readfirstlane(i); // (the workgroup is one wave)
     }
 }
 
@@ -503,21 +502,24 @@ void launch_long_list_sort_at(int64_t beg, int64_t len, int m, int32_t *ids, uin
 // 16 lanes, four lists a wave, where they are short (2 M points in 524 288 lists: a wave each left 60 of 64 lanes idle:
 // 3.34 -> 0.90 ms).  Sums in the same order either way: the squared edge is added up as 64 lanes do it, a point's
 // terms one after the other.  VEC: D/m a multiple of four, rows on 16 bytes.
-template <int LPL, bool VEC>
-__global__ __launch_bounds__(256) void k_list_static(const int64_t *__restrict__ off, int64_t nl, int n, int D, int m,
+// 16 lanes leave lists of more than LS_FEW points to the second launch, whose waves take the lists on the worklist (n_work[0]
+// of them, handed out through n_work[2] after the first of each wave): the points of a long list would be walked by 16 lanes alone (2 M points in 8 cells
+// of 16 384, finalisation 3.1 -> 4.0 ms; half of them in one list 255 -> 382).
+template <int LPL, bool VEC, bool WORK>
+__global__ __launch_bounds__(256, LPL == 64 ? 4 : 5) void k_list_static(const int64_t *__restrict__ off, int64_t nl, int n, int D, int m,
                                                      const float *__restrict__ C, const int32_t *__restrict__ S,
                                                      const float *__restrict__ P, const float *__restrict__ mu,
                                                      const uint8_t *__restrict__ codes,
                                                      const uint8_t *__restrict__ lam, double lam_step, float lam_zero,
+                                                     const int32_t *__restrict__ work, int32_t *__restrict__ n_work,
                                                      float *__restrict__ sx)
 {
     int own = threadIdx.x / LPL;
     if (LPL == 64) own = __builtin_amdgcn_readfirstlane(own);
-    const int64_t l = (int64_t)blockIdx.x * (256 / LPL) + own;
     const int lane = threadIdx.x % LPL;
-    if (l >= nl) return; // (whole groups of LPL lanes)
+    auto list_terms = [&](int64_t l) {
     const int64_t beg = off[l], end = off[l + 1];
-    if (beg == end) return;
+    if (beg == end || (LPL < 64 && end - beg > LS_FEW)) return;
     const int i = (int)(l / n);
     const float *ci = C + (int64_t)i * D;
     const float *sj = C + (int64_t)S[l] * D;
@@ -538,6 +540,7 @@ __global__ __launch_bounds__(256) void k_list_static(const int64_t *__restrict__
 #pragma unroll
     for (int o = LPL / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
     const int ds = D / m;
+#pragma unroll 1
     for (int64_t t = beg + lane; t < end; t += LPL) {
         const double lh = ((double)lam[t] - (double)lam_zero) * lam_step;
         double q2n = 0.0, q12 = 0.0;
@@ -564,20 +567,36 @@ __global__ __launch_bounds__(256) void k_list_static(const int64_t *__restrict__
         }
         sx[t] = (float)(q2n + 2.0 * q12 + (lh * lh - lh) * c);
     }
+    };
+    if (WORK) {
+        const int todo = n_work[0], waves = (int)gridDim.x * 4;
+        for (int i = (int)blockIdx.x * 4 + own; i < todo;) {
+            list_terms(work[i]);
+            if (lane == 0) i = waves + atomicAdd(&n_work[2], 1);
+            i = __builtin_amdgcn_readfirstlane(i);
+        }
+    } else {
+        const int64_t l = (int64_t)blockIdx.x * (256 / LPL) + own;
+        if (l < nl) list_terms(l); // (whole groups of LPL lanes)
+    }
 }
 
 void launch_list_static(const int64_t *off, int64_t nl, int n, int D, int m, const float *C, const int32_t *S,
                         const float *P, const float *mu, const uint8_t *codes, const uint8_t *lam, double lam_step,
-                        float lam_zero, int64_t N, float *sx, hipStream_t st)
+                        float lam_zero, int64_t N, const int32_t *work, int32_t *n_work, float *sx, hipStream_t st)
 {
     if (nl <= 0) return;
     const bool vec = (D / m) % 4 == 0 && (((uintptr_t)C | (uintptr_t)P | (uintptr_t)mu) % 16) == 0;
-    auto go = [&](auto kern, int lists) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)((nl + lists - 1) / lists)), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu, codes,
-                           lam, lam_step, lam_zero, sx);
+    auto go = [&](auto kern, int64_t blocks, const int32_t *list) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu, codes, lam, lam_step,
+                           lam_zero, list, n_work, sx);
     };
-    if (lists_are_short(nl, N))
-        vec ? go(k_list_static<16, true>, 16) : go(k_list_static<16, false>, 16);
-    else
-        vec ? go(k_list_static<64, true>, 4) : go(k_list_static<64, false>, 4);
+    const int32_t *none = nullptr;
+    if (!lists_are_short(nl, N)) {
+        vec ? go(k_list_static<64, true, false>, (nl + 3) / 4, none) : go(k_list_static<64, false, false>, (nl + 3) / 4, none);
+        return;
+    }
+    vec ? go(k_list_static<16, true, false>, (nl + 15) / 16, none) : go(k_list_static<16, false, false>, (nl + 15) / 16, none);
+    const int64_t most = N / (LS_FEW + 1), blocks = most < 4 * 2048 ? (most + 3) / 4 : 2048; // eight workgroups per compute unit
+    if (most > 0) vec ? go(k_list_static<64, true, true>, blocks, work) : go(k_list_static<64, false, true>, blocks, work);
 }

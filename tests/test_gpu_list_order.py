@@ -109,3 +109,56 @@ def test_crowded_cells_of_an_empty_index_are_no_slower():
     edge = torch.randint(0, n, (N,), generator=g, device=DEV, dtype=torch.int32)
     empty = finalise_time(16_384, n, cell[:1000], edge[:1000])
     assert finalise_time(16_384, n, cell, edge) < 1.5 * finalise_time(1000, n, cell, edge) + empty
+
+
+def test_a_long_list_among_short_ones_is_no_slower():
+    """Half of 600 000 points in one list, the others spread: with 16 384 cells and with 100."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    n, N = 32, 600_000
+    cell = torch.randint(0, 100, (N,), generator=g, device=DEV, dtype=torch.int32)
+    edge = torch.randint(0, n, (N,), generator=g, device=DEV, dtype=torch.int32)
+    cell[::2], edge[::2] = 5, 3
+    empty = finalise_time(16_384, n, cell[1:1000:2].contiguous(), edge[1:1000:2].contiguous())
+    assert finalise_time(16_384, n, cell, edge) < 1.3 * finalise_time(100, n, cell, edge) + empty
+
+
+@pytest.mark.parametrize("m,ds", [(8, 4), (16, 6), (8, 5)])
+@pytest.mark.parametrize("k", [500, 60])  # 4.3 points a list and 36
+def test_static_terms_of_every_list(m, ds, k):
+    """Distances to points of lists of every size class, against fp64: short lists, long ones among them, long ones all."""
+    import paper_1901_00275_amd as vlq
+
+    sizes, n, N, D, K = [1, 2, 15, 16, 17, 63, 64, 65, 66, 128, 129, 700, 1025], 8, 17_000, m * ds, 100
+    rng = np.random.default_rng(m + ds + k)
+    label = np.repeat(np.arange(len(sizes)) + 5, sizes)
+    label = np.concatenate([label, rng.integers(len(sizes) + 9, k * n, N - len(label))])
+    lam, codes = rng.integers(0, 256, N), rng.integers(0, 256, (N, m))
+    C, P = rng.normal(size=(k, D)).astype(np.float32), (0.3 * rng.normal(size=(m, 256, ds))).astype(np.float32)
+    t = lambda a, dt: torch.tensor(a).to(dt).to(DEV)  # noqa: E731
+    idx = vlq.vlq_build_index(vlq.vlq_params_t(D, k, n, m, 0.0, 0.0), t(C, torch.float32), t(P, torch.float32))
+    try:
+        S, E = torch.empty(k, n, dtype=torch.int32, device=DEV), torch.empty(k, n, device=DEV)
+        vlq.vlq_index_get_graph(idx, S, E)
+        S = S.cpu().numpy()
+        lh = (lam * 0.75 / 255 - 0.25)[:, None]  # the default grid
+        c, s = C[label // n].astype(np.float64), C[S[label // n, label % n]].astype(np.float64)
+        X = c + lh * (s - c) + P[np.arange(m), codes].reshape(N, D)
+        seen = np.concatenate([np.flatnonzero(label == 5 + i)[:70] for i in range(len(sizes))] + [rng.integers(0, N, 100)])
+        Y = (X[seen] + 1e-2 * rng.normal(size=(len(seen), D))).astype(np.float32)
+        nq = len(Y)
+        vlq.vlq_index_add_encoded(idx, t(label // n, torch.int32), t(label % n, torch.int32), t(lam, torch.uint8), t(codes, torch.uint8), None, N)
+        vlq.vlq_index_finalize(idx)
+        dist, ids = torch.empty(nq, K, device=DEV), torch.empty(nq, K, dtype=torch.int32, device=DEV)
+        vlq.vlq_search(idx, t(Y, torch.float32), nq, min(k, 64), min(k, 64) * n, K, dist, ids)
+        torch.cuda.synchronize()
+    finally:
+        vlq.vlq_index_free(idx)
+    dist, ids = dist.cpu().numpy(), ids.cpu().numpy()
+    found = 0
+    for q in range(nq):
+        d = ((Y[q].astype(np.float64) - X[ids[q]]) ** 2).sum(1)
+        # fp32 sums of terms of the size of ||y||^2 and ||x||^2 + ||s - c||^2, a hundred roundings at most
+        assert (np.abs(dist[q] - d) < 100 * 2.0 ** -24 * 8 * ((Y[q] ** 2).sum() + (X[ids[q]] ** 2).sum(1) + 4 * D)).all()
+        found += seen[q] in ids[q]
+    assert found > 0.95 * nq
