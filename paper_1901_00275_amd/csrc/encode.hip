@@ -65,15 +65,18 @@ __device__ __forceinline__ uint64_t resolve_markers(const uint64_t *__restrict__
 }
 
 // width of the band around the smallest shortlist distance of vector gid
+template <bool HALF>
 __device__ __forceinline__ float shortlist_band(const EncodeArgs &a, int64_t gid, float xn, float dmin)
 {
-    if (a.bhdr) return nn_half_band(xn, a.xres[gid], a.bhdr[0], a.bhdr[1], dmin, a.band_dist, a.D);
+    if (HALF) return nn_half_band(xn, a.xres[gid], a.bhdr[0], a.bhdr[1], dmin, a.band_dist, a.D);
     return a.band_norm * (3.f * xn + 2.f * dmin);
 }
 
 // Nearest centroid of vector gid from its shortlist: what lies inside the band of the smallest distance is
 // re-evaluated as direct sums of squared differences, the smallest (distance, index) is the cell (Eq. 2).
-// x: the vector (one wave's), xn: its squared norm as the product saw it.
+// x: the vector (one wave's), xn: its squared norm as the product saw it.  HALF: the shortlist is the fp16 product's, else
+// the fp32 product's (told apart at run time, the one form's branches and registers cost the other 2 %).
+template <bool HALF>
 __device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gid, const float *x, float xn, int lane, bool vec)
 {
     const int nc = a.nsplit * VLQ_NN_CANDS, l16 = lane & 15;
@@ -82,21 +85,21 @@ __device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gi
     bool marked = false;
     for (int c = lane; c < nc; c += 64) {
         const uint64_t key = cd[c];
-        if (!a.bhdr && (uint32_t)(key >> 32) == VLQ_NN_MARK)
+        if (!HALF && (uint32_t)(key >> 32) == VLQ_NN_MARK)
             marked = true;
         else
             mn = key < mn ? key : mn;
     }
     // fp32 product: incomplete shortlists first, the marked slots (or all columns) exactly
-    if (__ballot(marked)) bk = resolve_markers(cd, nc, a.nsplit, x, a.C, a.k, a.D, lane);
+    if (!HALF && __ballot(marked)) bk = resolve_markers(cd, nc, a.nsplit, x, a.C, a.k, a.D, lane);
     mn = wave_min_u64(mn);
     if (mn != KEY_MAX) {
         const float dmin = __uint_as_float((uint32_t)(mn >> 32));
-        const float band = dmin + shortlist_band(a, gid, xn, dmin);
+        const float band = dmin + shortlist_band<HALF>(a, gid, xn, dmin);
         const int ntiles = (a.k + VLQ_NN_TILE - 1) / VLQ_NN_TILE, per = (ntiles + a.nsplit - 1) / a.nsplit;
         for (int c0 = 0; c0 < nc; c0 += 64) { // the few candidates inside the band, found 64 keys at a time
             const uint64_t key = c0 + lane < nc ? cd[c0 + lane] : KEY_MAX;
-            const bool inb = key != KEY_MAX && (a.bhdr || (uint32_t)(key >> 32) != VLQ_NN_MARK) &&
+            const bool inb = key != KEY_MAX && (HALF || (uint32_t)(key >> 32) != VLQ_NN_MARK) &&
                              !(__uint_as_float((uint32_t)(key >> 32)) > band);
             uint64_t mask = __ballot(inb);
             while (mask) {
@@ -104,7 +107,7 @@ __device__ __forceinline__ uint64_t nearest_cell(const EncodeArgs &a, int64_t gi
                 mask &= mask - 1;
                 const uint32_t idx = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, src);
                 uint64_t got;
-                if (!a.bhdr) {
+                if (!HALF) {
                     got = make_key(sqdist16(x, a.C + (int64_t)idx * a.D, a.D, l16, vec), idx);
                 } else if (!(idx & VLQ_NN_SLOT)) { // columns idx + 16 j, a group of 16 lanes each
                     const uint32_t i = idx + 16 * (lane >> 4);
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(NC_NT) void k_nearest_cells(EncodeArgs a)
         const int s = (__ffsll((unsigned long long)left) - 1) >> 4;
         left &= ~(0xFFFFull << (16 * s));
         const float sn = __shfl(xn, 16 * s, 64);
-        const uint64_t got = nearest_cell(a, g0 + s, xs + (wave * 4 + s) * D, sn, lane, true);
+        const uint64_t got = nearest_cell<true>(a, g0 + s, xs + (wave * 4 + s) * D, sn, lane, true);
         if (sub == s) bk = got;
     }
     if (l16 == 0 && g0 + sub < a.nb) a.cell[gid] = (int32_t)(uint32_t)bk;
@@ -252,7 +255,7 @@ __device__ __forceinline__ float line_byte_and_residual(float *x, const float *_
 //    lambda -> byte -> grid value; residual to the anchor of that grid value (Eq. 12).
 //  phase 2 (thread = codeword): for every sub-space the nearest codeword by direct
 //    squared distance, ties to the smaller codeword (Alg. 2).
-template <int DS>
+template <int DS, bool HALF>
 __global__ __launch_bounds__(ENC_NT) void k_encode_finish(EncodeArgs a, int PB)
 {
     extern __shared__ unsigned char smem[];
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish(EncodeArgs a, int PB)
         }
         xn = wave_sum(xn);
         wave_lds_order(); // every lane reads the whole of x from here on
-        const uint64_t bk = nearest_cell(a, gid, x, xn, lane, vec16);
+        const uint64_t bk = nearest_cell<HALF>(a, gid, x, xn, lane, vec16);
         const int cell = (int)(uint32_t)bk;
         const float av = ord2f((uint32_t)(bk >> 32));
         if (!a.S) { // nearest centroid only (Lloyd iterations)
@@ -381,7 +384,7 @@ __device__ __forceinline__ float wave_min_f32(float v)
     return fminf(v, __shfl_xor(v, 32, 64));
 }
 
-template <int DS, int PB>
+template <int DS, int PB, bool HALF>
 __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
 {
     extern __shared__ unsigned char smem[];
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(ENC_NT) void k_encode_finish_lanes(EncodeArgs a)
         }
         xn = wave_sum(xn);
         wave_lds_order(); // every lane reads the whole of x from here on
-        const uint64_t bk = nearest_cell(a, gid, x, xn, lane, vec16);
+        const uint64_t bk = nearest_cell<HALF>(a, gid, x, xn, lane, vec16);
         const int cell = (int)(uint32_t)bk;
         const float av = ord2f((uint32_t)(bk >> 32));
         // line quantisation inside the cell, four neighbour rows per pass
@@ -587,13 +590,12 @@ void launch_encode_finish(const EncodeArgs &a, hipStream_t st)
         const int pb = few ? ENC_FEW_PB : ENC2_PB;
         const size_t smem2 = (size_t)pb * (a.D + 1) * 4 + (size_t)pb * a.m;
         const unsigned grid2 = (unsigned)((a.nb + pb - 1) / pb);
-#define ENC2_LAUNCH(DSV)                                                                                       \
-    do {                                                                                                       \
-        if (few)                                                                                               \
-            hipLaunchKernelGGL((k_encode_finish_lanes<DSV, ENC_FEW_PB>), dim3(grid2), dim3(ENC_NT), smem2, st, a); \
-        else                                                                                                   \
-            hipLaunchKernelGGL((k_encode_finish_lanes<DSV, ENC2_PB>), dim3(grid2), dim3(ENC_NT), smem2, st, a);  \
-    } while (0)
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid2), dim3(ENC_NT), smem2, st, a); };
+#define ENC2_LAUNCH(DSV)                                                                                          \
+    if (few)                                                                                                      \
+        a.bhdr ? go(k_encode_finish_lanes<DSV, ENC_FEW_PB, true>) : go(k_encode_finish_lanes<DSV, ENC_FEW_PB, false>); \
+    else                                                                                                          \
+        a.bhdr ? go(k_encode_finish_lanes<DSV, ENC2_PB, true>) : go(k_encode_finish_lanes<DSV, ENC2_PB, false>)
         switch (a.D / a.m) {
         case 4: ENC2_LAUNCH(4); break;
         case 6: ENC2_LAUNCH(6); break;
@@ -616,12 +618,11 @@ void launch_encode_finish(const EncodeArgs &a, hipStream_t st)
     const size_t smem = (size_t)PB * a.D * 4 + (size_t)PB * a.m * 8;
     const unsigned grid = (unsigned)((a.nb + PB - 1) / PB);
     const int ds = a.D / a.m;
-#define ENC_LAUNCH(DSV)                                                                                        \
-    do {                                                                                                       \
-        (void)hipFuncSetAttribute((const void *)k_encode_finish<DSV>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                  (int)smem);                                                                  \
-        hipLaunchKernelGGL(k_encode_finish<DSV>, dim3(grid), dim3(ENC_NT), smem, st, a, PB);                    \
-    } while (0)
+    auto go = [&](auto kern) {
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(ENC_NT), smem, st, a, PB);
+    };
+#define ENC_LAUNCH(DSV) a.bhdr ? go(k_encode_finish<DSV, true>) : go(k_encode_finish<DSV, false>)
     switch (ds) {
     case 2: ENC_LAUNCH(2); break;
     case 4: ENC_LAUNCH(4); break;
