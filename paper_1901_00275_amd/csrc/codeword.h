@@ -26,7 +26,9 @@
 // farther from the vector than d: it is not the nearest, whatever its value.
 __device__ __forceinline__ float codeword_band(int ds, float xn, float v, float cmax)
 {
-    const float x = sqrtf(xn), s = x + sqrtf(fmaxf(fmaf(2.f, v, xn), 0.f)), c = fminf(cmax, 1.1f * s);
+    // (the hardware's root: what it is off by at most, and what it flushes, is far below the slack of s and of the band)
+    const float x = __builtin_amdgcn_sqrtf(xn), s = x + __builtin_amdgcn_sqrtf(fmaxf(fmaf(2.f, v, xn), 0.f));
+    const float c = fminf(cmax, 1.1f * s);
     return 4.f * (float)(ds + 8) * 0x1p-24f * (x + c) * (x + c) + 0x1p-119f;
 }
 

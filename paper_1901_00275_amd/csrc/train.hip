@@ -8,6 +8,7 @@
 // >= max |x| over the sample, shift = 62 - ceil(log2(points)); the sum of all members cannot
 // overflow and the resolution is s * 2^-shift (2^-38 s for 16 M points).
 #include "codeword.h"
+#include <type_traits>
 
 // One atomic per workgroup at most, and only if the workgroup has something larger to report than what is
 // there already: an atomic per wave on the one address took 0.20 ms for a sample of 16 MB.
@@ -231,6 +232,22 @@ __global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restric
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) out[i] = img[i];
 }
 
+// the mean of the middle two of four finite values (halves are added, so that nothing overflows)
+__device__ __forceinline__ float middle_of_four(float a, float b, float c, float d)
+{
+    return 0.5f * fmaxf(fminf(a, b), fminf(c, d)) + 0.5f * fminf(fmaxf(a, b), fmaxf(c, d));
+}
+// the same over four lanes, those that the two steps reach
+template <int STEP1, int STEP2>
+__device__ __forceinline__ float middle_of_lanes(float v)
+{
+    auto from = [](float x, auto step) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(step)::value, 0xF, 0xF, true));
+    };
+    const float w = from(v, std::integral_constant<int, STEP1>{}), lo = fminf(v, w), hi = fmaxf(v, w);
+    return 0.5f * fmaxf(lo, from(lo, std::integral_constant<int, STEP2>{})) + 0.5f * fminf(hi, from(hi, std::integral_constant<int, STEP2>{}));
+}
+
 // The same iteration for up to 256 centroids with the nearest one from the matrix cores (codeword.h), 64 vectors a
 // wave.  262 144 x 16 against 256 centroids: 73 us with the lanes' walk over the centroids, 46 so (66 with
 // the centroids read from their rows): the products 14, the rest loads and the LDS additions of the sums.
@@ -256,35 +273,26 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
         for (int d = 0; d < DS; ++d) ct[d * LLOYD_CT + tid] = tid < k ? C[(int64_t)tid * DS + d] : 0.f;
     }
     __syncthreads();
-    // The point: component by component a value with three to five eighths of the centroids below it.  (The mean would do as
-    // well, but for a centroid far from the others, which takes it along.)
+    // The point: component by component the mean of the middle two of four values, of four such means, and so on over all
+    // centroids (from k on they begin anew).  The plain mean would do as well, but for centroids far from the others, which take
+    // it along; a median by bisection is 1 us an iteration slower.
     for (int d = wave; d < DS; d += LLOYD_NT / 64) {
-        uint32_t o[4], lo = 0xFFFFFFFFu, hi = 0;
-        int there = 0;
+        float v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float v = ct[d * LLOYD_CT + lane + 64 * j];
-            const bool in = lane + 64 * j < k && fabsf(v) < INFINITY;
-            there += __popcll(__ballot(in));
-            o[j] = in ? f2ord(v) : 0xFFFFFFFFu;
-            lo = min(lo, o[j]);
-            hi = max(hi, in ? o[j] : 0u);
+            int t = lane + 64 * j;
+            t -= t >= k ? k : 0;
+            t -= t >= k ? k : 0; // (k >= 96)
+            v[j] = ct[d * LLOYD_CT + t];
+            if (!(fabsf(v[j]) < INFINITY)) v[j] = 0.f;
         }
-        lo = wave_min_u32(lo);
-        hi = wave_max_u32(hi);
-        while (lo < hi) {
-            const uint32_t mid = lo + ((hi - lo + 1) >> 1);
-            int below = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) below += __popcll(__ballot(o[j] < mid));
-            if (8 * below > 5 * there) {
-                hi = mid - 1;
-                continue;
-            }
-            lo = mid;
-            if (8 * below >= 3 * there) break;
-        }
-        if (lane == 0) mu[d] = there ? ord2f(lo) : 0.f;
+        float m = middle_of_four(v[0], v[1], v[2], v[3]);
+        m = middle_of_lanes<0xB1, 0x4E>(m);   // quad_perm [1, 0, 3, 2] and [2, 3, 0, 1]: the four lanes of a quad
+        m = middle_of_lanes<0x141, 0x140>(m); // row_half_mirror and row_mirror: the four quads of a row
+        const int mi = __float_as_int(m);
+        m = middle_of_four(__int_as_float(__builtin_amdgcn_readlane(mi, 0)), __int_as_float(__builtin_amdgcn_readlane(mi, 16)),
+                           __int_as_float(__builtin_amdgcn_readlane(mi, 32)), __int_as_float(__builtin_amdgcn_readlane(mi, 48)));
+        if (lane == 0) mu[d] = m;
     }
     __syncthreads();
     if (tid < 256) {
