@@ -898,7 +898,8 @@ __global__ __launch_bounds__(1024) void k_small_cells(const float *__restrict__ 
     const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x;
     const int G = (k + SMALL_ROWS - 1) / SMALL_ROWS; // <= 1 024
     const float *drow = dist + (int64_t)row * k;
-    const uint32_t mymin = tid < G ? f2ord(gmin[(int64_t)row * G + tid]) : 0xFFFFFFFFu;
+    // (the largest pattern stands for no group; a NaN can have it as well and goes by the one below)
+    const uint32_t mymin = tid < G ? min(f2ord(gmin[(int64_t)row * G + tid]), 0xFFFFFFFEu) : 0xFFFFFFFFu;
     mins[tid] = mymin;
     if (tid == 0) {
         sh_n = 0;
@@ -910,8 +911,8 @@ __global__ __launch_bounds__(1024) void k_small_cells(const float *__restrict__ 
 #pragma unroll
         for (int e = 0; e < 16; ++e) u[e] = mins[lane + 64 * e];
         // (fewer groups than cells wanted: every group is looked at)
-        const uint32_t result = w > G ? 0xFFFFFFFEu : wave_kth(u, w);
-        if (lane == 0) sh_tau = result;
+        const uint32_t kth = w > G ? 0u : wave_kth(u, w);
+        if (lane == 0) sh_tau = w > G ? 0xFFFFFFFEu : (kth == 0xFFFFFFFEu ? 0xFFFFFFFFu : kth);
     }
     __syncthreads();
     const uint32_t tau = sh_tau;

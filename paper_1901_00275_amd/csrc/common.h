@@ -111,8 +111,7 @@ __device__ __forceinline__ uint32_t wave_cut(const uint32_t (&o)[N], uint32_t lo
     return lo + 1;
 }
 
-// The need-th smallest of a wave's values (1-based).  0xFFFFFFFF stands for no value, and is the answer where fewer than
-// `need` are there (the ordered pattern of a NaN can be that, too).
+// The need-th smallest of a wave's values (1-based); 0xFFFFFFFF stands for no value, at least `need` are there.
 template <int N>
 __device__ __forceinline__ uint32_t wave_kth(const uint32_t (&o)[N], int need)
 {
@@ -124,13 +123,9 @@ __device__ __forceinline__ uint32_t wave_kth(const uint32_t (&o)[N], int need)
     }
     const uint32_t cut = wave_cut(o, wave_min_u32(lo), wave_max_u32(hi), need);
     uint32_t v = 0;
-    int below = 0;
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-        v = max(v, o[j] < cut ? o[j] : 0u);
-        below += __popcll(__ballot(o[j] < cut));
-    }
-    return below < need ? 0xFFFFFFFFu : wave_max_u32(v);
+    for (int j = 0; j < N; ++j) v = max(v, o[j] < cut ? o[j] : 0u);
+    return wave_max_u32(v);
 }
 
 // Orders the LDS traffic of one wave across its lanes: what any lane wrote before is what every lane reads behind.
