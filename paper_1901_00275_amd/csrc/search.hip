@@ -428,11 +428,13 @@ __global__ __launch_bounds__(256) void k_subregions(const float *__restrict__ Q,
 // counted with ballots and the four wave counts meet in LDS (one barrier a round); it ends with the first
 // value that has w2 keys below it (bit by bit from the top it took 32 rounds).  Only where scores are
 // equal at the cut are they separated by label.  w1 = 64, n = 32: one query 17 -> 12 us with the bisection, 10 with the
-// 16-byte loads; 10 000 queries 137 -> 124 -> 100 us; n = 64: 267 -> 250 -> 224 us.  The selected sub-regions keep the order of
-// their positions (nearer cells first, which tightens the scan's bound early).
+// 16-byte loads; 10 000 queries 137 -> 124 -> 100 us; n = 64: 263 us bit by bit, 211 with both.  With 16 keys a thread the 16-byte loads
+// took registers for three waves a SIMD only; asked for four, it is 175 us, and n = 50 (no 16-byte loads) 215
+// (258 with three, 237 bit by bit).  The selected sub-regions keep the order of their positions (nearer cells first,
+// which tightens the scan's bound early).
 // ---------------------------------------------------------------------------
 template <int KPT>
-__global__ __launch_bounds__(256) void k_subregions_lean(const float *__restrict__ E, int n,
+__global__ __launch_bounds__(256, 4) void k_subregions_lean(const float *__restrict__ E, int n,
                                                          const int32_t *__restrict__ cells,
                                                          const float *__restrict__ cell_dist, int w1, int w2,
                                                          float lam_min, float lam_max,
