@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m", [8, 16])
 @pytest.mark.parametrize("N,spread,K", [(0, 1, 5), (1, 1, 3), (90, 1, 128), (700, 1, 100), (700, 9, 127), (1500, 0, 128), (5000, 9, 1),
-                                        (5000, 2, 8), (5000, 40, 9), (30_000, 1, 128), (30_000, 300, 100), (30_000, 0, 10)])
+                                        (5000, 2, 8), (5000, 40, 9), (900, 300, 128), (1000, 0, 120),
+                                        (1000, 40, 128), (30_000, 1, 128), (30_000, 300, 100), (30_000, 0, 10)])
 def test_ties_and_order(m, N, spread, K):
     import paper_1901_00275_amd as vlq
 
