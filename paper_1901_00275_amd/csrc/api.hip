@@ -743,19 +743,17 @@ extern "C" int vlq_index_finalize(vlq_index_t *idx, void *stream)
     Bump plan(nullptr);
     plan.take<int32_t>((size_t)nl);
     plan.take<int32_t>((size_t)nl);
+    plan.take<int32_t>(MAX_LONG + 4);
     plan.take<int32_t>(MAX_LONG + 1);
-    plan.take<int32_t>(MAX_LONG + 1);
-    plan.take<int32_t>(3);
     int rc = ws_reserve(idx, plan.off + 256);
     if (rc) return rc;
     Bump b(idx->ws);
     int32_t *cnt = b.take<int32_t>((size_t)nl);
     int32_t *cursor = b.take<int32_t>((size_t)nl);
-    int32_t *longs = b.take<int32_t>(MAX_LONG + 1);
-    int32_t *n_long = longs + MAX_LONG;
+    int32_t *longs = b.take<int32_t>(MAX_LONG + 4);
+    int32_t *n_long = longs + MAX_LONG, *n_work = n_long + 1; // (1 + 3 counters, cleared together)
     int32_t *longs2 = b.take<int32_t>(MAX_LONG + 1);
     int32_t *n_long2 = longs2 + MAX_LONG;
-    int32_t *n_work = b.take<int32_t>(3);
     HIPCHK(hipMemsetAsync(cnt, 0, (size_t)nl * 4, st));
     HIPCHK(hipMemsetAsync(cursor, 0, (size_t)nl * 4, st));
     launch_list_histogram(idx->st_label, N, cnt, st);
@@ -770,8 +768,7 @@ extern "C" int vlq_index_finalize(vlq_index_t *idx, void *stream)
     // still is sorted in global memory, one list at a time.
     std::vector<int64_t> hoff; // host copy of the offsets, fetched only if the third tier is needed
     for (int round = 0; round < 1 << 20; ++round) {
-        HIPCHK(hipMemsetAsync(n_long, 0, 4, st));
-        HIPCHK(hipMemsetAsync(n_work, 0, 12, st));
+        HIPCHK(hipMemsetAsync(n_long, 0, 16, st));
         // (the cursors of the scatter have done their work: theirs is the worklist's place)
         launch_list_sort(idx->off, nl, m, idx->ids, idx->codes, idx->lam, N, longs, n_long, MAX_LONG, cursor, n_work, st);
         LAUNCHCHK();

@@ -279,21 +279,25 @@ __global__ __launch_bounds__(64) void k_list_sort(const int64_t *__restrict__ of
     }
 }
 
-// Lists of few points: 64 of them a workgroup, those of up to 16 points sorted by 16 lanes each, those of up to LS_FEW by the wave,
+// Lists of few points: 4 to 64 of them a workgroup, those of up to 16 points sorted by 16 lanes each, those of up to LS_FEW by the wave,
 // without keys in LDS or barriers (2 M points in 524 288 lists, a workgroup each: 1.90 -> 0.23 ms); longer ones go on the
 // worklist.  (Sorted here as well, one after the other, the lists of a crowded cell, which lie next to each other, kept one
-// wave busy: 2 M points in 2 560 of 1 M lists, finalisation 2.0 -> 6.7 ms.)
+// wave busy: 2 M points in 2 560 of 1 M lists, finalisation 2.0 -> 6.7 ms.)  As few lists a workgroup as give 64 waves a compute unit:
+// 64 lists each are one chain of loads behind the other and leave a small index on a few waves (16 384 lists of 4 points, uneven cells:
+// 53 us with 16 lists each, 16 with 4).  Finalisation of 65 536 points in those lists, D/m = 6: a workgroup and a wave a list 222 us, 364 with 64
+// lists a workgroup and the long lists' terms in a launch of their own, 218 now; even cells 211, 166, 154.
 #define LS_SHORT 16 // mean points a list up to which that is done
 #define LS_FEW 64
-__global__ __launch_bounds__(64) void k_list_sort_few(const int64_t *__restrict__ off, int64_t nl, int m,
+#define LS_WAVES 8192 // waves that run at once: 32 a compute unit
+__global__ __launch_bounds__(64) void k_list_sort_few(const int64_t *__restrict__ off, int64_t nl, int per, int m,
                                                       int32_t *__restrict__ ids, uint8_t *__restrict__ codes,
                                                       uint8_t *__restrict__ lam, int32_t *__restrict__ work,
                                                       int32_t *__restrict__ n_work)
 {
     extern __shared__ unsigned char smem[]; // [4][16 (m + 1)], or [64 (m + 1)]
     const int tid = threadIdx.x;
-    const int64_t l0 = (int64_t)blockIdx.x * 64;
-    const int64_t mybeg = off[min(l0 + tid, nl)], mylen = off[min(l0 + tid + 1, nl)] - mybeg;
+    const int64_t l0 = (int64_t)blockIdx.x * per;
+    const int64_t mybeg = off[min(l0 + tid, nl)], mylen = tid < per ? off[min(l0 + tid + 1, nl)] - mybeg : 0;
     const uint64_t more = __ballot(mylen > LS_FEW);
     if (more) {
         int at = 0;
@@ -381,8 +385,10 @@ void launch_list_sort(const int64_t *off, int64_t nl, int m, int32_t *ids, uint8
                            max_long, (const int32_t *)nullptr, (int32_t *)nullptr);
         return;
     }
-    hipLaunchKernelGGL(k_list_sort_few, dim3((unsigned)((nl + 63) / 64)), dim3(64), (size_t)LS_FEW * (m + 1), st, off, nl, m,
-                       ids, codes, lam, work, n_work);
+    int per = 4; // lists a workgroup
+    while (per < 64 && nl > (int64_t)per * 2 * LS_WAVES) per *= 2;
+    hipLaunchKernelGGL(k_list_sort_few, dim3((unsigned)((nl + per - 1) / per)), dim3(64), (size_t)LS_FEW * (m + 1), st, off, nl, per,
+                       m, ids, codes, lam, work, n_work);
     const int64_t most = N / (LS_FEW + 1); // lists on the worklist; more workgroups than run at once are of no use
     if (most > 0)
         hipLaunchKernelGGL(k_list_sort, dim3((unsigned)(most < 4096 ? most : 4096)), dim3(64), smem, st, off, m, ids, codes, lam,
@@ -498,31 +504,28 @@ void launch_long_list_sort_at(int64_t beg, int64_t len, int m, int32_t *ids, uin
 // distance of the data from the origin and would cancel between them in fp32).
 // Summed in fp64 and rounded once.  LPL lanes a list: the edge length c is formed by them together, then they stride over
 // the points, every lane walking the D coordinates of its point (the lanes of a list read the same centroid rows and mean:
-// with a list a wave its number is uniform, and the rows come through scalar loads).  A wave a list where lists hold many points;
-// 16 lanes, four lists a wave, where they are short (2 M points in 524 288 lists: a wave each left 60 of 64 lanes idle:
-// 3.34 -> 0.90 ms).  Sums in the same order either way: the squared edge is added up as 64 lanes do it, a point's
-// terms one after the other.  VEC: D/m a multiple of four, rows on 16 bytes.
-// 16 lanes leave lists of more than LS_FEW points to the second launch, whose waves take the lists on the worklist (n_work[0]
-// of them, handed out through n_work[2] after the first of each wave): the points of a long list would be walked by 16 lanes alone (2 M points in 8 cells
-// of 16 384, finalisation 3.1 -> 4.0 ms; half of them in one list 255 -> 382).
-template <int LPL, bool VEC, bool WORK>
-__global__ __launch_bounds__(256, LPL == 64 ? 4 : 5) void k_list_static(const int64_t *__restrict__ off, int64_t nl, int n, int D, int m,
-                                                     const float *__restrict__ C, const int32_t *__restrict__ S,
-                                                     const float *__restrict__ P, const float *__restrict__ mu,
-                                                     const uint8_t *__restrict__ codes,
-                                                     const uint8_t *__restrict__ lam, double lam_step, float lam_zero,
-                                                     const int32_t *__restrict__ work, int32_t *__restrict__ n_work,
-                                                     float *__restrict__ sx)
+// with a list a wave its number is uniform, and the rows come through scalar loads).  Sums in the same order for every LPL: the
+// squared edge is added up as 64 lanes do it, a point's terms one after the other.  V: components a load takes; D/m is a multiple
+// of it and rows lie on 4 V bytes.
+struct StaticArgs {
+    const int64_t *off;
+    int64_t nl;
+    int n, D, m;
+    const float *C;
+    const int32_t *S;
+    const float *P, *mu;
+    const uint8_t *codes, *lam;
+    double lam_step;
+    float lam_zero;
+    float *sx;
+};
+template <int LPL, int V>
+__device__ __forceinline__ void list_terms(const StaticArgs &a, int64_t l, int64_t beg, int64_t end, int lane)
 {
-    int own = threadIdx.x / LPL;
-    if (LPL == 64) own = __builtin_amdgcn_readfirstlane(own);
-    const int lane = threadIdx.x % LPL;
-    auto list_terms = [&](int64_t l) {
-    const int64_t beg = off[l], end = off[l + 1];
-    if (beg == end || (LPL < 64 && end - beg > LS_FEW)) return;
-    const int i = (int)(l / n);
-    const float *ci = C + (int64_t)i * D;
-    const float *sj = C + (int64_t)S[l] * D;
+    typedef float vec __attribute__((ext_vector_type(V)));
+    const int D = a.D, m = a.m;
+    const float *ci = a.C + (int64_t)(int)(l / a.n) * D;
+    const float *sj = a.C + (int64_t)a.S[l] * D;
     double part[64 / LPL]; // of the lanes lane, lane + LPL, .. of 64
 #pragma unroll
     for (int u = 0; u < 64 / LPL; ++u) {
@@ -542,43 +545,61 @@ __global__ __launch_bounds__(256, LPL == 64 ? 4 : 5) void k_list_static(const in
     const int ds = D / m;
 #pragma unroll 1
     for (int64_t t = beg + lane; t < end; t += LPL) {
-        const double lh = ((double)lam[t] - (double)lam_zero) * lam_step;
+        const double lh = ((double)a.lam[t] - (double)a.lam_zero) * a.lam_step;
         double q2n = 0.0, q12 = 0.0;
-        auto term = [&](float cf, float sf, float mf, float wf) {
-            const double cv = (double)cf, wv = (double)wf;
-            const double q1 = (cv - (double)mf) + lh * ((double)sf - cv);
-            q2n = fma(wv, wv, q2n);
-            q12 = fma(q1, wv, q12);
-        };
         for (int p = 0; p < m; ++p) {
-            const float *w = P + ((int64_t)p * 256 + codes[t * m + p]) * ds;
-            if (VEC) {
-#pragma unroll 4
-                for (int d = 0; d < ds; d += 4) {
-                    const int g = p * ds + d;
-                    const f32x4 c4 = *(const f32x4 *)(ci + g), s4 = *(const f32x4 *)(sj + g), m4 = *(const f32x4 *)(mu + g);
-                    const f32x4 w4 = *(const f32x4 *)(w + d);
+            const float *w = a.P + ((int64_t)p * 256 + a.codes[t * m + p]) * ds;
+#pragma unroll V
+            for (int d = 0; d < ds; d += V) {
+                const int g = p * ds + d;
+                const vec cv4 = *(const vec *)(ci + g), s4 = *(const vec *)(sj + g), m4 = *(const vec *)(a.mu + g);
+                const vec w4 = *(const vec *)(w + d);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) term(c4[e], s4[e], m4[e], w4[e]);
+                for (int e = 0; e < V; ++e) {
+                    const double cv = (double)cv4[e], wv = (double)w4[e];
+                    const double q1 = (cv - (double)m4[e]) + lh * ((double)s4[e] - cv);
+                    q2n = fma(wv, wv, q2n);
+                    q12 = fma(q1, wv, q12);
                 }
-            } else {
-                for (int d = 0; d < ds; ++d) term(ci[p * ds + d], sj[p * ds + d], mu[p * ds + d], w[d]);
             }
         }
-        sx[t] = (float)(q2n + 2.0 * q12 + (lh * lh - lh) * c);
+        a.sx[t] = (float)(q2n + 2.0 * q12 + (lh * lh - lh) * c);
     }
-    };
-    if (WORK) {
-        const int todo = n_work[0], waves = (int)gridDim.x * 4;
-        for (int i = (int)blockIdx.x * 4 + own; i < todo;) {
-            list_terms(work[i]);
+}
+
+// a wave a list: lists of many points
+template <int V>
+__global__ __launch_bounds__(256, 4) void k_list_static(StaticArgs a)
+{
+    const int64_t l = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    if (l >= a.nl) return;
+    const int64_t beg = a.off[l], end = a.off[l + 1];
+    if (beg < end) list_terms<64, V>(a, l, beg, end, threadIdx.x & 63);
+}
+
+// Short lists: 16 lanes each, four a wave (2 M points in 524 288 lists: a wave each left 60 of 64 lanes idle: 3.34 -> 0.90 ms).
+// Lists of more than LS_FEW points are on a worklist (n_work[0] of them, handed out through n_work[2] after the first of each
+// wave) and get a wave each, of the first `blocks` workgroups: their points would be walked by 16 lanes alone (2 M points in 8 cells
+// of 16 384, finalisation 3.1 -> 4.0 ms; half of them in one list 255 -> 382), and behind the short ones, in a launch of their own, the
+// longest list would be waited for with the chip idle.
+template <int V>
+__global__ __launch_bounds__(256, 5) void k_list_static_few(StaticArgs a, const int32_t *__restrict__ work,
+                                                            int32_t *__restrict__ n_work, int blocks)
+{
+    if ((int)blockIdx.x < blocks) {
+        const int todo = n_work[0], waves = blocks * 4, lane = threadIdx.x & 63;
+        for (int i = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64); i < todo;) {
+            const int64_t l = work[i];
+            list_terms<64, V>(a, l, a.off[l], a.off[l + 1], lane);
             if (lane == 0) i = waves + atomicAdd(&n_work[2], 1);
             i = __builtin_amdgcn_readfirstlane(i);
         }
-    } else {
-        const int64_t l = (int64_t)blockIdx.x * (256 / LPL) + own;
-        if (l < nl) list_terms(l); // (whole groups of LPL lanes)
+        return;
     }
+    const int64_t l = (int64_t)((int)blockIdx.x - blocks) * 16 + threadIdx.x / 16;
+    if (l >= a.nl) return; // (whole groups of 16 lanes)
+    const int64_t beg = a.off[l], end = a.off[l + 1];
+    if (beg < end && end - beg <= LS_FEW) list_terms<16, V>(a, l, beg, end, threadIdx.x & 15);
 }
 
 void launch_list_static(const int64_t *off, int64_t nl, int n, int D, int m, const float *C, const int32_t *S,
@@ -586,17 +607,21 @@ void launch_list_static(const int64_t *off, int64_t nl, int n, int D, int m, con
                         float lam_zero, int64_t N, const int32_t *work, int32_t *n_work, float *sx, hipStream_t st)
 {
     if (nl <= 0) return;
-    const bool vec = (D / m) % 4 == 0 && (((uintptr_t)C | (uintptr_t)P | (uintptr_t)mu) % 16) == 0;
-    auto go = [&](auto kern, int64_t blocks, const int32_t *list) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, st, off, nl, n, D, m, C, S, P, mu, codes, lam, lam_step,
-                           lam_zero, list, n_work, sx);
+    const StaticArgs a = {off, nl, n, D, m, C, S, P, mu, codes, lam, lam_step, lam_zero, sx};
+    const uintptr_t rows = (uintptr_t)C | (uintptr_t)P | (uintptr_t)mu;
+    const int v = (D / m) % 4 == 0 && rows % 16 == 0 ? 4 : ((D / m) % 2 == 0 && rows % 8 == 0 ? 2 : 1);
+    auto go = [&](auto kern, auto few) {
+        if (!lists_are_short(nl, N) || nl <= LS_WAVES) { // (up to LS_WAVES a wave each is all there is to run at once)
+            hipLaunchKernelGGL(kern, dim3((unsigned)((nl + 3) / 4)), dim3(256), 0, st, a);
+            return;
+        }
+        const int64_t most = N / (LS_FEW + 1); // lists on the worklist; eight workgroups per compute unit at most
+        const int blocks = (int)(most < 4 * 2048 ? (most + 3) / 4 : 2048);
+        hipLaunchKernelGGL(few, dim3((unsigned)(blocks + (nl + 15) / 16)), dim3(256), 0, st, a, work, n_work, blocks);
     };
-    const int32_t *none = nullptr;
-    if (!lists_are_short(nl, N)) {
-        vec ? go(k_list_static<64, true, false>, (nl + 3) / 4, none) : go(k_list_static<64, false, false>, (nl + 3) / 4, none);
-        return;
+    switch (v) {
+    case 4: go(k_list_static<4>, k_list_static_few<4>); break;
+    case 2: go(k_list_static<2>, k_list_static_few<2>); break;
+    default: go(k_list_static<1>, k_list_static_few<1>); break;
     }
-    vec ? go(k_list_static<16, true, false>, (nl + 15) / 16, none) : go(k_list_static<16, false, false>, (nl + 15) / 16, none);
-    const int64_t most = N / (LS_FEW + 1), blocks = most < 4 * 2048 ? (most + 3) / 4 : 2048; // eight workgroups per compute unit
-    if (most > 0) vec ? go(k_list_static<64, true, true>, blocks, work) : go(k_list_static<64, false, true>, blocks, work);
 }

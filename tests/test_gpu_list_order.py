@@ -74,17 +74,17 @@ def check(m, k, n, N, lists, rng):
         assert np.array_equal(rec(oid[s:e], olam[s:e], ocode[s:e]), rec(ids[mine], lam[mine].astype(np.uint8), codes[mine].astype(np.uint8)))
 
 
-def finalise_time(k, n, cell, edge):
+def finalise_time(k, n, cell, edge, m=8, D=32):
     """Milliseconds of vlq_index_finalize over points in these lists, in random order."""
     import time
 
     import paper_1901_00275_amd as vlq
 
-    m, N = 8, len(cell)
+    N = len(cell)
     g = torch.Generator(device=DEV)
     g.manual_seed(k)
-    C, P = torch.randn(k, 32, generator=g, device=DEV), torch.randn(m, 256, 4, generator=g, device=DEV)
-    idx = vlq.vlq_build_index(vlq.vlq_params_t(32, k, n, m, 0.0, 0.0), C, P)
+    C, P = torch.randn(k, D, generator=g, device=DEV), torch.randn(m, 256, D // m, generator=g, device=DEV)
+    idx = vlq.vlq_build_index(vlq.vlq_params_t(D, k, n, m, 0.0, 0.0), C, P)
     try:
         lam = torch.full((N,), 100, dtype=torch.uint8, device=DEV)
         codes = torch.randint(0, 256, (N, m), generator=g, device=DEV, dtype=torch.uint8)
@@ -123,8 +123,19 @@ def test_a_long_list_among_short_ones_is_no_slower():
     assert finalise_time(16_384, n, cell, edge) < 1.3 * finalise_time(100, n, cell, edge) + empty
 
 
+def test_both_sides_of_the_line_between_short_and_long_lists():
+    """2 048 cells of 8 edges filled unevenly, with 16 points a list on average and with one point more."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    k, n = 2048, 8
+    N = 16 * k * n
+    cell = torch.rand(N + 1, generator=g, device=DEV).pow_(2).mul_(k).to(torch.int32).clamp_(max=k - 1)
+    edge = torch.rand(N + 1, generator=g, device=DEV).pow_(1.3).mul_(n).to(torch.int32).clamp_(max=n - 1)
+    assert finalise_time(k, n, cell[:N], edge[:N], 16, 96) < 1.2 * finalise_time(k, n, cell, edge, 16, 96)
+
+
 @pytest.mark.parametrize("m,ds", [(8, 4), (16, 6), (8, 5)])
-@pytest.mark.parametrize("k", [500, 60])  # 4.3 points a list and 36
+@pytest.mark.parametrize("k", [1200, 500, 60])  # 1.8 points a list, 4.3 and 36; more than 8 192 lists, fewer
 def test_static_terms_of_every_list(m, ds, k):
     """Distances to points of lists of every size class, against fp64: short lists, long ones among them, long ones all."""
     import paper_1901_00275_amd as vlq
