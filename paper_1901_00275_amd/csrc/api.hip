@@ -176,7 +176,7 @@ extern "C" void vlq_index_free(vlq_index_t *idx)
 {
     if (!idx) return;
     (void)hipDeviceSynchronize();
-    void *ptrs[] = {idx->C, idx->cn, idx->P, idx->Pt, idx->E, idx->S, idx->st_label, idx->st_ids, idx->st_lam,
+    void *ptrs[] = {idx->C, idx->cn, idx->P, idx->E, idx->S, idx->st_label, idx->st_ids, idx->st_lam,
                     idx->st_codes, idx->off, idx->ids, idx->codes, idx->lam, idx->sx, idx->ws,
                     idx->Cimg, idx->Chalf, idx->flags, idx->mu, idx->mu_c, idx->Cc};
     for (void *p : ptrs)
@@ -282,8 +282,8 @@ extern "C" int vlq_build_index(const vlq_params_t *params, const float *d_centro
         HIPCHK(hipMalloc(&idx->Cc, (size_t)k * D * 4));
         HIPCHK(hipMalloc(&idx->mu, (size_t)D * 4));
         HIPCHK(hipMalloc(&idx->mu_c, (size_t)D * 4));
-        HIPCHK(hipMalloc(&idx->P, (size_t)256 * D * 4));
-        HIPCHK(hipMalloc(&idx->Pt, (size_t)256 * D * 4));
+        HIPCHK(hipMalloc(&idx->P, (size_t)2 * 256 * D * 4)); // (and Pt: 256 D floats are a multiple of 16 bytes)
+        idx->Pt = idx->P + (size_t)256 * D;
         HIPCHK(hipMalloc(&idx->S, (size_t)k * n * 4));
         HIPCHK(hipMalloc(&idx->E, (size_t)k * n * 4));
         HIPCHK(hipMalloc(&idx->off, ((size_t)k * n + 1) * 8));
