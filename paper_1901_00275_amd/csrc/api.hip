@@ -493,15 +493,16 @@ extern "C" int vlq_kmeans(const float *d_x, int64_t nt, int32_t d, int32_t k, in
         uint32_t *amax;
         HIPCHK(small.get(&part, lloyd_lanes_words(nt, D, k)));
         HIPCHK(small.get(&amax, 64));
-        HIPCHK(hipMemsetAsync(amax, 0, 4, st));
+        int *turns = (int *)amax + 1; // (cleared with it)
+        HIPCHK(hipMemsetAsync(amax, 0, 4 * (1 + LLOYD_TURNS), st));
         launch_absmax(d_x, nt * D, amax, st);
         LAUNCHCHK();
         for (int it = 0; it < iters; ++it) {
-            launch_lloyd_lanes(d_x, nt, D, k, d_centroids, amax, shift, true, part, nullptr, nullptr, st);
+            launch_lloyd_lanes(d_x, nt, D, k, d_centroids, amax, shift, true, part, nullptr, nullptr, turns, st);
             LAUNCHCHK();
         }
         if (d_assign || d_counts) {
-            launch_lloyd_lanes(d_x, nt, D, k, d_centroids, amax, shift, false, part, d_assign, d_counts, st);
+            launch_lloyd_lanes(d_x, nt, D, k, d_centroids, amax, shift, false, part, d_assign, d_counts, turns, st);
             LAUNCHCHK();
         }
         HIPCHK(hipStreamSynchronize(st)); // the temporaries are freed on return

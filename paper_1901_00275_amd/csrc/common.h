@@ -450,9 +450,16 @@ void launch_kmeans_accumulate(const float *X, int64_t nb, int D, const int32_t *
                               int shift, long long *sums, int32_t *cnt, hipStream_t st);
 bool lloyd_lanes_supported(int64_t nt, int D, int k);
 size_t lloyd_lanes_words(int64_t nt, int D, int k); // 64-bit words of `part`
-// One iteration (update), or assignment and counts alone; assign and counts may be NULL (train.hip).
+// What the iterations of a call hand on (train.hip, k_lloyd_cores): for how many more the products are left out, how many that was at
+// first, and the vectors that were compared one by one.
+#define LLOYD_WAIT 0
+#define LLOYD_STEP 1
+#define LLOYD_COMPARED 2
+#define LLOYD_TURNS 3
+// One iteration (update), or assignment and counts alone; assign and counts may be NULL (train.hip).  turns [LLOYD_TURNS]: zero
+// before the first iteration.
 void launch_lloyd_lanes(const float *X, int64_t nt, int D, int k, float *C, const uint32_t *absmax_bits, int shift,
-                        bool update, uint64_t *part, int32_t *assign, int32_t *counts, hipStream_t st);
+                        bool update, uint64_t *part, int32_t *assign, int32_t *counts, int *turns, hipStream_t st);
 void launch_kmeans_update(float *C, int k, int D, const long long *sums, const int32_t *cnt,
                           const uint32_t *absmax_bits, int shift, hipStream_t st);
 

@@ -140,14 +140,12 @@ __device__ __forceinline__ float lloyd_dist(const float (&r)[DS], const float *w
     return s;
 }
 
+// One pass by the walk, of a whole workgroup.
 template <int DS>
-__global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restrict__ X, int64_t nt, int k,
-                                                          const float *__restrict__ C,
-                                                          const uint32_t *__restrict__ absmax_bits, int shift, int want_sums,
-                                                          int vec, unsigned long long *__restrict__ part,
-                                                          int32_t *__restrict__ assign)
+__device__ __forceinline__ void lloyd_lanes(const float *__restrict__ X, int64_t nt, int k, const float *__restrict__ C,
+                                            const uint32_t *__restrict__ absmax_bits, int shift, int want_sums, int vec,
+                                            unsigned long long *__restrict__ part, int32_t *__restrict__ assign, unsigned long long *img)
 {
-    extern __shared__ unsigned long long img[]; // [k][DS + 1]
     const int tid = threadIdx.x;
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) img[i] = 0;
     __syncthreads();
@@ -224,6 +222,17 @@ __global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restric
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) out[i] = img[i];
 }
 
+template <int DS>
+__global__ __launch_bounds__(LLOYD_NT) void k_lloyd_lanes(const float *__restrict__ X, int64_t nt, int k,
+                                                          const float *__restrict__ C,
+                                                          const uint32_t *__restrict__ absmax_bits, int shift, int want_sums,
+                                                          int vec, unsigned long long *__restrict__ part,
+                                                          int32_t *__restrict__ assign)
+{
+    extern __shared__ unsigned long long img[]; // [k][DS + 1]
+    lloyd_lanes<DS>(X, nt, k, C, absmax_bits, shift, want_sums, vec, part, assign, img);
+}
+
 // The nearest of k centroids to the lane's vector, the first of equal ones; 0 where no distance is finite.  (The loop of
 // k_lloyd_lanes.  That kernel has it written out: as a call its scalar registers are copied from batch to batch, and ten
 // iterations of 262 144 x 8, k = 800 take 1 640 us instead of 1 280.)
@@ -288,22 +297,30 @@ __device__ __forceinline__ float middle_of_lanes(float v)
 // The same iteration for up to 256 centroids with the nearest one from the matrix cores (codeword.h), 64 vectors a
 // wave.  262 144 x 16 against 256 centroids: 73 us with the lanes' walk over the centroids, 46 so (66 with
 // the centroids read from their rows): the products 14, the rest loads and the LDS additions of the sums.
+// Where too many vectors are not decided by the products (groups of centroids closer to each other than the products resolve at
+// their distance from the point), they are left out of the next three iterations, then tried again, and left out of fifteen ..: ten
+// iterations of 262 144 vectors in 64 tight groups, k = 256, us, by the walk alone / with the products each time / so: D = 8 615 / 913 /
+// 653, D = 16 1 000 / 1 247 / 1 032.  Every vector gets the same centroid either way.
 #define LLOYD_CT 272 // floats a component: the four that a wave reads at once start 16 banks apart
 template <int DS>
 __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__restrict__ X, int64_t nt, int k,
                                                              const float *__restrict__ C,
                                                              const uint32_t *__restrict__ absmax_bits, int shift, int want_sums,
                                                              int vec, unsigned long long *__restrict__ part,
-                                                             int32_t *__restrict__ assign)
+                                                             int32_t *__restrict__ assign, int *__restrict__ turns)
 {
     extern __shared__ unsigned long long img[]; // [k][DS + 1]
     __shared__ __align__(16) float half[256];
     __shared__ float ct[DS * LLOYD_CT]; // the centroids component by component
     __shared__ float mu[DS];
-    __shared__ int sh_cmax;
+    __shared__ int sh_cmax, sh_compared;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (__builtin_amdgcn_readfirstlane(turns[LLOYD_WAIT]) > 0) {
+        lloyd_lanes<DS>(X, nt, k, C, absmax_bits, shift, want_sums, vec, part, assign, img);
+        return;
+    }
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) img[i] = 0;
-    if (tid == 0) sh_cmax = 0;
+    if (tid == 0) sh_cmax = sh_compared = 0;
     __syncthreads();
     if (tid < 256) {
 #pragma unroll
@@ -348,6 +365,7 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
             for (int d = 0; d < DS; ++d) ct[d * LLOYD_CT + tid] = mu[d]; // (at the largest "norm", and never the nearest)
     }
     __syncthreads();
+    int compared = 0; // vectors of the wave that were compared one by one; the walk takes the time of CODEWORD_OPEN of them
     const float cmax = __uint_as_float((uint32_t)sh_cmax);
     const double f = ldexp(1.0, shift) / scale_of(*absmax_bits);
     const int64_t stride = (int64_t)gridDim.x * LLOYD_NT;
@@ -362,6 +380,7 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
             return lloyd_dist<DS>(r, w);
         };
         auto all = [&](int v) {
+            ++compared;
             uint64_t key = KEY_MAX;
             for (int t = lane; t < k; t += 64) {
                 const float s = exact(v, t);
@@ -374,6 +393,7 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
         auto walk = [&]() {
             float r[DS];
             load_row<DS>(row_of(lane), vec, r);
+            compared += CODEWORD_OPEN;
             return walk_centroids<DS>(C, k, r);
         };
         const int bt = nearest_codeword64<DS>(ct, LLOYD_CT, k, half, cmax, lane, [&](int d) { return mu[d]; },
@@ -393,7 +413,9 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
             if (assign) assign[row] = bt;
         }
     }
+    if (lane == 0 && compared) atomicAdd(&sh_compared, compared);
     __syncthreads();
+    if (tid == 0 && sh_compared) atomicAdd(&turns[LLOYD_COMPARED], sh_compared);
     unsigned long long *out = part + (int64_t)blockIdx.x * k * (DS + 1);
     for (int i = tid; i < k * (DS + 1); i += LLOYD_NT) out[i] = img[i];
 }
@@ -402,10 +424,20 @@ __global__ __launch_bounds__(LLOYD_NT, 4) void k_lloyd_cores(const float *__rest
 // the mean of its members (one without members stays), with counts the number of members is written.
 __global__ __launch_bounds__(256) void k_lloyd_reduce(const unsigned long long *__restrict__ part, int blocks, int k,
                                                       int D, const uint32_t *__restrict__ absmax_bits, int shift,
-                                                      float *__restrict__ C, int32_t *__restrict__ counts)
+                                                      float *__restrict__ C, int32_t *__restrict__ counts,
+                                                      int64_t most, int *__restrict__ turns)
 {
     __shared__ unsigned long long sum[256];
     const int tid = threadIdx.x, c = blockIdx.x;
+    if (turns && c == 0 && tid == 0) {
+        if (turns[LLOYD_WAIT] > 0) {
+            --turns[LLOYD_WAIT];
+        } else {
+            turns[LLOYD_STEP] = turns[LLOYD_COMPARED] > most ? min(4 * turns[LLOYD_STEP] + 3, 1 << 20) : 0;
+            turns[LLOYD_WAIT] = turns[LLOYD_STEP];
+        }
+        turns[LLOYD_COMPARED] = 0;
+    }
     const int E = D + 1, slices = 256 / E;
     const int e = tid % E, sl = tid / E;
     unsigned long long s = 0;
@@ -449,17 +481,17 @@ static int lloyd_blocks(int64_t nt)
 size_t lloyd_lanes_words(int64_t nt, int D, int k) { return (size_t)lloyd_blocks(nt) * k * (D + 1); }
 
 void launch_lloyd_lanes(const float *X, int64_t nt, int D, int k, float *C, const uint32_t *absmax_bits, int shift,
-                        bool update, uint64_t *part, int32_t *assign, int32_t *counts, hipStream_t st)
+                        bool update, uint64_t *part, int32_t *assign, int32_t *counts, int *turns, hipStream_t st)
 {
     const int blocks = lloyd_blocks(nt);
     const int vec = ((uintptr_t)X) % 16 == 0;
     const size_t lds = (size_t)k * (D + 1) * 8;
-    auto go = [&](auto kern) {
+    auto go = [&](auto kern, auto... more) {
         if (lds > 49152 && // (48 KB of dynamic LDS need no asking)
             hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return; // (the caller asks for the error)
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(LLOYD_NT), lds, st, X, nt, k, (const float *)C, absmax_bits,
-                           shift, update ? 1 : 0, vec, (unsigned long long *)part, assign);
+                           shift, update ? 1 : 0, vec, (unsigned long long *)part, assign, more...);
     };
     // The products' fixed cost (norms, direct distances of four centroids a vector) against the walk, ten iterations of
     // 262 144 vectors, us: D = 16, k = 256 780 and 1 112; D = 6, k = 256 599 and 1 129; D = 4, k = 256 459 and 470; D = 8, k = 64
@@ -467,12 +499,15 @@ void launch_lloyd_lanes(const float *X, int64_t nt, int D, int k, float *C, cons
     const bool cores = k <= 256 && k * D >= 1536;
     switch (D) {
     case 4: go(k_lloyd_lanes<4>); break;
-    case 6: cores ? go(k_lloyd_cores<6>) : go(k_lloyd_lanes<6>); break;
-    case 8: cores ? go(k_lloyd_cores<8>) : go(k_lloyd_lanes<8>); break;
-    case 12: cores ? go(k_lloyd_cores<12>) : go(k_lloyd_lanes<12>); break;
-    default: cores ? go(k_lloyd_cores<16>) : go(k_lloyd_lanes<16>); break;
+    case 6: cores ? go(k_lloyd_cores<6>, turns) : go(k_lloyd_lanes<6>); break;
+    case 8: cores ? go(k_lloyd_cores<8>, turns) : go(k_lloyd_lanes<8>); break;
+    case 12: cores ? go(k_lloyd_cores<12>, turns) : go(k_lloyd_lanes<12>); break;
+    default: cores ? go(k_lloyd_cores<16>, turns) : go(k_lloyd_lanes<16>); break;
     }
+    // From so many comparisons one by one a batch on the walk alone is as fast: an iteration of 262 144 vectors, k = 256, the walk and the
+    // products with none of them, us: D = 6 50 and 46, D = 8 54 and 49, D = 12 80 and 56, D = 16 92 and 65.
+    const int64_t most = (D < 12 ? 3 : 14) * ((nt + 63) / 64);
     if (update || counts)
         hipLaunchKernelGGL(k_lloyd_reduce, dim3((unsigned)k), dim3(256), 0, st, (const unsigned long long *)part, blocks, k,
-                           D, absmax_bits, shift, update ? C : nullptr, counts);
+                           D, absmax_bits, shift, update ? C : nullptr, counts, most, cores ? turns : nullptr);
 }

@@ -133,15 +133,16 @@ def test_far_centroids(D, k, far, times):
     assert np.array_equal(assigned(X, C), nearest(X, C))
 
 
-def time_of(X, C):
+def time_of(X, C, iters=0):
     import paper_1901_00275_amd as vlq
 
     best, a = np.inf, torch.empty(len(X), dtype=torch.int32, device=DEV)
     for _ in range(8):
         s, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start = C.clone()
         torch.cuda.synchronize()
         s.record()
-        vlq.vlq_kmeans(X, len(X), X.shape[1], len(C), 0, C, a, None)
+        vlq.vlq_kmeans(X, len(X), X.shape[1], len(C), iters, start, a, None)
         e.record()
         e.synchronize()
         best = min(best, s.elapsed_time(e))
@@ -175,3 +176,34 @@ def test_codebooks_without_use_for_the_products(kind):
     else:
         C[:] = X[0]
     assert time_of(X, C) < 1.2 * time_of(X, X[:264].clone())
+
+
+def tight_groups(D, k, nt):
+    """Vectors in k / 4 groups that are far narrower than their distance from each other, so that the products decide nothing."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + k)
+    X = 10 * torch.randn(k // 4, D, generator=g, device=DEV)[torch.randint(0, k // 4, (nt,), generator=g, device=DEV)]
+    return X + 0.01 * torch.randn(nt, D, generator=g, device=DEV)
+
+
+@pytest.mark.parametrize("D,k,nt", [(6, 256, 4100), (8, 255, 4100), (12, 128, 33_000), (16, 256, 4100)])
+def test_iterations_of_one_call_and_of_many(D, k, nt):
+    """The iterations that leave the products out give what those with them do."""
+    import paper_1901_00275_amd as vlq
+
+    X = tight_groups(D, k, nt)
+    one, many = X[:k].clone(), X[:k].clone()
+    assign, counts = torch.empty(nt, dtype=torch.int32, device=DEV), torch.empty(k, dtype=torch.int32, device=DEV)
+    vlq.vlq_kmeans(X, nt, D, k, 7, one, assign, counts)
+    for _ in range(7):
+        vlq.vlq_kmeans(X, nt, D, k, 1, many, None, None)
+    assert torch.equal(one, many)
+    want = nearest(X.cpu().numpy(), many.cpu().numpy())
+    assert np.array_equal(assign.cpu().numpy(), want)
+    assert np.array_equal(counts.cpu().numpy(), np.bincount(want, minlength=k))
+
+
+def test_groups_that_the_products_do_not_tell_apart():
+    """256 centroids, which the products serve, against 257, which they do not."""
+    X = tight_groups(8, 256, 262_144)
+    assert time_of(X, X[:256], 10) < 1.3 * time_of(X, X[:257], 10)
