@@ -441,9 +441,10 @@ static int launch_mode(Bf16Args &a, hipStream_t st)
 // A query whose list overflows (masses of coinciding distances) is ranked exactly over all
 // columns instead.
 // ---------------------------------------------------------------------------
-// tau = the want-th smallest of the G group minima of a row, found bit by bit from the top of the
-// ordered bit patterns: a wave per row, every trial value is compared with all minima and the lanes
-// that lie below are counted with ballots (scalar work, no sorting, no barriers).
+// tau = the want-th smallest of the G group minima of a row: a wave per row, by bisection between the smallest and the largest
+// ordered bit pattern (wave_kth), every trial value compared with all minima and the lanes that lie below counted with ballots
+// (scalar work, no sorting, no barriers).  Only rows of more than 4 096 minima, which do not fit the registers, are still searched
+// bit by bit from the top.
 // (The hi-only sweeps carry their own, wider error inside the values they compare; the band added here is that
 // of the fp32 arithmetic and of the split product, which the hi-only bound exceeds by far.)
 __global__ __launch_bounds__(256) void k_cell_threshold(const float *__restrict__ gmin, int G, int want, int nq,

@@ -33,7 +33,7 @@
 // merges and a sort of the result): with few points a query that took more of the LDS pipe than the table lookups
 // (10 000 queries of 4 900 points, K = 100: 20 500 of 27 000 clocks a workgroup, 9 400 now; the scan 452 -> 360 us), and
 // with many it was in the lookups' way (10 000 queries, 1 024 lists of 238 points, m = 16: 8.7 -> 8.3 ms; 512 of 480, m = 8:
-// 4.94 -> 4.90).
+// no difference beyond the noise).
 #include "common.h"
 
 #define SS_NT 512
